@@ -6,7 +6,7 @@
 // channels in chunks of 16.  Operand lane layout of that instruction: lane l
 // holds A[l % 32][8 (l / 32) + 0..7] and B[8 (l / 32) + 0..7][l % 32]; the
 // 16 accumulators of lane l hold D[8 (r / 4) + 4 (l / 32) + r % 4][l % 32].
-// The weight-gradient of those layers is a GEMM with K = pixels on the same
+// The weight gradients of layers 1 to 3 are GEMMs with K = pixels on the same
 // instruction.  Layer 1 (3 -> 32) runs on the same instruction with K = 9
 // taps x 4 channels (channel 3 and taps 9..11 zero) in three chunks.  Layer 4
 // (32 -> 1) is split in two: the layer-3 kernel turns each pixel's 32
@@ -15,8 +15,7 @@
 // y[p] = b4 + sum_tap t[p + off(tap)][tap].  GELU uses the erf
 // approximation 7.1.26 of Abramowitz and Stegun (absolute error <= 1.5e-7,
 // far below the bf16 rounding of the activations), branch-free.  Layer 4's
-// backward-data and the weight gradients of layers 1 and 4 run on the vector
-// ALUs.  Every kernel indexes only inside
+// backward pass runs on the vector ALUs.  Every kernel indexes only inside
 // the buffers described in zk_cnn.hpp for the geometry it is given (checked
 // by the host before launch); periodic wrap-around adds or subtracts one
 // period (every offset is a single pixel).
@@ -138,10 +137,9 @@ constexpr int kRing = 4;
 constexpr int kFetch = (kLdsPx * 4 + 255) / 256;  // 16-byte pieces of a ring row per thread
 
 // Modes: forward (out = bf16(GELU(z)), z optional); forward of the last
-// hidden layer, which also (or only: out may be null) writes layer 4's
-// per-tap partial sums taps[p][12] (taps 0..8; the bf16 activations of the
-// lane's 16 channels are the B operand of two MFMAs against W4, its rows the
-// taps); backward-data (out = bf16(conv'(din) * GELU'(zprev))).
+// hidden layer, which writes layer 4's per-tap partial sums taps[p][12] (taps
+// 0..8; the bf16 activations of the lane's 16 channels are the B operand of
+// two MFMAs against W4, its rows the taps) in place of out; backward-data (out = bf16(conv'(din) * GELU'(zprev))).
 enum ConvMode { kFwd = 0, kFwdTaps = 1, kBwd = 2 };
 
 template <int MODE>
@@ -236,7 +234,7 @@ __global__ __launch_bounds__(256) void conv32_kernel(const uint16_t *__restrict_
         u16x4 o;
 #pragma unroll
         for (int k = 0; k < 4; ++k) o[k] = f2bf(v[k]);
-        if (MODE != kFwdTaps || out) *reinterpret_cast<u16x4 *>(out + pix * CH + c0) = o;
+        if constexpr (MODE != kFwdTaps) *reinterpret_cast<u16x4 *>(out + pix * CH + c0) = o;
         if constexpr (MODE == kFwdTaps) {
 #pragma unroll
           for (int k = 0; k < 4; ++k) act[g / 2][4 * (g % 2) + k] = o[k];
@@ -302,191 +300,350 @@ __global__ __launch_bounds__(256) void loss_kernel(const float *__restrict__ y, 
   if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
 }
 
-// ---- layer 4 backward-data: dz3 = (W4^T dz4) * GELU'(z3) ---------------------------
-__global__ __launch_bounds__(256) void conv4_bwd_kernel(const uint16_t *__restrict__ dz4, const float *__restrict__ w4f,
-                                                        const float *__restrict__ z3, uint16_t *__restrict__ dz3, int H,
-                                                        int W, long long P) {
-  __shared__ float w[9 * CH];
-  for (int i = threadIdx.x; i < 9 * CH; i += 256) w[i] = w4f[i];
-  __syncthreads();
-  const long long p = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (p >= P) return;
-  const int x = (int)(p % W);
-  const long long r = p / W;
-  const int yy0 = (int)(r % H);
-  const long long b = r / H;
-  float d[9];
+// ---- layer 4 backward: dz3 = (W4^T dz4) * GELU'(z3) and dW4, db4 -----------------------
+// One pass over z3 serves both: pixel p's neighbours d[t] = dz4[p - off(t)]
+// that backward-data weights with W4 are also the factors of its activations
+// a3[p] in dW4[c][t] = sum_p a3[p][c] d[t], and a3 = bf16(GELU(z3)) comes from
+// the same normal CDF as GELU'(z3), so the forward pass stores no a3.  Thread:
+// 4 channels of every 128 gridDim.x-th pixel, its 36 weights and 36 sums in
+// registers.  Bounded by memory (128 B read, 64 B written a pixel): 23 us at 16
+// x 128 x 128 pixels, where backward-data alone took 23 us and a weight-gradient
+// kernel with one channel and tap a thread 420 us.
+constexpr int kL4Threads = 1024;
+__global__ __launch_bounds__(kL4Threads) void conv4_bwd_kernel(const uint16_t *__restrict__ dz4,
+                                                               const float *__restrict__ w4f,
+                                                               const float *__restrict__ z3,
+                                                               uint16_t *__restrict__ dz3, float *__restrict__ part,
+                                                               int H, int W, int P) {
+  constexpr int NWV = kL4Threads / 64;
+  __shared__ float red[NWV][PART4];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int c0 = 4 * (tid & 7);
+  float w[9][4], acc[9][4], accb = 0.f;
 #pragma unroll
-  for (int t = 0; t < 9; ++t) {  // output pixel q - (u-1, v-1) read this pixel through tap (u, v)
-    const int yy = wrap(yy0 - t / 3 + 1, H), xx = wrap(x - t % 3 + 1, W);
-    d[t] = bf2f(dz4[(b * H + yy) * W + xx]);
-  }
+  for (int t = 0; t < 9; ++t)
 #pragma unroll
-  for (int c0 = 0; c0 < CH; c0 += 4) {
-    const float4 zp = *reinterpret_cast<const float4 *>(z3 + p * CH + c0);
+    for (int k = 0; k < 4; ++k) {
+      w[t][k] = w4f[t * CH + c0 + k];
+      acc[t][k] = 0.f;
+    }
+  for (int p = blockIdx.x * (kL4Threads / 8) + (tid >> 3); p < P; p += gridDim.x * (kL4Threads / 8)) {
+    const int r = p / W, x = p - r * W;
+    const int y = r % H, row0 = r - y;  // row0: first row of the image, in rows
+    const float4 zp = *reinterpret_cast<const float4 *>(z3 + (long long)p * CH + c0);
     const float zz[4] = {zp.x, zp.y, zp.z, zp.w};
+    float d[9];
+#pragma unroll
+    for (int t = 0; t < 9; ++t)  // output pixel p - (u-1, v-1) read this pixel through tap (u, v)
+      d[t] = bf2f(dz4[(long long)(row0 + wrap(y - t / 3 + 1, H)) * W + wrap(x - t % 3 + 1, W)]);
+    accb += d[4];
     u16x4 o;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
+      float e;
+      const float cdf = norm_cdf(zz[k], e);
+      const float a = bf2f(f2bf(zz[k] * cdf));
       float s = 0.f;
 #pragma unroll
-      for (int t = 0; t < 9; ++t) s += w[t * CH + c0 + k] * d[t];
-      o[k] = f2bf(s * gelu_d(zz[k]));
+      for (int t = 0; t < 9; ++t) {
+        s += w[t][k] * d[t];
+        acc[t][k] += a * d[t];
+      }
+      o[k] = f2bf(s * fmaf(zz[k] * 0.39894228040143268f, e, cdf));
     }
-    *reinterpret_cast<u16x4 *>(dz3 + p * CH + c0) = o;
+    *reinterpret_cast<u16x4 *>(dz3 + (long long)p * CH + c0) = o;
+  }
+  // the wavefront's 8 pixels, then the block's wavefronts, in a fixed order
+#pragma unroll
+  for (int t = 0; t < 9; ++t)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      float v = acc[t][k];
+      v += __shfl_xor(v, 8);
+      v += __shfl_xor(v, 16);
+      v += __shfl_xor(v, 32);
+      if (lane < 8) red[wv][t * CH + c0 + k] = v;
+    }
+  accb += __shfl_xor(accb, 8);
+  accb += __shfl_xor(accb, 16);
+  accb += __shfl_xor(accb, 32);
+  if (lane == 0) red[wv][9 * CH] = accb;
+  __syncthreads();
+  if (tid < NW4 + NB4) {
+    float v = 0.f;
+    for (int k = 0; k < NWV; ++k) v += red[k][tid];
+    part[(long long)blockIdx.x * kPartSlots + SLOT4 + tid] = v;
   }
 }
 
-// ---- weight gradients of layers 4 and 1 (vector ALUs) --------------------------------
-// Thread t owns channel t % 32 and taps t / 32 (and tap 8 for t < 32); each
-// block sums a contiguous chunk of pixels.
-__global__ __launch_bounds__(256) void dw4_kernel(const uint16_t *__restrict__ dz4, const uint16_t *__restrict__ a3,
-                                                  float *__restrict__ part, int H, int W, long long P) {
-  const int c = threadIdx.x & 31, g = threadIdx.x >> 5;
-  const long long chunk = (P + gridDim.x - 1) / gridDim.x;
-  const long long p0 = (long long)blockIdx.x * chunk, p1 = min(P, p0 + chunk);
-  float acc0 = 0.f, acc8 = 0.f, accb = 0.f;
-  for (long long p = p0; p < p1; ++p) {
-    const float d = bf2f(dz4[p]);
-    const int x = (int)(p % W);
-    const long long r = p / W;
-    const int y = (int)(r % H);
-    const long long b = r / H;
-    {
-      const int yy = wrap(y + g / 3 - 1, H), xx = wrap(x + g % 3 - 1, W);
-      acc0 += d * bf2f(a3[((b * H + yy) * W + xx) * CH + c]);
-    }
-    if (g == 0) {
-      const int yy = wrap(y + 1, H), xx = wrap(x + 1, W);  // tap 8 = (2, 2)
-      acc8 += d * bf2f(a3[((b * H + yy) * W + xx) * CH + c]);
-      accb += d;
-    }
-  }
-  float *o = part + (long long)blockIdx.x * (NW4 + NB4);
-  o[c * 9 + g] = acc0;
-  if (g == 0) o[c * 9 + 8] = acc8;
-  if (threadIdx.x == 0) o[NW4] = accb;
+// ---- weight gradients of layers 1, 2 and 3 on MFMA --------------------------------------
+// dW[o][c][tap] = sum_p dz[p][o] in[p + off(tap)][c]: M = o, K = pixels,
+// 16 at a time.  Both operands want 8 consecutive pixels of one channel per
+// lane while memory holds pixels of 32 channels, so a wavefront copies its
+// rows to LDS as they are (no transposing stores) and gathers an operand with
+// 16-bit reads, 32 channels of one pixel a half wavefront: with 72 bytes a
+// pixel the two halves (8 pixels apart) fall on different banks.  The three
+// horizontal taps of a row are windows of the same 10 pixels, so a chunk of 16
+// pixels takes 8 + 30 reads for 9 products.  A wavefront owns a strip of
+// kSegPx pixels and walks down its rows with a ring of three input rows (the
+// next row in registers), all in LDS of its own: no block barrier until the
+// block sums its wavefronts' results.  At 16 x 128 x 128 pixels layers 2 and
+// 3 take 19 us each (66 us with a block staging transposed copies by 2-byte
+// stores behind two barriers a segment), layer 1 8.4 us (420 us on the vector
+// ALUs); the bytes they read take 10 and 4 us.
+constexpr int kDwWaves = 8;               // wavefronts per block
+constexpr int kDwStride = 36;             // uint16 per pixel in LDS
+constexpr int kDwPx = kSegPx + 2;         // pixels of an input row in LDS
+constexpr int kDwFewestRows = 4;          // rows a wavefront walks at least
+
+// Rows y0 .. y0 + nrows - 1 of one strip.
+struct DwStrip {
+  int b, y0, nrows, x0;
+};
+__device__ __forceinline__ DwStrip dw_strip(int item, int bands, int rows, int H, int W) {
+  const int segs = W / kSegPx, s = item / bands, y0 = (item - s * bands) * rows;
+  return {s / segs, y0, min(rows, H - y0), (s % segs) * kSegPx};
+}
+// Wavefront-private LDS: its operations complete in order.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+__device__ __forceinline__ void put_pixel(uint16_t *dst, u16x8 v) {  // 8-byte aligned
+  *reinterpret_cast<u16x4 *>(dst) = u16x4{v[0], v[1], v[2], v[3]};
+  *reinterpret_cast<u16x4 *>(dst + 4) = u16x4{v[4], v[5], v[6], v[7]};
 }
 
-__global__ __launch_bounds__(256) void dw1_kernel(const uint16_t *__restrict__ dz1, const uint16_t *__restrict__ xin,
-                                                  float *__restrict__ part, int H, int W, long long P) {
-  const int co = threadIdx.x & 31, g = threadIdx.x >> 5;
-  const long long chunk = (P + gridDim.x - 1) / gridDim.x;
-  const long long p0 = (long long)blockIdx.x * chunk, p1 = min(P, p0 + chunk);
-  float a0[3] = {0.f, 0.f, 0.f}, a8[3] = {0.f, 0.f, 0.f}, accb = 0.f;
-  for (long long p = p0; p < p1; ++p) {
-    const float d = bf2f(dz1[p * CH + co]);
-    const int x = (int)(p % W);
-    const long long r = p / W;
-    const int y = (int)(r % H);
-    const long long b = r / H;
-    {
-      const int yy = wrap(y + g / 3 - 1, H), xx = wrap(x + g % 3 - 1, W);
-      const u16x4 v = *reinterpret_cast<const u16x4 *>(xin + ((b * H + yy) * W + xx) * 4);
-#pragma unroll
-      for (int ci = 0; ci < 3; ++ci) a0[ci] += d * bf2f(v[ci]);
-    }
-    if (g == 0) {
-      const int yy = wrap(y + 1, H), xx = wrap(x + 1, W);
-      const u16x4 v = *reinterpret_cast<const u16x4 *>(xin + ((b * H + yy) * W + xx) * 4);
-#pragma unroll
-      for (int ci = 0; ci < 3; ++ci) a8[ci] += d * bf2f(v[ci]);
-      accb += d;
-    }
-  }
-  float *o = part + (long long)blockIdx.x * (NW1 + NB1);
-#pragma unroll
-  for (int ci = 0; ci < 3; ++ci) o[(co * 3 + ci) * 9 + g] = a0[ci];
-  if (g == 0) {
-#pragma unroll
-    for (int ci = 0; ci < 3; ++ci) o[(co * 3 + ci) * 9 + 8] = a8[ci];
-    o[NW1 + co] = accb;
-  }
-}
-
-// ---- weight gradient of layers 2, 3 on MFMA -----------------------------------------
-// dW[o][c][tap] = sum_p dz[p][o] a[p + off(tap)][c]: M = o, N = c, K = the
-// 64 pixels of one row segment.  The segment's dz and the three shifted
-// copies of the three activation rows are staged transposed in LDS
-// (channel-major, pixels contiguous), so each operand is one 16-byte read.
-constexpr int kTS = kSegPx + 8;  // uint16 stride of a transposed LDS row
-
-__global__ __launch_bounds__(256) void dw32_kernel(const uint16_t *__restrict__ dz, const uint16_t *__restrict__ act,
-                                                   float *__restrict__ part, int B, int H, int W) {
-  __shared__ __attribute__((aligned(16))) uint16_t dzT[CH * kTS];
-  __shared__ __attribute__((aligned(16))) uint16_t aT[9][CH * kTS];  // [u * 3 + shift][c][px]
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+__global__ __launch_bounds__(64 * kDwWaves) void dw32_kernel(const uint16_t *__restrict__ dz,
+                                                            const uint16_t *__restrict__ act,
+                                                            float *__restrict__ part, int slot0, int items, int bands,
+                                                            int rows, int H, int W) {
+  constexpr int ROW = kDwPx * kDwStride, LDS1 = 3 * ROW + kSegPx * kDwStride;  // uint16 per wavefront
+  __shared__ __attribute__((aligned(16))) uint16_t smem[kDwWaves * LDS1];
+  static_assert(kDwWaves * LDS1 * 2 >= (kDwWaves / 2) * 9 * 1024 * 4, "the final sums fit");
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 31, half = lane >> 5;
-  f32x16 acc[3] = {{}, {}, {}};
+  uint16_t *ring = smem + wv * LDS1, *dzs = ring + 3 * ROW;
+  f32x16 acc[9] = {};
   float accb = 0.f;
-  const int segs_row = W / kSegPx;
-  const long long nseg = (long long)B * H * segs_row;
-  for (long long s = blockIdx.x; s < nseg; s += gridDim.x) {
-    const int xs = (int)(s % segs_row);
-    const long long r = s / segs_row;
-    const int y = (int)(r % H);
-    const long long b = r / H;
-    const int x0 = xs * kSegPx;
-    {
-      const int p = tid >> 2, q = tid & 3;  // 64 pixels x 4 chunks of 8 channels
-      const u16x8 v = *reinterpret_cast<const u16x8 *>(dz + ((b * H + y) * (long long)W + x0 + p) * CH + 8 * q);
+  for (int item = blockIdx.x + gridDim.x * wv; item < items; item += gridDim.x * kDwWaves) {
+    const DwStrip st = dw_strip(item, bands, rows, H, W);
+    const long long img = (long long)st.b * H;
+    // 16-byte pieces: pixel i / 4, channels 8 (i % 4) ..; an input row holds pixels x0 - 1 .. x0 + kSegPx
+    u16x8 ra[5], rd[4];
+    auto fetch_a = [&](int yy) {
+      const uint16_t *src = act + (img + wrap(yy, H)) * W * CH;
 #pragma unroll
-      for (int k = 0; k < 8; ++k) dzT[(8 * q + k) * kTS + p] = v[k];
-    }
-    for (int i = tid; i < 3 * (kSegPx + 2) * 4; i += 256) {
-      const int u = i / ((kSegPx + 2) * 4), rem = i % ((kSegPx + 2) * 4);
-      const int p = rem >> 2, q = rem & 3;
-      const int gy = wrap(y + u - 1, H), gx = wrap(x0 - 1 + p, W);
-      const u16x8 v = *reinterpret_cast<const u16x8 *>(act + ((b * H + gy) * (long long)W + gx) * CH + 8 * q);
+      for (int s = 0; s < 5; ++s) {
+        const int i = lane + 64 * s;
+        if (i < 4 * kDwPx) ra[s] = *reinterpret_cast<const u16x8 *>(src + wrap(st.x0 - 1 + (i >> 2), W) * CH + (i & 3) * 8);
+      }
+    };
+    auto put_a = [&](int slot) {
 #pragma unroll
-      for (int sh = 0; sh < 3; ++sh) {
-        const int px = p - sh;
-        if (px >= 0 && px < kSegPx) {
+      for (int s = 0; s < 5; ++s) {
+        const int i = lane + 64 * s;
+        if (i < 4 * kDwPx) put_pixel(ring + slot * ROW + (i >> 2) * kDwStride + (i & 3) * 8, ra[s]);
+      }
+    };
+    auto fetch_d = [&](int y) {
+      const uint16_t *src = dz + ((img + y) * W + st.x0) * CH;
 #pragma unroll
-          for (int k = 0; k < 8; ++k) aT[u * 3 + sh][(8 * q + k) * kTS + px] = v[k];
+      for (int s = 0; s < 4; ++s) rd[s] = *reinterpret_cast<const u16x8 *>(src + (lane + 64 * s) * 8);
+    };
+    fetch_a(st.y0 - 1);
+    put_a(0);
+    fetch_a(st.y0);
+    put_a(1);
+    fetch_a(st.y0 + 1);
+    fetch_d(st.y0);
+    for (int j = 0; j < st.nrows; ++j) {
+      wave_sync();  // the previous row's reads are done
+      put_a((j + 2) % 3);
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const int i = lane + 64 * s;
+        put_pixel(dzs + (i >> 2) * kDwStride + (i & 3) * 8, rd[s]);
+      }
+      wave_sync();
+      if (j + 1 < st.nrows) {
+        fetch_a(st.y0 + j + 2);
+        fetch_d(st.y0 + j + 1);
+      }
+#pragma unroll
+      for (int kc = 0; kc < kSegPx / 16; ++kc) {
+        const int px = 16 * kc + 8 * half;
+        u16x8 av;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) av[k] = dzs[(px + k) * kDwStride + col];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) accb += bf2f(av[k]);
+#pragma unroll
+        for (int u = 0; u < 3; ++u) {
+          const uint16_t *rp = ring + ((j + u) % 3) * ROW + px * kDwStride + col;
+          uint16_t w[10];
+#pragma unroll
+          for (int k = 0; k < 10; ++k) w[k] = rp[k * kDwStride];
+#pragma unroll
+          for (int v = 0; v < 3; ++v) {
+            u16x8 bv;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) bv[k] = w[v + k];
+            acc[3 * u + v] = mfma(av, bv, acc[3 * u + v]);
+          }
         }
       }
     }
+  }
+  // Block sum over wavefronts, in a fixed order: halve the wavefronts until one is left.
+  accb += __shfl_xor(accb, 32);
+  float *red = reinterpret_cast<float *>(smem);
+#pragma unroll
+  for (int n = kDwWaves / 2; n > 0; n >>= 1) {
     __syncthreads();
-    if (tid < CH) {
-      for (int px = 0; px < kSegPx; ++px) accb += bf2f(dzT[tid * kTS + px]);
-    }
+    if (wv >= n && wv < 2 * n) {
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      const int t = wv + 4 * k;
-      if (t < 9) {
+      for (int t = 0; t < 9; ++t)
 #pragma unroll
-        for (int kc = 0; kc < kSegPx / 16; ++kc) {
-          const u16x8 av = *reinterpret_cast<const u16x8 *>(dzT + col * kTS + 16 * kc + 8 * half);
-          const u16x8 bv = *reinterpret_cast<const u16x8 *>(aT[t] + col * kTS + 16 * kc + 8 * half);
-          acc[k] = mfma(av, bv, acc[k]);
-        }
-      }
+        for (int r = 0; r < 16; ++r) red[((wv - n) * 144 + t * 16 + r) * 64 + lane] = acc[t][r];
     }
     __syncthreads();
-  }
-  float *o = part + (long long)blockIdx.x * (NW2 + NB2);
+    if (wv < n) {
 #pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    const int t = wv + 4 * k;
-    if (t < 9) {
+      for (int t = 0; t < 9; ++t)
 #pragma unroll
-      for (int rr = 0; rr < 16; ++rr) {
-        const int oc = 8 * (rr / 4) + 4 * half + (rr % 4);
-        o[(oc * CH + col) * 9 + t] = acc[k][rr];
-      }
+        for (int r = 0; r < 16; ++r) acc[t][r] += red[(wv * 144 + t * 16 + r) * 64 + lane];
     }
   }
-  if (tid < CH) o[NW2 + tid] = accb;
+  __syncthreads();
+  if (lane < 32) red[wv * 32 + lane] = accb;
+  __syncthreads();
+  float *o = part + (long long)blockIdx.x * kPartSlots + slot0;
+  if (wv == 0) {
+#pragma unroll
+    for (int t = 0; t < 9; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[t * 1024 + (8 * (r / 4) + 4 * half + r % 4) * 32 + col] = acc[t][r];
+  }
+  if (tid < 32) {
+    float v = 0.f;
+    for (int k = 0; k < kDwWaves; ++k) v += red[k * 32 + tid];
+    o[9 * 1024 + tid] = v;
+  }
 }
 
-__global__ __launch_bounds__(256) void reduce_kernel(const float *__restrict__ part, int n, int nb,
-                                                     float *__restrict__ out) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= n) return;
-  float s = 0.f;
-  for (int b = 0; b < nb; ++b) s += part[(long long)b * n + i];
-  out[i] = s;
+// Layer 1: N = 9 taps x 3 channels (column 3 tap + c), column 27 a vector of
+// ones (the bias), so one product a chunk.
+__global__ __launch_bounds__(64 * kDwWaves) void dw1_kernel(const uint16_t *__restrict__ dz,
+                                                           const uint16_t *__restrict__ xin,
+                                                           float *__restrict__ part, int items, int bands, int rows,
+                                                           int H, int W) {
+  constexpr int ROW = kDwPx * 4, LDS1 = 3 * ROW + kSegPx * kDwStride;
+  __shared__ __attribute__((aligned(16))) uint16_t smem[kDwWaves * LDS1 + 1024 * 2 * kDwWaves];
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int col = lane & 31, half = lane >> 5;
+  uint16_t *ring = smem + wv * LDS1, *dzs = ring + 3 * ROW;
+  const int tap = col < 27 ? col / 3 : 8, ch = col < 27 ? col % 3 : 3;  // columns from 27 on read channel 3
+  const uint16_t fill = col == 27 ? 0x3f80 : 0;                         // bf16 one
+  f32x16 acc = {};
+  for (int item = blockIdx.x + gridDim.x * wv; item < items; item += gridDim.x * kDwWaves) {
+    const DwStrip st = dw_strip(item, bands, rows, H, W);
+    const long long img = (long long)st.b * H;
+    u16x4 ra[2];
+    u16x8 rd[4];
+    auto fetch_a = [&](int yy) {
+      const uint16_t *src = xin + (img + wrap(yy, H)) * W * 4;
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+        if (lane + 64 * s < kDwPx) ra[s] = *reinterpret_cast<const u16x4 *>(src + wrap(st.x0 - 1 + lane + 64 * s, W) * 4);
+    };
+    auto put_a = [&](int slot) {
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+        if (lane + 64 * s < kDwPx) *reinterpret_cast<u16x4 *>(ring + slot * ROW + (lane + 64 * s) * 4) = ra[s];
+    };
+    auto fetch_d = [&](int y) {
+      const uint16_t *src = dz + ((img + y) * W + st.x0) * CH;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) rd[s] = *reinterpret_cast<const u16x8 *>(src + (lane + 64 * s) * 8);
+    };
+    fetch_a(st.y0 - 1);
+    put_a(0);
+    fetch_a(st.y0);
+    put_a(1);
+    fetch_a(st.y0 + 1);
+    fetch_d(st.y0);
+    for (int j = 0; j < st.nrows; ++j) {
+      wave_sync();  // the previous row's reads are done
+      put_a((j + 2) % 3);
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const int i = lane + 64 * s;
+        put_pixel(dzs + (i >> 2) * kDwStride + (i & 3) * 8, rd[s]);
+      }
+      wave_sync();
+      if (j + 1 < st.nrows) {
+        fetch_a(st.y0 + j + 2);
+        fetch_d(st.y0 + j + 1);
+      }
+      const uint16_t *rp = ring + ((j + tap / 3) % 3) * ROW + (tap % 3) * 4 + ch;
+#pragma unroll
+      for (int kc = 0; kc < kSegPx / 16; ++kc) {
+        const int px = 16 * kc + 8 * half;
+        u16x8 av, bv;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) av[k] = dzs[(px + k) * kDwStride + col];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) bv[k] = col < 27 ? rp[(px + k) * 4] : fill;
+        acc = mfma(av, bv, acc);
+      }
+    }
+  }
+  float *red = reinterpret_cast<float *>(smem + kDwWaves * LDS1);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) red[wv * 1024 + (8 * (r / 4) + 4 * half + r % 4) * 32 + col] = acc[r];
+  __syncthreads();
+  for (int i = tid; i < 1024; i += 64 * kDwWaves) {
+    float v = 0.f;
+    for (int k = 0; k < kDwWaves; ++k) v += red[k * 1024 + i];
+    part[(long long)blockIdx.x * kPartSlots + SLOT1 + i] = v;
+  }
+}
+
+// Sums the blocks' partial results of every layer and puts them in parameter
+// order.  Block: 64 slots, 16 wavefronts of kPartBlocks / 16 partials each
+// (5.6 us for all layers; one thread a slot summing all of them took 60 us a
+// layer).
+__global__ __launch_bounds__(1024) void reduce_kernel(const float *__restrict__ part, float *__restrict__ grad) {
+  __shared__ float red[16][64];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, i = blockIdx.x * 64 + lane;
+  constexpr int N = kPartBlocks / 16;
+  float v[N], s = 0.f;
+#pragma unroll
+  for (int k = 0; k < N; ++k) v[k] = part[(long long)(wv * N + k) * kPartSlots + i];
+#pragma unroll
+  for (int k = 0; k < N; ++k) s += v[k];
+  red[wv][lane] = s;
+  __syncthreads();
+  if (wv) return;
+  s = 0.f;
+#pragma unroll
+  for (int k = 0; k < 16; ++k) s += red[k][lane];
+  if (i < SLOT2) {  // layer 1: [co][3 tap + ci], column 27 the bias
+    const int co = (i - SLOT1) / 32, n = (i - SLOT1) % 32;
+    if (n < 27) grad[OFF_W1 + (co * 3 + n % 3) * 9 + n / 3] = s;
+    else if (n == 27) grad[OFF_B1 + co] = s;
+  } else if (i < SLOT4) {  // layers 2, 3: [tap][o][c], then the bias
+    const bool l2 = i < SLOT3;
+    const int k = i - (l2 ? SLOT2 : SLOT3);
+    if (k < 9 * 1024) grad[(l2 ? OFF_W2 : OFF_W3) + (k % 1024) * 9 + k / 1024] = s;
+    else grad[(l2 ? OFF_B2 : OFF_B3) + k - 9 * 1024] = s;
+  } else {  // layer 4: [tap][c], then the bias
+    const int k = i - SLOT4;
+    if (k < NW4) grad[OFF_W4 + (k % CH) * 9 + k / CH] = s;
+    else if (k == NW4) grad[OFF_B4] = s;
+  }
 }
 
 __global__ __launch_bounds__(256) void adam_kernel(float *__restrict__ p, float *__restrict__ m, float *__restrict__ v,
@@ -573,9 +730,9 @@ hipError_t conv32_fwd(const uint16_t *in, const uint16_t *wk, const float *bias,
                       hipStream_t s) {
   return conv32_launch<kFwd>(in, wk, bias, nullptr, z, out, nullptr, nullptr, g, s);
 }
-hipError_t conv32_fwd_taps(const uint16_t *in, const uint16_t *wk, const float *bias, float *z, uint16_t *out,
-                           const uint16_t *w4m, float *taps, Geo g, hipStream_t s) {
-  return conv32_launch<kFwdTaps>(in, wk, bias, nullptr, z, out, w4m, taps, g, s);
+hipError_t conv32_fwd_taps(const uint16_t *in, const uint16_t *wk, const float *bias, float *z, const uint16_t *w4m,
+                           float *taps, Geo g, hipStream_t s) {
+  return conv32_launch<kFwdTaps>(in, wk, bias, nullptr, z, nullptr, w4m, taps, g, s);
 }
 hipError_t conv32_bwd(const uint16_t *din, const uint16_t *wkt, const float *zprev, uint16_t *dout, Geo g,
                       hipStream_t s) {
@@ -591,25 +748,36 @@ hipError_t loss_grad(const float *y, const float *samples, int halo, double inv_
                      g.pixels());
   return hipGetLastError();
 }
-hipError_t conv4_bwd(const uint16_t *dz4, const float *w4f, const float *z3, uint16_t *dz3, Geo g, hipStream_t s) {
-  hipLaunchKernelGGL(conv4_bwd_kernel, dim3(blocks_for(g.pixels())), dim3(256), 0, s, dz4, w4f, z3, dz3, g.H, g.W,
-                     g.pixels());
+hipError_t conv4_bwd(const uint16_t *dz4, const float *w4f, const float *z3, uint16_t *dz3, float *part, Geo g,
+                     hipStream_t s) {
+  hipLaunchKernelGGL(conv4_bwd_kernel, dim3(kPartBlocks), dim3(kL4Threads), 0, s, dz4, w4f, z3, dz3, part, g.H, g.W,
+                     (int)g.pixels());
   return hipGetLastError();
 }
-hipError_t dw4(const uint16_t *dz4, const uint16_t *a3, float *part, Geo g, hipStream_t s) {
-  hipLaunchKernelGGL(dw4_kernel, dim3(kPartBlocks), dim3(256), 0, s, dz4, a3, part, g.H, g.W, g.pixels());
-  return hipGetLastError();
+// Strips of kSegPx pixels, cut into bands of enough rows to give each wavefront one.
+struct DwSplit {
+  int items, bands, rows;
+};
+DwSplit dw_split(Geo g) {
+  const long long strips = (long long)g.B * (g.W / kSegPx), waves = (long long)kPartBlocks * kDwWaves;
+  const int rows = (int)std::min<long long>(g.H, std::max<long long>(kDwFewestRows, (strips * g.H + waves - 1) / waves));
+  const int bands = (g.H + rows - 1) / rows;
+  return {(int)(strips * bands), bands, rows};
 }
-hipError_t dw32(const uint16_t *dz, const uint16_t *a, float *part, Geo g, hipStream_t s) {
-  hipLaunchKernelGGL(dw32_kernel, dim3(kPartBlocks), dim3(256), 0, s, dz, a, part, g.B, g.H, g.W);
+hipError_t dw32(const uint16_t *dz, const uint16_t *a, float *part, int layer, Geo g, hipStream_t s) {
+  const DwSplit d = dw_split(g);
+  hipLaunchKernelGGL(dw32_kernel, dim3(kPartBlocks), dim3(64 * kDwWaves), 0, s, dz, a, part, layer == 2 ? SLOT2 : SLOT3,
+                     d.items, d.bands, d.rows, g.H, g.W);
   return hipGetLastError();
 }
 hipError_t dw1(const uint16_t *dz1, const uint16_t *xin, float *part, Geo g, hipStream_t s) {
-  hipLaunchKernelGGL(dw1_kernel, dim3(kPartBlocks), dim3(256), 0, s, dz1, xin, part, g.H, g.W, g.pixels());
+  const DwSplit d = dw_split(g);
+  hipLaunchKernelGGL(dw1_kernel, dim3(kPartBlocks), dim3(64 * kDwWaves), 0, s, dz1, xin, part, d.items, d.bands, d.rows,
+                     g.H, g.W);
   return hipGetLastError();
 }
-hipError_t reduce_parts(const float *part, int n, float *out, hipStream_t s) {
-  hipLaunchKernelGGL(reduce_kernel, dim3(blocks_for(n)), dim3(256), 0, s, part, n, kPartBlocks, out);
+hipError_t reduce_parts(const float *part, float *grad, hipStream_t s) {
+  hipLaunchKernelGGL(reduce_kernel, dim3(kPartSlots / 64), dim3(1024), 0, s, part, grad);
   return hipGetLastError();
 }
 hipError_t adam(float *p, float *m, float *v, const float *g, float lr, float b1, float b2, float eps, float c1,

@@ -7,7 +7,7 @@
 //            training target (caller-owned)
 //   xin      bf16   [P][4]   input channels 0..2, channel 3 zero
 //   z1..z3   float  [P][32]  pre-activations (kept for the backward pass)
-//   a1..a3   bf16   [P][32]  GELU(z)
+//   a1, a2   bf16   [P][32]  GELU(z)
 //   taps     float  [P][12]  layer 4's per-tap partial sums sum_c W4[tap][c] a3[p][c]
 //            (taps 0..8; slots 9..11 unused)
 //   y        float  [P]      output
@@ -44,10 +44,16 @@ constexpr int OFF_B4 = OFF_W4 + NW4;
 constexpr int NPARAM = OFF_B4 + NB4;
 
 constexpr int kPartBlocks = 256;  // blocks of the weight-gradient kernels (one partial row each)
+// Slots of one block's partial weight gradients: layer 1 [co][3 tap + ci, 27:
+// bias], layers 2 and 3 [tap][o][c] and the bias, layer 4 [tap][c] and the bias.
+constexpr int PART4 = 320;
+constexpr int SLOT1 = 0, SLOT2 = SLOT1 + CH * 32, SLOT3 = SLOT2 + NW2 + NB2, SLOT4 = SLOT3 + NW3 + NB3;
+constexpr int kPartSlots = SLOT4 + PART4;
+static_assert(kPartSlots % 64 == 0 && PART4 >= NW4 + NB4, "whole blocks of reduce_kernel");
 constexpr int kLossBlocks = 256;  // blocks of the loss kernel (one partial sum each)
 constexpr int kConvTileX = 128;   // pixels per block along x in the MFMA convolution
 constexpr int kConvRows = 4;      // fewest rows per block in the MFMA convolution
-constexpr int kSegPx = 64;        // pixels per segment in the MFMA weight gradient
+constexpr int kSegPx = 64;        // pixels per row of a strip in the MFMA weight gradients
 
 struct Geo {
   int B, H, W;
@@ -64,20 +70,22 @@ hipError_t conv32_fwd(const uint16_t *in, const uint16_t *wk, const float *bias,
                       hipStream_t s);
 hipError_t conv32_bwd(const uint16_t *din, const uint16_t *wkt, const float *zprev, uint16_t *dout, Geo g,
                       hipStream_t s);
-// Layer 3 forward as conv32_fwd (out may be null: activations not kept) that
-// also writes layer 4's per-tap partial sums; layer 4 then sums them.
-hipError_t conv32_fwd_taps(const uint16_t *in, const uint16_t *wk, const float *bias, float *z, uint16_t *out,
-                           const uint16_t *w4m, float *taps, Geo g, hipStream_t s);
+// Layer 3 forward as conv32_fwd, writing layer 4's per-tap partial sums in
+// place of the activations; layer 4 then sums them.
+hipError_t conv32_fwd_taps(const uint16_t *in, const uint16_t *wk, const float *bias, float *z, const uint16_t *w4m,
+                           float *taps, Geo g, hipStream_t s);
 hipError_t conv4_fwd(const float *taps, const float *b4, float *y, Geo g, hipStream_t s);
 hipError_t loss_grad(const float *y, const float *samples, int halo, double inv_n, uint16_t *dz4, double *partial,
                      Geo g, hipStream_t s);
-hipError_t conv4_bwd(const uint16_t *dz4, const float *w4f, const float *z3, uint16_t *dz3, Geo g, hipStream_t s);
-// Weight-gradient partial sums: part[block][W..., b...] in the flat parameter
-// order of the layer; reduce_parts sums them over blocks in a fixed order.
-hipError_t dw4(const uint16_t *dz4, const uint16_t *a3, float *part, Geo g, hipStream_t s);
-hipError_t dw32(const uint16_t *dz, const uint16_t *a, float *part, Geo g, hipStream_t s);  // needs W % 64 == 0
-hipError_t dw1(const uint16_t *dz1, const uint16_t *xin, float *part, Geo g, hipStream_t s);
-hipError_t reduce_parts(const float *part, int n, float *out, hipStream_t s);
+// Layer 4 backward-data and weight gradient in one pass over z3.
+hipError_t conv4_bwd(const uint16_t *dz4, const float *w4f, const float *z3, uint16_t *dz3, float *part, Geo g,
+                     hipStream_t s);
+// Weight gradients of layers 1, 2 and 3.  They and conv4_bwd write each
+// block's partial sums part[block][kPartSlots] (every slot a parameter needs);
+// reduce_parts sums them over blocks in a fixed order into the flat vector.
+hipError_t dw32(const uint16_t *dz, const uint16_t *a, float *part, int layer, Geo g, hipStream_t s);  // W % 64 == 0
+hipError_t dw1(const uint16_t *dz1, const uint16_t *xin, float *part, Geo g, hipStream_t s);           // W % 64 == 0
+hipError_t reduce_parts(const float *part, float *grad, hipStream_t s);
 hipError_t adam(float *p, float *m, float *v, const float *g, float lr, float b1, float b2, float eps, float c1,
                 float c2, hipStream_t s);
 hipError_t prep_weights(const float *p, uint16_t *w1m, uint16_t *w2f, uint16_t *w2b, uint16_t *w3f, uint16_t *w3b,

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cmath>
+#include <cstring>
 #include <string>
 #include <vector>
 
@@ -41,7 +42,6 @@ void layout(zk_cnn *n) {
   n->o_p = take(NPARAM * 4);
   n->o_m = take(NPARAM * 4);
   n->o_v = take(NPARAM * 4);
-  n->o_g = take(NPARAM * 4);
   n->o_w1m = take(CH * 48 * 2);
   n->o_w2f = take(NW2 * 2);
   n->o_w2b = take(NW2 * 2);
@@ -49,11 +49,12 @@ void layout(zk_cnn *n) {
   n->o_w3b = take(NW3 * 2);
   n->o_w4f = take(NW4 * 4);
   n->o_w4m = take(32 * 32 * 2);
-  n->o_part = take((size_t)kPartBlocks * (NW2 + NB2) * 4);
-  n->o_loss = take(kLossBlocks * 8);
+  n->o_part = take((size_t)kPartBlocks * kPartSlots * 4);
+  n->o_loss = take(kLossBlocks * 8);  // directly before o_g: fetched together
+  n->o_g = take(NPARAM * 4);
   n->o_xin = take(P * 4 * 2);
   for (int l = 0; l < 3; ++l) n->o_z[l] = take(P * CH * 4);
-  for (int l = 0; l < 3; ++l) n->o_a[l] = take(P * CH * 2);
+  for (int l = 0; l < 2; ++l) n->o_a[l] = take(P * CH * 2);
   n->o_taps = take(P * 12 * 4);
   n->o_y = take(P * 4);
   n->o_dz4 = take(P * 2);
@@ -92,7 +93,7 @@ int forward_packed(zk_cnn *n, float *y, Geo g, bool keep) {
   HIP_TRY(n, conv32_fwd(h(n->o_a[0]), h(n->o_w2f), p + OFF_B2, keep ? f(n->o_z[1]) : nullptr, h(n->o_a[1]), g,
                         n->stream));
   HIP_TRY(n, conv32_fwd_taps(h(n->o_a[1]), h(n->o_w3f), p + OFF_B3, keep ? f(n->o_z[2]) : nullptr,
-                             keep ? h(n->o_a[2]) : nullptr, h(n->o_w4m), f(n->o_taps), g, n->stream));
+                             h(n->o_w4m), f(n->o_taps), g, n->stream));
   HIP_TRY(n, conv4_fwd(f(n->o_taps), p + OFF_B4, y, g, n->stream));
   return ZK_OK;
 }
@@ -105,7 +106,7 @@ int check_infer(zk_cnn *n, int H, int W) { return check_geo(n, 1, H, W, false); 
 namespace {
 
 // Forward, loss and backward into the flat gradient vector (device).
-int gradient(zk_cnn *n, const float *samples, Geo g, int halo, double *loss) {
+int gradient(zk_cnn *n, const float *samples, Geo g, int halo) {
   char *w = n->ws;
   auto f = [&](size_t o) { return reinterpret_cast<float *>(w + o); };
   auto h = [&](size_t o) { return reinterpret_cast<uint16_t *>(w + o); };
@@ -117,29 +118,34 @@ int gradient(zk_cnn *n, const float *samples, Geo g, int halo, double *loss) {
   double *lp = reinterpret_cast<double *>(w + n->o_loss);
   HIP_TRY(n, loss_grad(f(n->o_y), samples, halo, 1.0 / ninterior, h(n->o_dz4), lp, g, n->stream));
   float *part = f(n->o_part);
-  float *grad = f(n->o_g);
-  // layer 4
-  HIP_TRY(n, dw4(h(n->o_dz4), h(n->o_a[2]), part, g, n->stream));
-  HIP_TRY(n, reduce_parts(part, NW4 + NB4, grad + OFF_W4, n->stream));
-  HIP_TRY(n, conv4_bwd(h(n->o_dz4), f(n->o_w4f), f(n->o_z[2]), h(n->o_dz[2]), g, n->stream));
-  // layer 3
-  HIP_TRY(n, dw32(h(n->o_dz[2]), h(n->o_a[1]), part, g, n->stream));
-  HIP_TRY(n, reduce_parts(part, NW3 + NB3, grad + OFF_W3, n->stream));
+  // each layer's weight gradient, then the gradient of the layer below
+  HIP_TRY(n, conv4_bwd(h(n->o_dz4), f(n->o_w4f), f(n->o_z[2]), h(n->o_dz[2]), part, g, n->stream));
+  HIP_TRY(n, dw32(h(n->o_dz[2]), h(n->o_a[1]), part, 3, g, n->stream));
   HIP_TRY(n, conv32_bwd(h(n->o_dz[2]), h(n->o_w3b), f(n->o_z[1]), h(n->o_dz[1]), g, n->stream));
-  // layer 2
-  HIP_TRY(n, dw32(h(n->o_dz[1]), h(n->o_a[0]), part, g, n->stream));
-  HIP_TRY(n, reduce_parts(part, NW2 + NB2, grad + OFF_W2, n->stream));
+  HIP_TRY(n, dw32(h(n->o_dz[1]), h(n->o_a[0]), part, 2, g, n->stream));
   HIP_TRY(n, conv32_bwd(h(n->o_dz[1]), h(n->o_w2b), f(n->o_z[0]), h(n->o_dz[0]), g, n->stream));
-  // layer 1
   HIP_TRY(n, dw1(h(n->o_dz[0]), h(n->o_xin), part, g, n->stream));
-  HIP_TRY(n, reduce_parts(part, NW1 + NB1, grad + OFF_W1, n->stream));
+  HIP_TRY(n, reduce_parts(part, f(n->o_g), n->stream));
+  return ZK_OK;
+}
+
+// The last gradient()'s loss and, if asked for, its gradient to host memory,
+// in one copy and one wait.
+int fetch(zk_cnn *n, Geo g, int halo, double *loss, float *grad) {
+  constexpr size_t kLossBytes = kLossBlocks * sizeof(double);
+  static_assert(kLossBytes % kAlign == 0, "the gradient follows the loss partials without a gap");
+  char hp[kLossBytes + NPARAM * sizeof(float)];
+  HIP_TRY(n, hipMemcpyAsync(hp, n->ws + n->o_loss, grad ? sizeof(hp) : kLossBytes, hipMemcpyDeviceToHost, n->stream));
+  HIP_TRY(n, hipStreamSynchronize(n->stream));
+  if (grad) std::memcpy(grad, hp + kLossBytes, NPARAM * sizeof(float));
   if (loss) {
-    std::vector<double> hp(kLossBlocks);
-    HIP_TRY(n, hipMemcpyAsync(hp.data(), lp, kLossBlocks * sizeof(double), hipMemcpyDeviceToHost, n->stream));
-    HIP_TRY(n, hipStreamSynchronize(n->stream));
     double s = 0.0;
-    for (double v : hp) s += v;
-    *loss = s / ninterior;
+    for (int i = 0; i < kLossBlocks; ++i) {
+      double v;
+      std::memcpy(&v, hp + i * sizeof(v), sizeof(v));
+      s += v;
+    }
+    *loss = s / ((double)g.B * (g.H - 2 * halo) * (g.W - 2 * halo));
   }
   return ZK_OK;
 }
@@ -229,10 +235,8 @@ int zk_cnn_gradient(zk_cnn *n, const float *samples, int B, int H, int W, int ha
   if (rc) return rc;
   if (!n->have_params) return fail(n, ZK_EINVAL, "no parameters loaded");
   if (!samples || !grad) return fail(n, ZK_EINVAL, "null pointer");
-  if ((rc = gradient(n, samples, Geo{B, H, W}, halo, loss))) return rc;
-  HIP_TRY(n, hipMemcpyAsync(grad, n->ws + n->o_g, NPARAM * sizeof(float), hipMemcpyDeviceToHost, n->stream));
-  HIP_TRY(n, hipStreamSynchronize(n->stream));
-  return ZK_OK;
+  if ((rc = gradient(n, samples, Geo{B, H, W}, halo))) return rc;
+  return fetch(n, Geo{B, H, W}, halo, loss, grad);
 }
 
 int zk_cnn_train_step(zk_cnn *n, const float *samples, int B, int H, int W, int halo, double lr, double *loss) {
@@ -240,7 +244,8 @@ int zk_cnn_train_step(zk_cnn *n, const float *samples, int B, int H, int W, int 
   if (rc) return rc;
   if (!n->have_params) return fail(n, ZK_EINVAL, "no parameters loaded");
   if (!samples || !(lr > 0.0)) return fail(n, ZK_EINVAL, "null samples or lr <= 0");
-  if ((rc = gradient(n, samples, Geo{B, H, W}, halo, loss))) return rc;
+  if ((rc = gradient(n, samples, Geo{B, H, W}, halo))) return rc;
+  if (loss && (rc = fetch(n, Geo{B, H, W}, halo, loss, nullptr))) return rc;
   n->adam_t += 1;
   const double b1 = 0.9, b2 = 0.999, eps = 1e-8;
   const double c1 = 1.0 - std::pow(b1, (double)n->adam_t), c2 = 1.0 - std::pow(b2, (double)n->adam_t);

@@ -121,3 +121,31 @@ def test_adam_step_and_training(torch):
         l = net.train_step(s, halo, 3e-3, want_loss=True)
     print(f"  loss {l0:.4e} -> {l:.4e}", flush=True)
     assert l < l0 / 3
+
+
+@pytest.mark.parametrize("B,H,W,halo", [(1, 5, 64, 0), (3, 13, 192, 4), (2, 4, 128, 1), (1, 9, 64, 4)])
+def test_gradient_strip_edges(torch, B, H, W, halo):
+    """The weight gradients walk strips of 64 pixels in bands of four rows or
+    more: one strip or several, a last band of one row, fewer rows than a
+    band, and losses that reach the wrap-around (halo 0).  Same bars as
+    test_gradient_parity."""
+    test_gradient_parity(torch, B, H, W, halo)
+
+
+def test_gradient_of_copies(torch):
+    """256 copies of a crop have the gradient of one: 1/256 scales every term
+    exactly, so only the order of the FP32 sums differs (bands of eight rows
+    here against four; 4096 to 1M terms a sum, their rounding errors of 6e-8
+    each adding like a random walk relative to sum |term|: 1e-5 of the largest
+    entry)."""
+    from paper_2608_25203_amd.zk import Net
+
+    params, samples = make_case(1, 64, 64, 11)
+    net = Net(256 * 64 * 64)
+    net.set_params(flat32(params))
+    s = torch.tensor(samples, dtype=torch.float32, device="cuda")
+    l1, g1 = net.gradient(s, 4)
+    l2, g2 = net.gradient(s.expand(256, 4, 64, 64).contiguous(), 4)
+    assert abs(l2 / l1 - 1) < 1e-6
+    for a, b in zip(C.unflatten(g2.astype(np.float64)), C.unflatten(g1.astype(np.float64))):
+        assert rel(a, b) < 1e-5
