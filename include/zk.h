@@ -253,7 +253,7 @@ int zk_kernel_stats(zk_ctx *ctx, int kind, double *ms, double *bytes, double *fl
 
 /* Autotuner: for each pass kind (row / column, padded / base transform),
  * time every compiled team shape (T threads per transform, first-pass radix
- * E = N / T, T a power of two in [16, 1024]) on the passes of one RK4 step of this
+ * E = N / T, T up to 1024) on the passes of one RK4 step of this
  * context (reps timed repetitions each; the context's internal spectra are
  * overwritten, no caller field is touched) and keep the fastest for later
  * calls.  Results are identical up to FP64 (or FP32) rounding order.
@@ -261,16 +261,17 @@ int zk_kernel_stats(zk_ctx *ctx, int kind, double *ms, double *bytes, double *fl
 int zk_autotune(zk_ctx *ctx, double dt, int reps);
 
 /* Team shape in use for a pass kind (row != 0: row pass; pad != 0: padded
- * transform). */
+ * transform).  zk_bind settles the default shapes (by the axis and its length);
+ * before it this reports the axis's power-of-two team of the smallest radix. */
 int zk_team_shape(const zk_ctx *ctx, int row, int pad, int *T, int *E);
 
 /* Choose the team shape of a pass kind by hand (the autotuner's setting):
  * T threads per transform, first-pass radix E = N / T for the pass's
  * transform length N (3n/2 padded, n base).  T = 0 restores the default.
- * ZK_EINVAL if T does not divide N into a compiled shape (T a power of two
- * in [16, 1024]; power-of-two axes: E in {3, 6, 12} padded or {2, 4, 8} base;
- * axes of 3 2^k points: E = 9 padded, 6 base; and the pair built for the
- * context's precision).  Host only; applies from the next call. */
+ * ZK_EINVAL if T does not divide N into a compiled shape (power-of-two axes:
+ * E in {3, 6, 12} padded or {2, 4, 8} base; axes of 3 2^k points: E = 9
+ * padded, 6 base; of 5 2^k points: 15 padded, 10 base; in FP64 also 3 padded, 2
+ * base on both; and the pair built for the context's precision).  Host only; applies from the next call. */
 int zk_set_team_shape(zk_ctx *ctx, int row, int pad, int T);
 
 /* Text of the last error on this context ("" if none).  Valid until the next
@@ -396,7 +397,7 @@ const char *zk_closure_last_error(const zk_closure *clo);
  * programs or tasks), and one step's phases are replayed as a HIP graph of
  * kernel nodes.  The team shape of each pass and size (threads per
  * transform and first-pass radix) is the default one (the smallest radix,
- * as for a context) until zk_batch_autotune times the compiled alternatives on the
+ * n / 2 threads) until zk_batch_autotune times the compiled alternatives on the
  * batch itself and keeps the fastest.  Tile sizes follow zk_create's rule.
  * ------------------------------------------------------------------------- */
 typedef struct zk_tile {

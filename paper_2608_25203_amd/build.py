@@ -25,9 +25,11 @@ BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libzk.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
-HIP_UNITS = ["zk_reduce.hip", "zk_bc.hip", "zk_cnn.hip", "zk_closure.hip", "zk_batch_row_f64.hip", "zk_batch_row_f32.hip", "zk_batch_col_f64.hip",
-             "zk_batch_col_f32.hip", "zk_persist.hip"]
-HIP_HOST_UNITS = ["zk_api.cpp", "zk_cnn_api.cpp", "zk_closure_api.cpp", "zk_batch.cpp"]
+# the longest units first; the kernel instances in several parts each (gen_batch_units.py)
+HIP_UNITS = [f"zk_batch_{name}{part}.hip" for name, parts in (("row_f64", 7), ("row_f32", 5), ("col_f64", 2), ("col_f32", 2))
+             for part in [""] + [f"_{k}" for k in range(1, parts)]]
+HIP_UNITS += ["zk_persist.hip", "zk_reduce.hip", "zk_bc.hip", "zk_cnn.hip", "zk_closure.hip"]
+HIP_HOST_UNITS = ["zk_launch.cpp", "zk_api.cpp", "zk_cnn_api.cpp", "zk_closure_api.cpp", "zk_batch.cpp"]
 CXX_UNITS = ["zk_plan.cpp"]
 
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-I", os.path.join(ROOT, "include"), "-I", CSRC]

@@ -1,6 +1,8 @@
-"""Writes the batched-kernel instantiation units zk_batch_{row,col}_{f64,f32}.hip
-(one function per unit mapping a team shape (T, E, padded) to its kernel).  Run
-from any directory; the units are committed, this script regenerates them."""
+"""Writes the kernel-instance units: zk_batch_{row,col}_{f64,f32}.hip and, so
+that they compile in parallel, their further parts ..._1.hip, ..._2.hip, ....
+Each part holds a table of its kernels by team shape (T, E, padded) and form;
+the first one also lists the tables of all parts.  Run from any directory; the
+units are committed, this script regenerates them."""
 import os
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -9,96 +11,89 @@ POW2 = ([(T, E) for T in (2, 4, 8, 16) for E in (2, 3, 4, 6)]
         + [(T, E) for T in (32, 64, 128, 256) for E in (2, 3, 4, 6, 8, 12)]
         + [(512, E) for E in (2, 3, 4, 6)] + [(1024, E) for E in (2, 3)])
 SHAPES = [(T, E, E % 3 == 0) for T, E in POW2]
-# axes of n = 3 2^k points: padded transforms with E = 9, base transforms with E = 6
+# axes of n = 3 2^k and 5 2^k points: teams of n / 2 threads, E = 3 padded and 2 base (FP64 only)
+ODD = sorted([3 * 2 ** k for k in range(1, 9)] + [5 * 2 ** k for k in range(1, 8)])
+SHAPES += [(T, E, E == 3) for T in ODD for E in (2, 3)]
+# and teams of a power of two: E = 9 padded and 6 base, E = 15 padded and 10 base
 SHAPES += ([(T, 9, True) for T in (2, 4, 8, 16, 32, 64, 128, 256)]
            + [(T, 6, False) for T in (2, 4, 8, 16, 32, 64, 128, 256)])
-# axes of n = 5 2^k points: padded transforms with E = 15, base transforms with E = 10
 SHAPES += [(T, 15, True) for T in (2, 4, 8, 16, 32, 64, 128)] + [(T, 10, False) for T in (2, 4, 8, 16, 32, 64, 128)]
+PARTS = {"row_f64": 7, "row_f32": 5, "col_f64": 2, "col_f32": 2}
 
 
-FOLD_SHAPES = [(T, E) for T in (64, 128, 256) for E in (2, 3)]  # as fold_team_shape() in zk_kernels.hpp
+def team_slot(T):
+    """as team_slot() in zk_kernels.hpp"""
+    return 1 << (T - 1).bit_length() if T <= 64 else (T + 63) // 64 * 64
+
+
+def block_threads(T):
+    """as block_threads() in zk_kernels.hpp"""
+    return team_slot(T) if team_slot(T) > 128 else 256
 
 
 def lanes_ok(T, E, pad, real_bytes):
     """as row_lanes_ok() in zk_kernels.hpp"""
-    N, tpb = T * E, max(T, 256) // T
-    return pad and E % 5 != 0 and T % 64 == 0 and T <= 1024 and 2 * tpb * N * 2 * real_bytes <= 100 * 1024
+    N, tpb = T * E, block_threads(T) // team_slot(T)
+    return (pad and E % 5 != 0 and T % 64 == 0 and T & (T - 1) == 0 and T <= 1024
+            and 2 * tpb * N * 2 * real_bytes <= 100 * 1024)
 
 
-def bs(T):
-    return max(256, T)
+def fold_team_shape(T, E, pad):
+    """as fold_team_shape() in zk_kernels.hpp"""
+    return pad and E == 3 and T >= 16 and 3 * ((T + 63) // 64 * 64) <= 1024
 
 
-def targs(kind, T, E, pad, lift=False):
-    """template arguments of a kernel instance after its real type: row
-    kernels (T, E[, PAD]), column kernels (T, E[, LIFTSYM[, PAD]]); the padded
-    flag is written only where it differs from its default, E % 3 == 0"""
-    out = [str(T), str(E)]
-    odd = pad != (E % 3 == 0)
-    if kind == "col" and (lift or odd):
-        out.append("true" if lift else "false")
-    if odd:
-        out.append("true" if pad else "false")
-    return ", ".join(out)
+def compiled(T, E, pad):
+    """as row_compiled_shapes() in zk_kernels.hpp"""
+    return pad and ((E == 3 and T >= 16) or (E == 6 and 128 <= T <= 512))
+
+
+def b(v):
+    return "true" if v else "false"
+
+
+def instances(kind, real):
+    """(weight, T, E, pad, form, kernel) of every instance; the weight is a rough compile time"""
+    out = []
+    for T, E, pad in SHAPES:
+        if T in ODD and real == "float":
+            continue
+        if kind == "row":
+            if T % 8 or (T * E * 2 // 3 if pad else T * E) % 16:  # no x axis has this shape
+                if T not in (2, 4):
+                    continue
+            out.append((30 if compiled(T, E, pad) else E, T, E, pad, "KF_PLAIN", f"row_kernel_batch<{real}, {T}, {E}, {b(pad)}>"))
+            if lanes_ok(T, E, pad, 8 if real == "double" else 4):
+                out.append((8, T, E, pad, "KF_LANES", f"row_kernel_batch<{real}, {T}, {E}, true, true>"))
+        else:
+            out.append((E, T, E, pad, "KF_PLAIN", f"col_kernel_batch<{real}, {T}, {E}, false, {b(pad)}>"))
+            if not pad:
+                out.append((E, T, E, pad, "KF_LIFTSYM", f"col_kernel_batch<{real}, {T}, {E}, true, false>"))
+            if fold_team_shape(T, E, pad):
+                out.append((4, T, E, pad, "KF_FOLDS", f"col_kernel_folds<{real}, {T}, {E}>"))
+    return out
+
 
 for kind in ("row", "col"):
     for real, tag in (("double", "f64"), ("float", "f32")):
-        lines = [f"// zk_batch_{kind}_{tag}.hip -- batched {kind}-pass kernel instances ({real} transforms);",
-                 "// written by gen_batch_units.py.",
-                 '#include "zk_kernels.hpp"', "", "namespace zk {", "", "template <>",
-                 f"const void *batch_{kind}_kernel<{real}>(int T, int E, bool pad) {{"]
-        for T, E, pad in SHAPES:
-            ta = targs(kind, T, E, pad)
-            lines.append(f"  if (T == {T} && E == {E} && pad == {'true' if pad else 'false'}) return reinterpret_cast<const void *>(&{kind}_kernel_batch<{real}, {ta}>);")
-        lines += ["  return nullptr;", "}", "",
-                  "template <>",
-                  f"hipError_t launch_batch_{kind}<{real}>(int T, int E, bool pad, dim3 grid, hipStream_t s, const {'RowArgs' if kind == 'row' else 'ColArgs'}<{real}> *args,",
-                  "                                   const BatchItem *items, int tile0, int first0, const void *sched0, PhysArgs ph) {"]
-        for T, E, pad in SHAPES:
-            ta = targs(kind, T, E, pad)
-            lines.append(f"  if (T == {T} && E == {E} && pad == {'true' if pad else 'false'}) {{")
-            lines.append(f"    hipLaunchKernelGGL(({kind}_kernel_batch<{real}, {ta}>), grid, dim3({bs(T)}), 0, s, args, items, tile0, first0, sched0, ph);")
-            lines.append("    return hipGetLastError();")
-            lines.append("  }")
-        lines += ["  return hipErrorInvalidValue;", "}", ""]
-        if kind == "col":  # the lift_sym variant, base-length shapes only
-            lines += ["template <>",
-                      f"hipError_t launch_batch_col_lift<{real}>(int T, int E, dim3 grid, hipStream_t s, const ColArgs<{real}> *args,",
-                      "                                        const BatchItem *items, int tile0, int first0, const void *sched0, PhysArgs ph) {"]
-            for T, E, pad in SHAPES:
-                if pad:
-                    continue
-                lines.append(f"  if (T == {T} && E == {E}) {{")
-                lines.append(f"    hipLaunchKernelGGL((col_kernel_batch<{real}, {targs('col', T, E, pad, True)}>), grid, dim3({bs(T)}), 0, s, args, items, tile0, first0, sched0, ph);")
-                lines.append("    return hipGetLastError();")
-                lines.append("  }")
-            lines += ["  return hipErrorInvalidValue;", "}", ""]
-            # fold teams: kMaxFolds teams of T threads, one column per block
-            lines += ["template <>",
-                      f"hipError_t launch_batch_col_folds<{real}>(int T, int E, dim3 grid, hipStream_t s, const ColArgs<{real}> *args,",
-                      "                                         const BatchItem *items, int tile0, int first0, const void *sched0, PhysArgs ph) {"]
-            for T, E in FOLD_SHAPES:
-                lines.append(f"  if (T == {T} && E == {E}) {{")
-                lines.append(f"    hipLaunchKernelGGL((col_kernel_folds<{real}, {T}, {E}>), grid, dim3(kMaxFolds * {T}), 0, s, args, items, tile0, first0, sched0, ph);")
-                lines.append("    return hipGetLastError();")
-                lines.append("  }")
-            lines += ["  return hipErrorInvalidValue;", "}", ""]
-        if kind == "row":  # the permuted-layout form of the padded shapes that have one
-            rb = 8 if real == "double" else 4
-            lanes = [(T, E) for T, E, pad in SHAPES if lanes_ok(T, E, pad, rb)]
-            lines += ["template <>", f"const void *lanes_row_kernel<{real}>(int T, int E) {{"]
-            for T, E in lanes:
-                lines.append(f"  if (T == {T} && E == {E}) return reinterpret_cast<const void *>(&row_kernel_batch<{real}, {T}, {E}, true, true>);")
-            lines += ["  return nullptr;", "}", "",
-                      "template <>",
-                      f"hipError_t launch_lanes_row<{real}>(int T, int E, dim3 grid, hipStream_t s, const RowArgs<{real}> *args,",
-                      "                                   const BatchItem *items, int tile0, int first0, const void *sched0, PhysArgs ph) {"]
-            for T, E in lanes:
-                lines.append(f"  if (T == {T} && E == {E}) {{")
-                lines.append(f"    hipLaunchKernelGGL((row_kernel_batch<{real}, {T}, {E}, true, true>), grid, dim3({bs(T)}), 0, s, args, items, tile0, first0, sched0, ph);")
-                lines.append("    return hipGetLastError();")
-                lines.append("  }")
-            lines += ["  return hipErrorInvalidValue;", "}", ""]
-        lines += ["}  // namespace zk", ""]
-        with open(os.path.join(HERE, f"zk_batch_{kind}_{tag}.hip"), "w") as f:
-            f.write("\n".join(lines))
+        parts = [[] for _ in range(PARTS[f"{kind}_{tag}"])]
+        load = [0] * len(parts)
+        for inst in sorted(instances(kind, real), reverse=True):
+            k = load.index(min(load))
+            parts[k].append(inst[1:])
+            load[k] += inst[0]
+        for k, part in enumerate(parts):
+            name = f"zk_batch_{kind}_{tag}" + (f"_{k}" if k else "")
+            lines = [f"// {name}.hip -- batched {kind}-pass kernel instances ({real} transforms);",
+                     "// written by gen_batch_units.py.", '#include "zk_kernels.hpp"', "", "namespace zk {", "",
+                     f"extern const KernelEntry {kind}_{tag}_{k}[];", f"const KernelEntry {kind}_{tag}_{k}[] = {{"]
+            for T, E, pad, form, fn in sorted(part):
+                lines.append(f"    {{{T}, {E}, {b(pad)}, {form}, reinterpret_cast<const void *>(&{fn})}},")
+            lines += ["    {0, 0, false, 0, nullptr}};", ""]
+            if k == 0:
+                lines += [f"extern const KernelEntry {kind}_{tag}_{j}[];" for j in range(1, len(parts))]
+                lines += [f"const KernelEntry *const {kind}_kernels_{tag}[] = {{"
+                          + "".join(f"{kind}_{tag}_{j}, " for j in range(len(parts))) + "nullptr};", ""]
+            lines += ["}  // namespace zk", ""]
+            with open(os.path.join(HERE, name + ".hip"), "w") as f:
+                f.write("\n".join(lines))

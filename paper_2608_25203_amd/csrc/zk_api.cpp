@@ -138,24 +138,21 @@ void compute_layout(zk_ctx *c) {
 // whose E does not give a valid team is unused; and the natural table W_n^m,
 // m < n, in slot kTwNatural.  In long double on the host.
 template <typename real>
-std::vector<cpx<real>> twiddles(int n) {
+std::vector<cpx<real>> twiddles(int axis, bool pad) {
+  const int n = pad ? 3 * axis / 2 : axis;
   std::vector<cpx<real>> t((size_t)kTwSlots * n, cpx<real>{(real)0, (real)0});
   const long double two_pi = 2.0L * 3.14159265358979323846264338327950288L;
   for (int m = 0; m < n; ++m) {
     const long double a = -two_pi * (long double)m / (long double)n;
     t[(size_t)kTwNatural * n + m] = {(real)cosl(a), (real)sinl(a)};
   }
-  // candidate first-pass radices of this length, one per slot (tw_slot)
-  const bool f5 = n % 5 == 0;  // 5 2^k lengths: one candidate, 15 (padded) or 10 (base)
-  const int cand[kTwNatural] = {f5 ? (n % 3 == 0 ? 15 : 10) : (n % 9 == 0 ? 9 : (n % 3 == 0 ? 3 : 2)),
-                                f5 ? 0 : (n % 9 == 0 ? 18 : (n % 3 == 0 ? 6 : 4)),
-                                f5 || n % 9 == 0 ? 0 : (n % 3 == 0 ? 12 : 8)};
-  for (int s = 0; s < kTwNatural; ++s) {
-    const int E = cand[s];
-    if (E == 0) continue;
-    const int T = n / E;
-    if (n % E || T < 2 || (T & (T - 1)) || num_passes(T, E) < 2) continue;
-    cpx<real> *tab = t.data() + (size_t)s * n;
+  // one table per candidate first-pass radix of this length
+  int cand[3];
+  const int ncand = radix_candidates(axis, pad, cand);
+  for (int ci = 0; ci < ncand; ++ci) {
+    const int E = cand[ci], T = n / E;
+    if (n % E || T < 2 || num_passes(T, E) < 2) continue;
+    cpx<real> *tab = t.data() + (size_t)tw_slot(E) * n;
     int ns = E;
     for (int p = 1; p < num_passes(T, E); ++p) {
       const int rp = later_radix(T, E, p), step = n / (ns * rp);
@@ -250,14 +247,13 @@ int upload(zk_ctx *c, double dt) {
       HIP_TRY(c, put(c->off_fy, fy.data(), fy.size() * sizeof(double)));
       HIP_TRY(c, hipStreamSynchronize(c->stream));
     }
-    const int lens[4] = {3 * nx / 2, nx, 3 * ny / 2, ny};
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < 4; ++i) {  // as off_tw: x padded, x base, y padded, y base
       if (c->precision == 32) {
-        auto t = twiddles<float>(lens[i]);
+        auto t = twiddles<float>(i < 2 ? nx : ny, i % 2 == 0);
         HIP_TRY(c, put(c->off_tw[i], t.data(), t.size() * sizeof(t[0])));
         HIP_TRY(c, hipStreamSynchronize(c->stream));
       } else {
-        auto t = twiddles<double>(lens[i]);
+        auto t = twiddles<double>(i < 2 ? nx : ny, i % 2 == 0);
         HIP_TRY(c, put(c->off_tw[i], t.data(), t.size() * sizeof(t[0])));
         HIP_TRY(c, hipStreamSynchronize(c->stream));
       }
@@ -361,28 +357,29 @@ int run_seq_t(zk_ctx *c, const std::vector<Launch> &seq, const Phys &ph) {
       // l.first + y of argument record 0 (padded passes) or 1 (base passes),
       // from the program or task table passed with the launch
       const BatchItem *items = nullptr;
-      const int tile0 = pad ? 0 : 1, first0 = l.first;
+      int tile0 = pad ? 0 : 1, first0 = l.first;
       const void *sched0 = ws + (row ? c->off_progs : c->off_tasks);
-      const PhysArgs pa{ph.in0, ph.in1, ph.in2, ph.out0, ph.out1, 1};
+      PhysArgs pa{ph.in0, ph.in1, ph.in2, ph.out0, ph.out1, 1};
       const dim3 grid(sh.blocks, l.count);
       const ColArgs<real> *cargs = reinterpret_cast<const ColArgs<real> *>(ws + c->off_cargs);
-      if (!row && c->pp.ny == 1)  // 1D grid: one element per column, no y transform
+      if (!row && c->pp.ny == 1) {  // 1D grid: one element per column, no y transform
         e = launch_col_1d<real>(l.c2 == 1, dim3((nx / 2 + 255) / 256, l.count), c->stream, cargs, tile0, first0);
-      else if (row && pad && c->row_fft == ZK_ROW_FFT_LANES && row_lanes_ok(sh.T, sh.E, true, (int)sizeof(real)))
-        e = launch_lanes_row<real>(sh.T, sh.E, grid, c->stream,
-                                   reinterpret_cast<const RowArgs<real> *>(ws + c->off_rargs), items, tile0, first0,
-                                   sched0, pa);
-      else if (row)
-        e = launch_batch_row<real>(sh.T, sh.E, pad, grid, c->stream,
-                                   reinterpret_cast<const RowArgs<real> *>(ws + c->off_rargs), items, tile0, first0,
-                                   sched0, pa);
-      else if (l.c2 == 1)
-        e = launch_batch_col_lift<real>(sh.T, sh.E, grid, c->stream, cargs, items, tile0, first0, sched0, pa);
-      else if (l.d2 == kMaxFolds && fold_team_shape(sh.T, sh.E))  // one block per column
-        e = launch_batch_col_folds<real>(sh.T, sh.E, dim3(nx / 2, l.count), c->stream, cargs, items, tile0, first0,
-                                         sched0, pa);
-      else
-        e = launch_batch_col<real>(sh.T, sh.E, pad, grid, c->stream, cargs, items, tile0, first0, sched0, pa);
+      } else {
+        int form = KF_PLAIN, threads = block_threads(sh.T);
+        if (row && pad && c->row_fft == ZK_ROW_FFT_LANES && row_lanes_ok(sh.T, sh.E, true, (int)sizeof(real))) {
+          form = KF_LANES;
+        } else if (!row && l.c2 == 1) {
+          form = KF_LIFTSYM;
+        } else if (!row && l.d2 == kMaxFolds && fold_team_shape(sh.T, sh.E)) {  // one block per column
+          form = KF_FOLDS;
+          threads = kMaxFolds * fold_slot(sh.T);
+        }
+        const void *fn = find_kernel(row, sizeof(real) == 8, form, sh.T, sh.E, pad);
+        if (!fn) return fail(c, ZK_EINVAL, "team shape not built");
+        const void *args = ws + (row ? c->off_rargs : c->off_cargs);
+        void *params[] = {&args, &items, &tile0, &first0, &sched0, &pa};
+        e = hipLaunchKernel(fn, form == KF_FOLDS ? dim3(nx / 2, l.count) : grid, dim3(threads), params, 0, c->stream);
+      }
     } else {
       double *red = reinterpret_cast<double *>(ws + c->off_red);
       e = launch_parseval(base + (long long)l.first * c->base_stride, base + (long long)l.count * c->base_stride,
@@ -436,9 +433,8 @@ int crop_out(zk_ctx *c, int k, double *a) {
 namespace zk {
 
 TeamShape ctx_team(const zk_ctx *c, bool row, bool pad) {
-  // default: the smallest first-pass radix (E = 3 padded, 2 base), i.e.
-  // T = N / E threads per transform (at most 1024 for n <= 2048), or the
-  // autotuned shape; a block has max(256, T) threads, 256 / T teams when T < 256
+  // the autotuned or chosen shape, else the default (T = N / E threads per
+  // transform, at most 1024)
   const int n = row ? c->pp.nx : c->pp.ny;
   const int N = pad ? 3 * n / 2 : n;
   TeamShape sh;
@@ -448,9 +444,9 @@ TeamShape ctx_team(const zk_ctx *c, bool row, bool pad) {
     sh.blocks = (c->pp.nx / 2 + 255) / 256;
     return sh;
   }
-  sh.T = c->tuneT[row][pad] ? c->tuneT[row][pad] : N / default_radix(n, pad);
+  sh.T = c->tuneT[row][pad] ? c->tuneT[row][pad] : N / (c->bound ? default_radix(c->precision == 64, row, n, pad) : pow2_team_radix(n, pad));
   sh.E = N / sh.T;
-  const int tpb = sh.T < 256 ? 256 / sh.T : 1;
+  const int tpb = block_threads(sh.T) / team_slot(sh.T);
   // (rows of a 1D grid: 1, in a block whose other teams idle)
   sh.blocks = row ? ((pad ? 3 * c->pp.ny / 2 : c->pp.ny) + tpb - 1) / tpb : (c->pp.nx / 2 + tpb - 1) / tpb;
   return sh;
@@ -893,11 +889,7 @@ int zk_autotune(zk_ctx *c, double dt, int reps) {
       for (int ci = 0; ci < ncand; ++ci) {
         const int E = cand[ci];
         const int T = N / E;
-        if (N % E || T < 2 || T > 1024 || (T & (T - 1))) continue;
-        const void *fn = c->precision == 32
-                             ? (row ? batch_row_kernel<float>(T, E, pad) : batch_col_kernel<float>(T, E, pad))
-                             : (row ? batch_row_kernel<double>(T, E, pad) : batch_col_kernel<double>(T, E, pad));
-        if (!fn) continue;
+        if (N % E || T < 2 || T > 1024 || !find_kernel(row, c->precision == 64, KF_PLAIN, T, E, pad)) continue;
         c->tuneT[row][pad] = T;
         float tot = 0.f;
         for (int r = 0; r <= reps; ++r) {  // r = 0 warms up
@@ -958,10 +950,9 @@ int zk_set_team_shape(zk_ctx *c, int row, int pad, int T) {
   const int n = row ? c->pp.nx : c->pp.ny;
   const int N = pad ? 3 * n / 2 : n;
   if (!row && n == 1) return fail(c, ZK_EINVAL, "a 1D grid's column passes have no team shape");
-  if (T < 2 || T > 1024 || (T & (T - 1)) || N % T) return fail(c, ZK_EINVAL, "team size must divide the transform length");
+  if (T < 2 || T > 1024 || N % T) return fail(c, ZK_EINVAL, "team size must divide the transform length");
   const int E = N / T;
-  const void *fn = c->precision == 32 ? (row ? batch_row_kernel<float>(T, E, pad) : batch_col_kernel<float>(T, E, pad))
-                                      : (row ? batch_row_kernel<double>(T, E, pad) : batch_col_kernel<double>(T, E, pad));
+  const void *fn = find_kernel(row, c->precision == 64, KF_PLAIN, T, E, pad);
   int cand[3];
   const int ncand = radix_candidates(n, pad, cand);
   if (!fn || std::find(cand, cand + ncand, E) == cand + ncand) return fail(c, ZK_EINVAL, "team shape not built");

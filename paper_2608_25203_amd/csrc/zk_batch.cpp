@@ -103,12 +103,11 @@ int hip_fail(zk_batch *b, hipError_t e, const char *what) {
 bool is_row(int kind) { return kind == L_ROW_PAD || kind == L_ROW_BASE; }
 
 const void *kernel_for(const zk_batch *b, bool row, int T, int E, bool pad) {
-  if (b->precision == 32) return row ? batch_row_kernel<float>(T, E, pad) : batch_col_kernel<float>(T, E, pad);
-  return row ? batch_row_kernel<double>(T, E, pad) : batch_col_kernel<double>(T, E, pad);
+  return find_kernel(row, b->precision == 64, KF_PLAIN, T, E, pad);
 }
 
 // Candidate team shapes of a transform of an axis of n points (radix_candidates),
-// T in {16, ..., 1024} threads.
+// up to 1024 threads.
 std::vector<std::pair<int, int>> candidates(const zk_batch *b, bool row, bool pad, int n) {
   std::vector<std::pair<int, int>> out;
   const int N = pad ? 3 * n / 2 : n;
@@ -119,7 +118,7 @@ std::vector<std::pair<int, int>> candidates(const zk_batch *b, bool row, bool pa
     if (N % E) continue;
     const int T = N / E;
     if (b->persistent && persist_shape(row, T, E) < 0) continue;  // not hosted by the persistent kernel
-    if (T >= 2 && T <= 1024 && !(T & (T - 1)) && kernel_for(b, row, T, E, pad)) out.push_back({T, E});
+    if (T >= 2 && T <= 1024 && kernel_for(b, row, T, E, pad)) out.push_back({T, E});
   }
   return out;
 }
@@ -128,13 +127,13 @@ std::pair<int, int> shape_of(zk_batch *b, bool row, bool pad, int nx, int ny) {
   const Key k{row, pad, nx, ny};
   auto it = b->tune.find(k);
   if (it != b->tune.end()) return it->second;
-  const int n = row ? nx : ny;  // default: the smallest first-pass radix (as a single context)
-  const int E = default_radix(n, pad);
+  // default: the smallest first-pass radix (which the persistent kernel hosts too)
+  const int n = row ? nx : ny, E = b->precision == 64 ? (pad ? 3 : 2) : pow2_team_radix(n, pad);
   return {(pad ? 3 * n / 2 : n) / E, E};
 }
 
 int blocks_of(bool row, bool pad, int nx, int ny, int T) {
-  const int per = T < 256 ? 256 / T : 1;  // teams per block; a partial last block idles its spare teams
+  const int per = block_threads(T) / team_slot(T);  // teams per block; a partial last block idles its spare teams
   return row ? ((pad ? 3 * ny / 2 : ny) + per - 1) / per : (nx / 2 + per - 1) / per;
 }
 
@@ -196,7 +195,7 @@ int launch(zk_batch *b, const BL &l) {
   int tile0 = 0, first0 = 0;  // unused: batches pass their item table
   const void *sched0 = nullptr;  // and read each tile's schedule from its record
   void *params[] = {&args, &it, &tile0, &first0, &sched0, &ph};
-  HIP_TRY(b, hipLaunchKernel(fn, dim3(l.blocks, l.nitems), dim3(std::max(256, l.T)), params, 0, b->stream));
+  HIP_TRY(b, hipLaunchKernel(fn, dim3(l.blocks, l.nitems), dim3(block_threads(l.T)), params, 0, b->stream));
   return ZK_OK;
 }
 
@@ -227,7 +226,7 @@ int build_graph(zk_batch *b, int s) {
       hipKernelNodeParams p{};
       p.func = const_cast<void *>(fn);
       p.gridDim = dim3(l.blocks, l.nitems);
-      p.blockDim = dim3(std::max(256, l.T));
+      p.blockDim = dim3(block_threads(l.T));
       p.sharedMemBytes = 0;
       p.kernelParams = params;
       p.extra = nullptr;

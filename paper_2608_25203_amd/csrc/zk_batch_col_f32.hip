@@ -4,583 +4,70 @@
 
 namespace zk {
 
-template <>
-const void *batch_col_kernel<float>(int T, int E, bool pad) {
-  if (T == 2 && E == 2 && pad == false) return reinterpret_cast<const void *>(&col_kernel_batch<float, 2, 2>);
-  if (T == 2 && E == 3 && pad == true) return reinterpret_cast<const void *>(&col_kernel_batch<float, 2, 3>);
-  if (T == 2 && E == 4 && pad == false) return reinterpret_cast<const void *>(&col_kernel_batch<float, 2, 4>);
-  if (T == 2 && E == 6 && pad == true) return reinterpret_cast<const void *>(&col_kernel_batch<float, 2, 6>);
-  if (T == 4 && E == 2 && pad == false) return reinterpret_cast<const void *>(&col_kernel_batch<float, 4, 2>);
-  if (T == 4 && E == 3 && pad == true) return reinterpret_cast<const void *>(&col_kernel_batch<float, 4, 3>);
-  if (T == 4 && E == 4 && pad == false) return reinterpret_cast<const void *>(&col_kernel_batch<float, 4, 4>);
-  if (T == 4 && E == 6 && pad == true) return reinterpret_cast<const void *>(&col_kernel_batch<float, 4, 6>);
-  if (T == 8 && E == 2 && pad == false) return reinterpret_cast<const void *>(&col_kernel_batch<float, 8, 2>);
-  if (T == 8 && E == 3 && pad == true) return reinterpret_cast<const void *>(&col_kernel_batch<float, 8, 3>);
-  if (T == 8 && E == 4 && pad == false) return reinterpret_cast<const void *>(&col_kernel_batch<float, 8, 4>);
-  if (T == 8 && E == 6 && pad == true) return reinterpret_cast<const void *>(&col_kernel_batch<float, 8, 6>);
-  if (T == 16 && E == 2 && pad == false) return reinterpret_cast<const void *>(&col_kernel_batch<float, 16, 2>);
-  if (T == 16 && E == 3 && pad == true) return reinterpret_cast<const void *>(&col_kernel_batch<float, 16, 3>);
-  if (T == 16 && E == 4 && pad == false) return reinterpret_cast<const void *>(&col_kernel_batch<float, 16, 4>);
-  if (T == 16 && E == 6 && pad == true) return reinterpret_cast<const void *>(&col_kernel_batch<float, 16, 6>);
-  if (T == 32 && E == 2 && pad == false) return reinterpret_cast<const void *>(&col_kernel_batch<float, 32, 2>);
-  if (T == 32 && E == 3 && pad == true) return reinterpret_cast<const void *>(&col_kernel_batch<float, 32, 3>);
-  if (T == 32 && E == 4 && pad == false) return reinterpret_cast<const void *>(&col_kernel_batch<float, 32, 4>);
-  if (T == 32 && E == 6 && pad == true) return reinterpret_cast<const void *>(&col_kernel_batch<float, 32, 6>);
-  if (T == 32 && E == 8 && pad == false) return reinterpret_cast<const void *>(&col_kernel_batch<float, 32, 8>);
-  if (T == 32 && E == 12 && pad == true) return reinterpret_cast<const void *>(&col_kernel_batch<float, 32, 12>);
-  if (T == 64 && E == 2 && pad == false) return reinterpret_cast<const void *>(&col_kernel_batch<float, 64, 2>);
-  if (T == 64 && E == 3 && pad == true) return reinterpret_cast<const void *>(&col_kernel_batch<float, 64, 3>);
-  if (T == 64 && E == 4 && pad == false) return reinterpret_cast<const void *>(&col_kernel_batch<float, 64, 4>);
-  if (T == 64 && E == 6 && pad == true) return reinterpret_cast<const void *>(&col_kernel_batch<float, 64, 6>);
-  if (T == 64 && E == 8 && pad == false) return reinterpret_cast<const void *>(&col_kernel_batch<float, 64, 8>);
-  if (T == 64 && E == 12 && pad == true) return reinterpret_cast<const void *>(&col_kernel_batch<float, 64, 12>);
-  if (T == 128 && E == 2 && pad == false) return reinterpret_cast<const void *>(&col_kernel_batch<float, 128, 2>);
-  if (T == 128 && E == 3 && pad == true) return reinterpret_cast<const void *>(&col_kernel_batch<float, 128, 3>);
-  if (T == 128 && E == 4 && pad == false) return reinterpret_cast<const void *>(&col_kernel_batch<float, 128, 4>);
-  if (T == 128 && E == 6 && pad == true) return reinterpret_cast<const void *>(&col_kernel_batch<float, 128, 6>);
-  if (T == 128 && E == 8 && pad == false) return reinterpret_cast<const void *>(&col_kernel_batch<float, 128, 8>);
-  if (T == 128 && E == 12 && pad == true) return reinterpret_cast<const void *>(&col_kernel_batch<float, 128, 12>);
-  if (T == 256 && E == 2 && pad == false) return reinterpret_cast<const void *>(&col_kernel_batch<float, 256, 2>);
-  if (T == 256 && E == 3 && pad == true) return reinterpret_cast<const void *>(&col_kernel_batch<float, 256, 3>);
-  if (T == 256 && E == 4 && pad == false) return reinterpret_cast<const void *>(&col_kernel_batch<float, 256, 4>);
-  if (T == 256 && E == 6 && pad == true) return reinterpret_cast<const void *>(&col_kernel_batch<float, 256, 6>);
-  if (T == 256 && E == 8 && pad == false) return reinterpret_cast<const void *>(&col_kernel_batch<float, 256, 8>);
-  if (T == 256 && E == 12 && pad == true) return reinterpret_cast<const void *>(&col_kernel_batch<float, 256, 12>);
-  if (T == 512 && E == 2 && pad == false) return reinterpret_cast<const void *>(&col_kernel_batch<float, 512, 2>);
-  if (T == 512 && E == 3 && pad == true) return reinterpret_cast<const void *>(&col_kernel_batch<float, 512, 3>);
-  if (T == 512 && E == 4 && pad == false) return reinterpret_cast<const void *>(&col_kernel_batch<float, 512, 4>);
-  if (T == 512 && E == 6 && pad == true) return reinterpret_cast<const void *>(&col_kernel_batch<float, 512, 6>);
-  if (T == 1024 && E == 2 && pad == false) return reinterpret_cast<const void *>(&col_kernel_batch<float, 1024, 2>);
-  if (T == 1024 && E == 3 && pad == true) return reinterpret_cast<const void *>(&col_kernel_batch<float, 1024, 3>);
-  if (T == 2 && E == 9 && pad == true) return reinterpret_cast<const void *>(&col_kernel_batch<float, 2, 9>);
-  if (T == 4 && E == 9 && pad == true) return reinterpret_cast<const void *>(&col_kernel_batch<float, 4, 9>);
-  if (T == 8 && E == 9 && pad == true) return reinterpret_cast<const void *>(&col_kernel_batch<float, 8, 9>);
-  if (T == 16 && E == 9 && pad == true) return reinterpret_cast<const void *>(&col_kernel_batch<float, 16, 9>);
-  if (T == 32 && E == 9 && pad == true) return reinterpret_cast<const void *>(&col_kernel_batch<float, 32, 9>);
-  if (T == 64 && E == 9 && pad == true) return reinterpret_cast<const void *>(&col_kernel_batch<float, 64, 9>);
-  if (T == 128 && E == 9 && pad == true) return reinterpret_cast<const void *>(&col_kernel_batch<float, 128, 9>);
-  if (T == 256 && E == 9 && pad == true) return reinterpret_cast<const void *>(&col_kernel_batch<float, 256, 9>);
-  if (T == 2 && E == 6 && pad == false) return reinterpret_cast<const void *>(&col_kernel_batch<float, 2, 6, false, false>);
-  if (T == 4 && E == 6 && pad == false) return reinterpret_cast<const void *>(&col_kernel_batch<float, 4, 6, false, false>);
-  if (T == 8 && E == 6 && pad == false) return reinterpret_cast<const void *>(&col_kernel_batch<float, 8, 6, false, false>);
-  if (T == 16 && E == 6 && pad == false) return reinterpret_cast<const void *>(&col_kernel_batch<float, 16, 6, false, false>);
-  if (T == 32 && E == 6 && pad == false) return reinterpret_cast<const void *>(&col_kernel_batch<float, 32, 6, false, false>);
-  if (T == 64 && E == 6 && pad == false) return reinterpret_cast<const void *>(&col_kernel_batch<float, 64, 6, false, false>);
-  if (T == 128 && E == 6 && pad == false) return reinterpret_cast<const void *>(&col_kernel_batch<float, 128, 6, false, false>);
-  if (T == 256 && E == 6 && pad == false) return reinterpret_cast<const void *>(&col_kernel_batch<float, 256, 6, false, false>);
-  if (T == 2 && E == 15 && pad == true) return reinterpret_cast<const void *>(&col_kernel_batch<float, 2, 15>);
-  if (T == 4 && E == 15 && pad == true) return reinterpret_cast<const void *>(&col_kernel_batch<float, 4, 15>);
-  if (T == 8 && E == 15 && pad == true) return reinterpret_cast<const void *>(&col_kernel_batch<float, 8, 15>);
-  if (T == 16 && E == 15 && pad == true) return reinterpret_cast<const void *>(&col_kernel_batch<float, 16, 15>);
-  if (T == 32 && E == 15 && pad == true) return reinterpret_cast<const void *>(&col_kernel_batch<float, 32, 15>);
-  if (T == 64 && E == 15 && pad == true) return reinterpret_cast<const void *>(&col_kernel_batch<float, 64, 15>);
-  if (T == 128 && E == 15 && pad == true) return reinterpret_cast<const void *>(&col_kernel_batch<float, 128, 15>);
-  if (T == 2 && E == 10 && pad == false) return reinterpret_cast<const void *>(&col_kernel_batch<float, 2, 10>);
-  if (T == 4 && E == 10 && pad == false) return reinterpret_cast<const void *>(&col_kernel_batch<float, 4, 10>);
-  if (T == 8 && E == 10 && pad == false) return reinterpret_cast<const void *>(&col_kernel_batch<float, 8, 10>);
-  if (T == 16 && E == 10 && pad == false) return reinterpret_cast<const void *>(&col_kernel_batch<float, 16, 10>);
-  if (T == 32 && E == 10 && pad == false) return reinterpret_cast<const void *>(&col_kernel_batch<float, 32, 10>);
-  if (T == 64 && E == 10 && pad == false) return reinterpret_cast<const void *>(&col_kernel_batch<float, 64, 10>);
-  if (T == 128 && E == 10 && pad == false) return reinterpret_cast<const void *>(&col_kernel_batch<float, 128, 10>);
-  return nullptr;
-}
+extern const KernelEntry col_f32_0[];
+const KernelEntry col_f32_0[] = {
+    {2, 2, false, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 2, 2, false, false>)},
+    {2, 3, true, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 2, 3, false, true>)},
+    {2, 4, false, KF_LIFTSYM, reinterpret_cast<const void *>(&col_kernel_batch<float, 2, 4, true, false>)},
+    {2, 6, false, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 2, 6, false, false>)},
+    {2, 9, true, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 2, 9, false, true>)},
+    {2, 10, false, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 2, 10, false, false>)},
+    {2, 15, true, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 2, 15, false, true>)},
+    {4, 2, false, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 4, 2, false, false>)},
+    {4, 4, false, KF_LIFTSYM, reinterpret_cast<const void *>(&col_kernel_batch<float, 4, 4, true, false>)},
+    {4, 6, false, KF_LIFTSYM, reinterpret_cast<const void *>(&col_kernel_batch<float, 4, 6, true, false>)},
+    {4, 6, true, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 4, 6, false, true>)},
+    {4, 10, false, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 4, 10, false, false>)},
+    {8, 2, false, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 8, 2, false, false>)},
+    {8, 3, true, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 8, 3, false, true>)},
+    {8, 4, false, KF_LIFTSYM, reinterpret_cast<const void *>(&col_kernel_batch<float, 8, 4, true, false>)},
+    {8, 6, false, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 8, 6, false, false>)},
+    {8, 9, true, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 8, 9, false, true>)},
+    {8, 10, false, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 8, 10, false, false>)},
+    {8, 15, true, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 8, 15, false, true>)},
+    {16, 2, false, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 16, 2, false, false>)},
+    {16, 3, true, KF_FOLDS, reinterpret_cast<const void *>(&col_kernel_folds<float, 16, 3>)},
+    {16, 4, false, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 16, 4, false, false>)},
+    {16, 6, false, KF_LIFTSYM, reinterpret_cast<const void *>(&col_kernel_batch<float, 16, 6, true, false>)},
+    {16, 6, true, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 16, 6, false, true>)},
+    {16, 10, false, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 16, 10, false, false>)},
+    {32, 2, false, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 32, 2, false, false>)},
+    {32, 3, true, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 32, 3, false, true>)},
+    {32, 4, false, KF_LIFTSYM, reinterpret_cast<const void *>(&col_kernel_batch<float, 32, 4, true, false>)},
+    {32, 6, false, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 32, 6, false, false>)},
+    {32, 8, false, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 32, 8, false, false>)},
+    {32, 9, true, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 32, 9, false, true>)},
+    {32, 10, false, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 32, 10, false, false>)},
+    {32, 15, true, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 32, 15, false, true>)},
+    {64, 2, false, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 64, 2, false, false>)},
+    {64, 3, true, KF_FOLDS, reinterpret_cast<const void *>(&col_kernel_folds<float, 64, 3>)},
+    {64, 4, false, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 64, 4, false, false>)},
+    {64, 6, false, KF_LIFTSYM, reinterpret_cast<const void *>(&col_kernel_batch<float, 64, 6, true, false>)},
+    {64, 6, true, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 64, 6, false, true>)},
+    {64, 8, false, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 64, 8, false, false>)},
+    {64, 10, false, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 64, 10, false, false>)},
+    {64, 12, true, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 64, 12, false, true>)},
+    {128, 2, false, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 128, 2, false, false>)},
+    {128, 3, true, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 128, 3, false, true>)},
+    {128, 4, false, KF_LIFTSYM, reinterpret_cast<const void *>(&col_kernel_batch<float, 128, 4, true, false>)},
+    {128, 6, false, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 128, 6, false, false>)},
+    {128, 8, false, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 128, 8, false, false>)},
+    {128, 9, true, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 128, 9, false, true>)},
+    {128, 10, false, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 128, 10, false, false>)},
+    {128, 15, true, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 128, 15, false, true>)},
+    {256, 2, false, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 256, 2, false, false>)},
+    {256, 3, true, KF_FOLDS, reinterpret_cast<const void *>(&col_kernel_folds<float, 256, 3>)},
+    {256, 4, false, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 256, 4, false, false>)},
+    {256, 6, false, KF_LIFTSYM, reinterpret_cast<const void *>(&col_kernel_batch<float, 256, 6, true, false>)},
+    {256, 6, true, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 256, 6, false, true>)},
+    {256, 9, true, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 256, 9, false, true>)},
+    {512, 2, false, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 512, 2, false, false>)},
+    {512, 3, true, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 512, 3, false, true>)},
+    {512, 4, false, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 512, 4, false, false>)},
+    {512, 6, true, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 512, 6, false, true>)},
+    {0, 0, false, 0, nullptr}};
 
-template <>
-hipError_t launch_batch_col<float>(int T, int E, bool pad, dim3 grid, hipStream_t s, const ColArgs<float> *args,
-                                   const BatchItem *items, int tile0, int first0, const void *sched0, PhysArgs ph) {
-  if (T == 2 && E == 2 && pad == false) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 2, 2>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 2 && E == 3 && pad == true) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 2, 3>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 2 && E == 4 && pad == false) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 2, 4>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 2 && E == 6 && pad == true) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 2, 6>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 4 && E == 2 && pad == false) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 4, 2>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 4 && E == 3 && pad == true) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 4, 3>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 4 && E == 4 && pad == false) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 4, 4>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 4 && E == 6 && pad == true) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 4, 6>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 8 && E == 2 && pad == false) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 8, 2>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 8 && E == 3 && pad == true) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 8, 3>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 8 && E == 4 && pad == false) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 8, 4>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 8 && E == 6 && pad == true) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 8, 6>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 16 && E == 2 && pad == false) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 16, 2>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 16 && E == 3 && pad == true) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 16, 3>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 16 && E == 4 && pad == false) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 16, 4>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 16 && E == 6 && pad == true) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 16, 6>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 32 && E == 2 && pad == false) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 32, 2>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 32 && E == 3 && pad == true) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 32, 3>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 32 && E == 4 && pad == false) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 32, 4>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 32 && E == 6 && pad == true) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 32, 6>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 32 && E == 8 && pad == false) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 32, 8>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 32 && E == 12 && pad == true) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 32, 12>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 64 && E == 2 && pad == false) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 64, 2>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 64 && E == 3 && pad == true) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 64, 3>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 64 && E == 4 && pad == false) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 64, 4>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 64 && E == 6 && pad == true) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 64, 6>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 64 && E == 8 && pad == false) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 64, 8>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 64 && E == 12 && pad == true) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 64, 12>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 128 && E == 2 && pad == false) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 128, 2>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 128 && E == 3 && pad == true) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 128, 3>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 128 && E == 4 && pad == false) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 128, 4>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 128 && E == 6 && pad == true) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 128, 6>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 128 && E == 8 && pad == false) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 128, 8>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 128 && E == 12 && pad == true) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 128, 12>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 256 && E == 2 && pad == false) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 256, 2>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 256 && E == 3 && pad == true) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 256, 3>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 256 && E == 4 && pad == false) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 256, 4>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 256 && E == 6 && pad == true) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 256, 6>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 256 && E == 8 && pad == false) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 256, 8>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 256 && E == 12 && pad == true) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 256, 12>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 512 && E == 2 && pad == false) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 512, 2>), grid, dim3(512), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 512 && E == 3 && pad == true) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 512, 3>), grid, dim3(512), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 512 && E == 4 && pad == false) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 512, 4>), grid, dim3(512), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 512 && E == 6 && pad == true) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 512, 6>), grid, dim3(512), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 1024 && E == 2 && pad == false) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 1024, 2>), grid, dim3(1024), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 1024 && E == 3 && pad == true) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 1024, 3>), grid, dim3(1024), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 2 && E == 9 && pad == true) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 2, 9>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 4 && E == 9 && pad == true) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 4, 9>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 8 && E == 9 && pad == true) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 8, 9>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 16 && E == 9 && pad == true) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 16, 9>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 32 && E == 9 && pad == true) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 32, 9>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 64 && E == 9 && pad == true) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 64, 9>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 128 && E == 9 && pad == true) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 128, 9>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 256 && E == 9 && pad == true) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 256, 9>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 2 && E == 6 && pad == false) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 2, 6, false, false>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 4 && E == 6 && pad == false) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 4, 6, false, false>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 8 && E == 6 && pad == false) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 8, 6, false, false>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 16 && E == 6 && pad == false) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 16, 6, false, false>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 32 && E == 6 && pad == false) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 32, 6, false, false>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 64 && E == 6 && pad == false) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 64, 6, false, false>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 128 && E == 6 && pad == false) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 128, 6, false, false>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 256 && E == 6 && pad == false) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 256, 6, false, false>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 2 && E == 15 && pad == true) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 2, 15>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 4 && E == 15 && pad == true) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 4, 15>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 8 && E == 15 && pad == true) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 8, 15>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 16 && E == 15 && pad == true) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 16, 15>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 32 && E == 15 && pad == true) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 32, 15>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 64 && E == 15 && pad == true) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 64, 15>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 128 && E == 15 && pad == true) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 128, 15>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 2 && E == 10 && pad == false) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 2, 10>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 4 && E == 10 && pad == false) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 4, 10>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 8 && E == 10 && pad == false) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 8, 10>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 16 && E == 10 && pad == false) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 16, 10>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 32 && E == 10 && pad == false) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 32, 10>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 64 && E == 10 && pad == false) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 64, 10>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 128 && E == 10 && pad == false) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 128, 10>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  return hipErrorInvalidValue;
-}
-
-template <>
-hipError_t launch_batch_col_lift<float>(int T, int E, dim3 grid, hipStream_t s, const ColArgs<float> *args,
-                                        const BatchItem *items, int tile0, int first0, const void *sched0, PhysArgs ph) {
-  if (T == 2 && E == 2) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 2, 2, true>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 2 && E == 4) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 2, 4, true>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 4 && E == 2) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 4, 2, true>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 4 && E == 4) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 4, 4, true>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 8 && E == 2) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 8, 2, true>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 8 && E == 4) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 8, 4, true>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 16 && E == 2) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 16, 2, true>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 16 && E == 4) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 16, 4, true>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 32 && E == 2) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 32, 2, true>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 32 && E == 4) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 32, 4, true>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 32 && E == 8) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 32, 8, true>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 64 && E == 2) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 64, 2, true>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 64 && E == 4) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 64, 4, true>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 64 && E == 8) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 64, 8, true>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 128 && E == 2) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 128, 2, true>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 128 && E == 4) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 128, 4, true>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 128 && E == 8) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 128, 8, true>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 256 && E == 2) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 256, 2, true>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 256 && E == 4) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 256, 4, true>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 256 && E == 8) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 256, 8, true>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 512 && E == 2) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 512, 2, true>), grid, dim3(512), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 512 && E == 4) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 512, 4, true>), grid, dim3(512), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 1024 && E == 2) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 1024, 2, true>), grid, dim3(1024), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 2 && E == 6) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 2, 6, true, false>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 4 && E == 6) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 4, 6, true, false>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 8 && E == 6) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 8, 6, true, false>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 16 && E == 6) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 16, 6, true, false>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 32 && E == 6) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 32, 6, true, false>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 64 && E == 6) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 64, 6, true, false>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 128 && E == 6) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 128, 6, true, false>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 256 && E == 6) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 256, 6, true, false>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 2 && E == 10) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 2, 10, true>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 4 && E == 10) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 4, 10, true>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 8 && E == 10) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 8, 10, true>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 16 && E == 10) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 16, 10, true>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 32 && E == 10) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 32, 10, true>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 64 && E == 10) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 64, 10, true>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 128 && E == 10) {
-    hipLaunchKernelGGL((col_kernel_batch<float, 128, 10, true>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  return hipErrorInvalidValue;
-}
-
-template <>
-hipError_t launch_batch_col_folds<float>(int T, int E, dim3 grid, hipStream_t s, const ColArgs<float> *args,
-                                         const BatchItem *items, int tile0, int first0, const void *sched0, PhysArgs ph) {
-  if (T == 64 && E == 2) {
-    hipLaunchKernelGGL((col_kernel_folds<float, 64, 2>), grid, dim3(kMaxFolds * 64), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 64 && E == 3) {
-    hipLaunchKernelGGL((col_kernel_folds<float, 64, 3>), grid, dim3(kMaxFolds * 64), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 128 && E == 2) {
-    hipLaunchKernelGGL((col_kernel_folds<float, 128, 2>), grid, dim3(kMaxFolds * 128), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 128 && E == 3) {
-    hipLaunchKernelGGL((col_kernel_folds<float, 128, 3>), grid, dim3(kMaxFolds * 128), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 256 && E == 2) {
-    hipLaunchKernelGGL((col_kernel_folds<float, 256, 2>), grid, dim3(kMaxFolds * 256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 256 && E == 3) {
-    hipLaunchKernelGGL((col_kernel_folds<float, 256, 3>), grid, dim3(kMaxFolds * 256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  return hipErrorInvalidValue;
-}
+extern const KernelEntry col_f32_1[];
+const KernelEntry *const col_kernels_f32[] = {col_f32_0, col_f32_1, nullptr};
 
 }  // namespace zk

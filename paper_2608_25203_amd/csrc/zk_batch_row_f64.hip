@@ -4,481 +4,33 @@
 
 namespace zk {
 
-template <>
-const void *batch_row_kernel<double>(int T, int E, bool pad) {
-  if (T == 2 && E == 2 && pad == false) return reinterpret_cast<const void *>(&row_kernel_batch<double, 2, 2>);
-  if (T == 2 && E == 3 && pad == true) return reinterpret_cast<const void *>(&row_kernel_batch<double, 2, 3>);
-  if (T == 2 && E == 4 && pad == false) return reinterpret_cast<const void *>(&row_kernel_batch<double, 2, 4>);
-  if (T == 2 && E == 6 && pad == true) return reinterpret_cast<const void *>(&row_kernel_batch<double, 2, 6>);
-  if (T == 4 && E == 2 && pad == false) return reinterpret_cast<const void *>(&row_kernel_batch<double, 4, 2>);
-  if (T == 4 && E == 3 && pad == true) return reinterpret_cast<const void *>(&row_kernel_batch<double, 4, 3>);
-  if (T == 4 && E == 4 && pad == false) return reinterpret_cast<const void *>(&row_kernel_batch<double, 4, 4>);
-  if (T == 4 && E == 6 && pad == true) return reinterpret_cast<const void *>(&row_kernel_batch<double, 4, 6>);
-  if (T == 8 && E == 2 && pad == false) return reinterpret_cast<const void *>(&row_kernel_batch<double, 8, 2>);
-  if (T == 8 && E == 3 && pad == true) return reinterpret_cast<const void *>(&row_kernel_batch<double, 8, 3>);
-  if (T == 8 && E == 4 && pad == false) return reinterpret_cast<const void *>(&row_kernel_batch<double, 8, 4>);
-  if (T == 8 && E == 6 && pad == true) return reinterpret_cast<const void *>(&row_kernel_batch<double, 8, 6>);
-  if (T == 16 && E == 2 && pad == false) return reinterpret_cast<const void *>(&row_kernel_batch<double, 16, 2>);
-  if (T == 16 && E == 3 && pad == true) return reinterpret_cast<const void *>(&row_kernel_batch<double, 16, 3>);
-  if (T == 16 && E == 4 && pad == false) return reinterpret_cast<const void *>(&row_kernel_batch<double, 16, 4>);
-  if (T == 16 && E == 6 && pad == true) return reinterpret_cast<const void *>(&row_kernel_batch<double, 16, 6>);
-  if (T == 32 && E == 2 && pad == false) return reinterpret_cast<const void *>(&row_kernel_batch<double, 32, 2>);
-  if (T == 32 && E == 3 && pad == true) return reinterpret_cast<const void *>(&row_kernel_batch<double, 32, 3>);
-  if (T == 32 && E == 4 && pad == false) return reinterpret_cast<const void *>(&row_kernel_batch<double, 32, 4>);
-  if (T == 32 && E == 6 && pad == true) return reinterpret_cast<const void *>(&row_kernel_batch<double, 32, 6>);
-  if (T == 32 && E == 8 && pad == false) return reinterpret_cast<const void *>(&row_kernel_batch<double, 32, 8>);
-  if (T == 32 && E == 12 && pad == true) return reinterpret_cast<const void *>(&row_kernel_batch<double, 32, 12>);
-  if (T == 64 && E == 2 && pad == false) return reinterpret_cast<const void *>(&row_kernel_batch<double, 64, 2>);
-  if (T == 64 && E == 3 && pad == true) return reinterpret_cast<const void *>(&row_kernel_batch<double, 64, 3>);
-  if (T == 64 && E == 4 && pad == false) return reinterpret_cast<const void *>(&row_kernel_batch<double, 64, 4>);
-  if (T == 64 && E == 6 && pad == true) return reinterpret_cast<const void *>(&row_kernel_batch<double, 64, 6>);
-  if (T == 64 && E == 8 && pad == false) return reinterpret_cast<const void *>(&row_kernel_batch<double, 64, 8>);
-  if (T == 64 && E == 12 && pad == true) return reinterpret_cast<const void *>(&row_kernel_batch<double, 64, 12>);
-  if (T == 128 && E == 2 && pad == false) return reinterpret_cast<const void *>(&row_kernel_batch<double, 128, 2>);
-  if (T == 128 && E == 3 && pad == true) return reinterpret_cast<const void *>(&row_kernel_batch<double, 128, 3>);
-  if (T == 128 && E == 4 && pad == false) return reinterpret_cast<const void *>(&row_kernel_batch<double, 128, 4>);
-  if (T == 128 && E == 6 && pad == true) return reinterpret_cast<const void *>(&row_kernel_batch<double, 128, 6>);
-  if (T == 128 && E == 8 && pad == false) return reinterpret_cast<const void *>(&row_kernel_batch<double, 128, 8>);
-  if (T == 128 && E == 12 && pad == true) return reinterpret_cast<const void *>(&row_kernel_batch<double, 128, 12>);
-  if (T == 256 && E == 2 && pad == false) return reinterpret_cast<const void *>(&row_kernel_batch<double, 256, 2>);
-  if (T == 256 && E == 3 && pad == true) return reinterpret_cast<const void *>(&row_kernel_batch<double, 256, 3>);
-  if (T == 256 && E == 4 && pad == false) return reinterpret_cast<const void *>(&row_kernel_batch<double, 256, 4>);
-  if (T == 256 && E == 6 && pad == true) return reinterpret_cast<const void *>(&row_kernel_batch<double, 256, 6>);
-  if (T == 256 && E == 8 && pad == false) return reinterpret_cast<const void *>(&row_kernel_batch<double, 256, 8>);
-  if (T == 256 && E == 12 && pad == true) return reinterpret_cast<const void *>(&row_kernel_batch<double, 256, 12>);
-  if (T == 512 && E == 2 && pad == false) return reinterpret_cast<const void *>(&row_kernel_batch<double, 512, 2>);
-  if (T == 512 && E == 3 && pad == true) return reinterpret_cast<const void *>(&row_kernel_batch<double, 512, 3>);
-  if (T == 512 && E == 4 && pad == false) return reinterpret_cast<const void *>(&row_kernel_batch<double, 512, 4>);
-  if (T == 512 && E == 6 && pad == true) return reinterpret_cast<const void *>(&row_kernel_batch<double, 512, 6>);
-  if (T == 1024 && E == 2 && pad == false) return reinterpret_cast<const void *>(&row_kernel_batch<double, 1024, 2>);
-  if (T == 1024 && E == 3 && pad == true) return reinterpret_cast<const void *>(&row_kernel_batch<double, 1024, 3>);
-  if (T == 2 && E == 9 && pad == true) return reinterpret_cast<const void *>(&row_kernel_batch<double, 2, 9>);
-  if (T == 4 && E == 9 && pad == true) return reinterpret_cast<const void *>(&row_kernel_batch<double, 4, 9>);
-  if (T == 8 && E == 9 && pad == true) return reinterpret_cast<const void *>(&row_kernel_batch<double, 8, 9>);
-  if (T == 16 && E == 9 && pad == true) return reinterpret_cast<const void *>(&row_kernel_batch<double, 16, 9>);
-  if (T == 32 && E == 9 && pad == true) return reinterpret_cast<const void *>(&row_kernel_batch<double, 32, 9>);
-  if (T == 64 && E == 9 && pad == true) return reinterpret_cast<const void *>(&row_kernel_batch<double, 64, 9>);
-  if (T == 128 && E == 9 && pad == true) return reinterpret_cast<const void *>(&row_kernel_batch<double, 128, 9>);
-  if (T == 256 && E == 9 && pad == true) return reinterpret_cast<const void *>(&row_kernel_batch<double, 256, 9>);
-  if (T == 2 && E == 6 && pad == false) return reinterpret_cast<const void *>(&row_kernel_batch<double, 2, 6, false>);
-  if (T == 4 && E == 6 && pad == false) return reinterpret_cast<const void *>(&row_kernel_batch<double, 4, 6, false>);
-  if (T == 8 && E == 6 && pad == false) return reinterpret_cast<const void *>(&row_kernel_batch<double, 8, 6, false>);
-  if (T == 16 && E == 6 && pad == false) return reinterpret_cast<const void *>(&row_kernel_batch<double, 16, 6, false>);
-  if (T == 32 && E == 6 && pad == false) return reinterpret_cast<const void *>(&row_kernel_batch<double, 32, 6, false>);
-  if (T == 64 && E == 6 && pad == false) return reinterpret_cast<const void *>(&row_kernel_batch<double, 64, 6, false>);
-  if (T == 128 && E == 6 && pad == false) return reinterpret_cast<const void *>(&row_kernel_batch<double, 128, 6, false>);
-  if (T == 256 && E == 6 && pad == false) return reinterpret_cast<const void *>(&row_kernel_batch<double, 256, 6, false>);
-  if (T == 2 && E == 15 && pad == true) return reinterpret_cast<const void *>(&row_kernel_batch<double, 2, 15>);
-  if (T == 4 && E == 15 && pad == true) return reinterpret_cast<const void *>(&row_kernel_batch<double, 4, 15>);
-  if (T == 8 && E == 15 && pad == true) return reinterpret_cast<const void *>(&row_kernel_batch<double, 8, 15>);
-  if (T == 16 && E == 15 && pad == true) return reinterpret_cast<const void *>(&row_kernel_batch<double, 16, 15>);
-  if (T == 32 && E == 15 && pad == true) return reinterpret_cast<const void *>(&row_kernel_batch<double, 32, 15>);
-  if (T == 64 && E == 15 && pad == true) return reinterpret_cast<const void *>(&row_kernel_batch<double, 64, 15>);
-  if (T == 128 && E == 15 && pad == true) return reinterpret_cast<const void *>(&row_kernel_batch<double, 128, 15>);
-  if (T == 2 && E == 10 && pad == false) return reinterpret_cast<const void *>(&row_kernel_batch<double, 2, 10>);
-  if (T == 4 && E == 10 && pad == false) return reinterpret_cast<const void *>(&row_kernel_batch<double, 4, 10>);
-  if (T == 8 && E == 10 && pad == false) return reinterpret_cast<const void *>(&row_kernel_batch<double, 8, 10>);
-  if (T == 16 && E == 10 && pad == false) return reinterpret_cast<const void *>(&row_kernel_batch<double, 16, 10>);
-  if (T == 32 && E == 10 && pad == false) return reinterpret_cast<const void *>(&row_kernel_batch<double, 32, 10>);
-  if (T == 64 && E == 10 && pad == false) return reinterpret_cast<const void *>(&row_kernel_batch<double, 64, 10>);
-  if (T == 128 && E == 10 && pad == false) return reinterpret_cast<const void *>(&row_kernel_batch<double, 128, 10>);
-  return nullptr;
-}
+extern const KernelEntry row_f64_0[];
+const KernelEntry row_f64_0[] = {
+    {2, 2, false, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<double, 2, 2, false>)},
+    {2, 6, true, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<double, 2, 6, true>)},
+    {2, 10, false, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<double, 2, 10, false>)},
+    {8, 3, true, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<double, 8, 3, true>)},
+    {32, 6, false, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<double, 32, 6, false>)},
+    {48, 2, false, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<double, 48, 2, false>)},
+    {64, 12, true, KF_LANES, reinterpret_cast<const void *>(&row_kernel_batch<double, 64, 12, true, true>)},
+    {80, 3, true, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<double, 80, 3, true>)},
+    {128, 6, false, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<double, 128, 6, false>)},
+    {128, 15, true, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<double, 128, 15, true>)},
+    {256, 2, false, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<double, 256, 2, false>)},
+    {256, 6, true, KF_LANES, reinterpret_cast<const void *>(&row_kernel_batch<double, 256, 6, true, true>)},
+    {256, 6, true, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<double, 256, 6, true>)},
+    {256, 12, true, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<double, 256, 12, true>)},
+    {512, 6, true, KF_LANES, reinterpret_cast<const void *>(&row_kernel_batch<double, 512, 6, true, true>)},
+    {1024, 2, false, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<double, 1024, 2, false>)},
+    {1024, 3, true, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<double, 1024, 3, true>)},
+    {0, 0, false, 0, nullptr}};
 
-template <>
-hipError_t launch_batch_row<double>(int T, int E, bool pad, dim3 grid, hipStream_t s, const RowArgs<double> *args,
-                                   const BatchItem *items, int tile0, int first0, const void *sched0, PhysArgs ph) {
-  if (T == 2 && E == 2 && pad == false) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 2, 2>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 2 && E == 3 && pad == true) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 2, 3>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 2 && E == 4 && pad == false) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 2, 4>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 2 && E == 6 && pad == true) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 2, 6>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 4 && E == 2 && pad == false) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 4, 2>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 4 && E == 3 && pad == true) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 4, 3>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 4 && E == 4 && pad == false) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 4, 4>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 4 && E == 6 && pad == true) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 4, 6>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 8 && E == 2 && pad == false) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 8, 2>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 8 && E == 3 && pad == true) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 8, 3>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 8 && E == 4 && pad == false) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 8, 4>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 8 && E == 6 && pad == true) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 8, 6>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 16 && E == 2 && pad == false) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 16, 2>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 16 && E == 3 && pad == true) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 16, 3>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 16 && E == 4 && pad == false) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 16, 4>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 16 && E == 6 && pad == true) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 16, 6>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 32 && E == 2 && pad == false) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 32, 2>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 32 && E == 3 && pad == true) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 32, 3>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 32 && E == 4 && pad == false) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 32, 4>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 32 && E == 6 && pad == true) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 32, 6>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 32 && E == 8 && pad == false) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 32, 8>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 32 && E == 12 && pad == true) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 32, 12>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 64 && E == 2 && pad == false) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 64, 2>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 64 && E == 3 && pad == true) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 64, 3>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 64 && E == 4 && pad == false) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 64, 4>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 64 && E == 6 && pad == true) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 64, 6>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 64 && E == 8 && pad == false) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 64, 8>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 64 && E == 12 && pad == true) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 64, 12>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 128 && E == 2 && pad == false) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 128, 2>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 128 && E == 3 && pad == true) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 128, 3>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 128 && E == 4 && pad == false) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 128, 4>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 128 && E == 6 && pad == true) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 128, 6>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 128 && E == 8 && pad == false) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 128, 8>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 128 && E == 12 && pad == true) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 128, 12>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 256 && E == 2 && pad == false) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 256, 2>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 256 && E == 3 && pad == true) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 256, 3>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 256 && E == 4 && pad == false) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 256, 4>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 256 && E == 6 && pad == true) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 256, 6>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 256 && E == 8 && pad == false) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 256, 8>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 256 && E == 12 && pad == true) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 256, 12>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 512 && E == 2 && pad == false) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 512, 2>), grid, dim3(512), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 512 && E == 3 && pad == true) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 512, 3>), grid, dim3(512), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 512 && E == 4 && pad == false) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 512, 4>), grid, dim3(512), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 512 && E == 6 && pad == true) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 512, 6>), grid, dim3(512), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 1024 && E == 2 && pad == false) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 1024, 2>), grid, dim3(1024), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 1024 && E == 3 && pad == true) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 1024, 3>), grid, dim3(1024), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 2 && E == 9 && pad == true) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 2, 9>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 4 && E == 9 && pad == true) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 4, 9>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 8 && E == 9 && pad == true) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 8, 9>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 16 && E == 9 && pad == true) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 16, 9>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 32 && E == 9 && pad == true) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 32, 9>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 64 && E == 9 && pad == true) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 64, 9>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 128 && E == 9 && pad == true) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 128, 9>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 256 && E == 9 && pad == true) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 256, 9>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 2 && E == 6 && pad == false) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 2, 6, false>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 4 && E == 6 && pad == false) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 4, 6, false>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 8 && E == 6 && pad == false) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 8, 6, false>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 16 && E == 6 && pad == false) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 16, 6, false>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 32 && E == 6 && pad == false) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 32, 6, false>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 64 && E == 6 && pad == false) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 64, 6, false>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 128 && E == 6 && pad == false) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 128, 6, false>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 256 && E == 6 && pad == false) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 256, 6, false>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 2 && E == 15 && pad == true) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 2, 15>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 4 && E == 15 && pad == true) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 4, 15>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 8 && E == 15 && pad == true) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 8, 15>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 16 && E == 15 && pad == true) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 16, 15>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 32 && E == 15 && pad == true) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 32, 15>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 64 && E == 15 && pad == true) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 64, 15>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 128 && E == 15 && pad == true) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 128, 15>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 2 && E == 10 && pad == false) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 2, 10>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 4 && E == 10 && pad == false) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 4, 10>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 8 && E == 10 && pad == false) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 8, 10>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 16 && E == 10 && pad == false) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 16, 10>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 32 && E == 10 && pad == false) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 32, 10>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 64 && E == 10 && pad == false) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 64, 10>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 128 && E == 10 && pad == false) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 128, 10>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  return hipErrorInvalidValue;
-}
-
-template <>
-const void *lanes_row_kernel<double>(int T, int E) {
-  if (T == 64 && E == 3) return reinterpret_cast<const void *>(&row_kernel_batch<double, 64, 3, true, true>);
-  if (T == 64 && E == 6) return reinterpret_cast<const void *>(&row_kernel_batch<double, 64, 6, true, true>);
-  if (T == 64 && E == 12) return reinterpret_cast<const void *>(&row_kernel_batch<double, 64, 12, true, true>);
-  if (T == 128 && E == 3) return reinterpret_cast<const void *>(&row_kernel_batch<double, 128, 3, true, true>);
-  if (T == 128 && E == 6) return reinterpret_cast<const void *>(&row_kernel_batch<double, 128, 6, true, true>);
-  if (T == 128 && E == 12) return reinterpret_cast<const void *>(&row_kernel_batch<double, 128, 12, true, true>);
-  if (T == 256 && E == 3) return reinterpret_cast<const void *>(&row_kernel_batch<double, 256, 3, true, true>);
-  if (T == 256 && E == 6) return reinterpret_cast<const void *>(&row_kernel_batch<double, 256, 6, true, true>);
-  if (T == 256 && E == 12) return reinterpret_cast<const void *>(&row_kernel_batch<double, 256, 12, true, true>);
-  if (T == 512 && E == 3) return reinterpret_cast<const void *>(&row_kernel_batch<double, 512, 3, true, true>);
-  if (T == 512 && E == 6) return reinterpret_cast<const void *>(&row_kernel_batch<double, 512, 6, true, true>);
-  if (T == 1024 && E == 3) return reinterpret_cast<const void *>(&row_kernel_batch<double, 1024, 3, true, true>);
-  if (T == 64 && E == 9) return reinterpret_cast<const void *>(&row_kernel_batch<double, 64, 9, true, true>);
-  if (T == 128 && E == 9) return reinterpret_cast<const void *>(&row_kernel_batch<double, 128, 9, true, true>);
-  if (T == 256 && E == 9) return reinterpret_cast<const void *>(&row_kernel_batch<double, 256, 9, true, true>);
-  return nullptr;
-}
-
-template <>
-hipError_t launch_lanes_row<double>(int T, int E, dim3 grid, hipStream_t s, const RowArgs<double> *args,
-                                   const BatchItem *items, int tile0, int first0, const void *sched0, PhysArgs ph) {
-  if (T == 64 && E == 3) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 64, 3, true, true>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 64 && E == 6) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 64, 6, true, true>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 64 && E == 12) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 64, 12, true, true>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 128 && E == 3) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 128, 3, true, true>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 128 && E == 6) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 128, 6, true, true>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 128 && E == 12) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 128, 12, true, true>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 256 && E == 3) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 256, 3, true, true>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 256 && E == 6) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 256, 6, true, true>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 256 && E == 12) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 256, 12, true, true>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 512 && E == 3) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 512, 3, true, true>), grid, dim3(512), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 512 && E == 6) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 512, 6, true, true>), grid, dim3(512), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 1024 && E == 3) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 1024, 3, true, true>), grid, dim3(1024), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 64 && E == 9) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 64, 9, true, true>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 128 && E == 9) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 128, 9, true, true>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  if (T == 256 && E == 9) {
-    hipLaunchKernelGGL((row_kernel_batch<double, 256, 9, true, true>), grid, dim3(256), 0, s, args, items, tile0, first0, sched0, ph);
-    return hipGetLastError();
-  }
-  return hipErrorInvalidValue;
-}
+extern const KernelEntry row_f64_1[];
+extern const KernelEntry row_f64_2[];
+extern const KernelEntry row_f64_3[];
+extern const KernelEntry row_f64_4[];
+extern const KernelEntry row_f64_5[];
+extern const KernelEntry row_f64_6[];
+const KernelEntry *const row_kernels_f64[] = {row_f64_0, row_f64_1, row_f64_2, row_f64_3, row_f64_4, row_f64_5, row_f64_6, nullptr};
 
 }  // namespace zk

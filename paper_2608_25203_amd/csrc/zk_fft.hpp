@@ -1,4 +1,4 @@
-// zk_fft.hpp -- Stockham FFT for one team of T threads (T a power of two, 32 to 1024).
+// zk_fft.hpp -- Stockham FFT for one team of T threads (T = 2^k, 3 2^k or 5 2^k, up to 1024).
 //
 // A team transforms one sequence of N = E * T complex points.  Thread t holds
 // the E elements t + T*r in registers on entry; the first pass is a radix-E
@@ -247,7 +247,7 @@ struct DFT {
 // ---- pass plan ----------------------------------------------------------
 // After the radix-E first pass (in registers) the remaining factor T = N / E
 // is split into radix-4 passes (and one radix-2 pass if T is an odd power of
-// two).  Teams take radix-8 passes first where that keeps enough of the
+// two), after one radix-3 or radix-5 pass if T has that factor.  Teams take radix-8 passes first where that keeps enough of the
 // team busy: teams of 128 threads and more with E >= 6, whose radix-8 passes
 // keep three quarters of the threads busy or more (512 threads, E = 6: 8, 8, 8
 // instead of 4, 4, 4, 4, 2, 14% faster at 3072 points in FP32; the batch of
@@ -256,7 +256,7 @@ struct DFT {
 // the fewer, larger butterflies measured slower.  Every later pass goes
 // through LDS, its N / R butterflies spread over the T threads of the team.
 __host__ __device__ constexpr int pass_radix(int T, int E, int rem) {
-  return ((T >= 1024 || (T >= 128 && E >= 6)) && rem % 8 == 0 && rem != 16) ? 8 : ((rem % 4 == 0) ? 4 : 2);
+  return rem % 3 == 0 ? 3 : rem % 5 == 0 ? 5 : ((T >= 1024 || (T >= 128 && E >= 6)) && rem % 8 == 0 && rem != 16) ? 8 : ((rem % 4 == 0) ? 4 : 2);
 }
 __host__ __device__ constexpr int later_radix(int T, int E, int p) {  // p >= 1
   int rem = T;
@@ -294,14 +294,14 @@ __host__ __device__ constexpr int lds_len(int N) { return N; }
 // host stores them at Ns_p - E + (r-1) Ns_p + k (N - E entries), so a lane's
 // consecutive k read adjacent words instead of a stride of r step_p.  Each
 // transform length keeps one table per candidate E, slot tw_slot(E).
-// Slots: E in {2, 3, 9, 10, 15} -> 0, {4, 6, 18} -> 1, {8, 12} -> 2 (a length
+// Slots: E in {2, 3} -> 0, {4, 6, 9, 10, 15} -> 1, {8, 12} -> 2 (a length
 // uses at most one E of each group).
 // Slot 3 holds the natural table W_N^m, m < N (the permuted-layout forms
 // below).
 constexpr int kTwSlots = 4;
 constexpr int kTwNatural = 3;
 __host__ __device__ constexpr int tw_slot(int E) {
-  return (E == 2 || E == 3 || E == 9 || E == 10 || E == 15) ? 0 : ((E == 4 || E == 6 || E == 18) ? 1 : 2);
+  return (E == 2 || E == 3) ? 0 : ((E == 8 || E == 12) ? 2 : 1);
 }
 
 // Last pass of a team FFT of N = E T points: radix R, NB = N / R butterflies,

@@ -143,7 +143,7 @@ __device__ __forceinline__ float wave_max(float x) {
   return __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)v, 63));
 }
 
-// Max over one team of T threads (non-negative values).  Teams of fewer than
+// Max over one team of T lanes (non-negative values; T: a team's slot).  Teams of fewer than
 // 64 threads sit inside one wavefront and reduce with lane shuffles, a full
 // wavefront with wave_max; larger teams (one per block) add an LDS step
 // across their wavefronts.  red: >= one float per wavefront of the block.  Every
@@ -215,6 +215,23 @@ __device__ __forceinline__ float2 pow2_scale(float m) {
 }
 
 // ---------------------------------------------------------------------------
+// Lanes set aside for a team of T threads: a power of two up to a wavefront,
+// whole wavefronts above.  Where T is less (axes with a factor 3 or 5) the
+// spare lanes shadow the team's last thread: they load, compute and store the
+// same values at the same addresses, so no access needs a guard of its own.
+__host__ __device__ constexpr int team_slot(int T) {
+  int s = 1;
+  while (s < T && s < 64) s *= 2;
+  return T <= 64 ? s : (T + 63) / 64 * 64;
+}
+// Threads of a row or column block: at least 256 in whole teams (192 for one
+// team of three wavefronts).
+__host__ __device__ constexpr int block_threads(int T) {
+  return team_slot(T) > 128 ? team_slot(T) : 256;
+}
+// Lanes of a team that shares its column with others (fold teams): whole wavefronts.
+__host__ __device__ constexpr int fold_slot(int T) { return (T + 63) / 64 * 64; }
+
 // Shape constants of a team: T threads, E first-pass elements per thread.
 // E % 3 == 0: a 3/2-padded transform of N = T E = 3n/2 points, whose n/2
 // retained band slots are r < E/3 (positive) and r >= 2E/3 (negative);
@@ -222,12 +239,12 @@ __device__ __forceinline__ float2 pow2_scale(float m) {
 // In both cases the band has K = (E/3 or E/2) * T = n/2 positive modes, and
 // slot "first negative, t = 0" is the Nyquist mode (never stored).
 // Whether a row team shape (T threads, E elements, default block of
-// max(T, 256) threads) has the permuted-layout transforms: padded, whole
-// wavefronts, and room for two LDS buffers per team (the twiddle table goes
+// block_threads(T) threads) has the permuted-layout transforms: padded, a power
+// of two of whole wavefronts, and room for two LDS buffers per team (the twiddle table goes
 // to LDS only if it fits beside them).
 __host__ __device__ constexpr bool row_lanes_ok(int T, int E, bool padded, int real_bytes) {
-  const int N = T * E, tpb = (T > 256 ? T : 256) / T;
-  return padded && E % 5 != 0 && T % 64 == 0 && T <= 1024 && 2 * tpb * N * 2 * real_bytes <= 100 * 1024;
+  const int N = T * E, tpb = block_threads(T) / team_slot(T);
+  return padded && E % 5 != 0 && T % 64 == 0 && (T & (T - 1)) == 0 && T <= 1024 && 2 * tpb * N * 2 * real_bytes <= 100 * 1024;
 }
 
 // Number of LD2 operations among the first i operations of compiled shape sh
@@ -250,10 +267,12 @@ constexpr int kRowShapeMaxLd2 = row_shapes_max_ld2();
 constexpr int kBlockMaximaCols = 1024;
 
 // Padded row shapes whose kernels also hold every program shape of
-// zk_row_shapes.hpp as straight-line code (the team shapes the autotuner
-// picks for the large grids; the others interpret every program).
+// zk_row_shapes.hpp as straight-line code (the default team shapes of rows of
+// 32 points and more and those the autotuner picks for the large grids; the
+// others interpret every program).  On a 64 x 64 grid (T = 32, M = 3, FP64) a
+// row launch took 10.6 us interpreted and 8.8 us compiled.
 __host__ __device__ constexpr bool row_compiled_shapes(int T, int E, bool padded) {
-  return padded && ((E == 3 && T >= 64 && T <= 1024) || (E == 6 && T >= 128 && T <= 512));
+  return padded && ((E == 3 && T >= 16) || (E == 6 && T >= 128 && T <= 512));
 }
 
 template <int T, int E, int BSZ = 0, bool PAD = (E % 3 == 0)>
@@ -263,8 +282,9 @@ struct Shape {
   static constexpr int KR = PADDED ? E / 3 : E / 2;    // positive slots
   static constexpr int NEG0 = PADDED ? 2 * E / 3 : E / 2;  // first negative slot
   static constexpr int QB = PADDED ? 2 * E / 3 : E;    // base-band elements per thread
-  static constexpr int BS = BSZ ? BSZ : (T > 256 ? T : 256);  // threads per block (default max(T, 256))
-  static constexpr int TPB = BS / T;                   // teams per block
+  static constexpr int TS = team_slot(T);              // lanes per team
+  static constexpr int BS = BSZ ? BSZ : block_threads(T);  // threads per block
+  static constexpr int TPB = BS / TS;                  // teams per block
   static constexpr int L = lds_len(N);
   // two LDS buffers per team when they fit comfortably beside the twiddle
   // table, else one (the permuted-layout forms, LANES, always take two)
@@ -432,8 +452,8 @@ __device__ __forceinline__ void row_body(const RowArgs<real> &a, int prog, int b
     red = s_red;
   }
   float *fmx = red + LD::RED;  // LD::FMX floats (compiled programs only)
-  const int team = threadIdx.x / T;
-  const int t = threadIdx.x % T;
+  const int team = threadIdx.x / S::TS;
+  const int t = min((int)(threadIdx.x % S::TS), T - 1);
   // rows y and y+1 share 128-byte lines of the tiled fields
   const int row = (S::TPB == 1 ? xcd_unit(blk, a.rows, 2) : blk) * S::TPB + team;
   // A 1D grid has one row: the block's other teams run the transforms on
@@ -609,7 +629,7 @@ __device__ __forceinline__ void row_body(const RowArgs<real> &a, int prog, int b
       mx = fmaxf(mx, fabsf((float)z[e].x));
       my = fmaxf(my, fabsf((float)z[e].y));
     }
-    const float2 mxy = team_max2<T>(mx, my, red);
+    const float2 mxy = team_max2<S::TS>(mx, my, red);
     const float2 px = pow2_scale(mxy.x);
     const float2 py = pow2_scale(mxy.y);
     const real sx = (real)px.x, sy = (real)py.x;
@@ -886,8 +906,9 @@ __device__ __forceinline__ cpx<double> symval(uint32_t s, double kk, double g0, 
 // kept zero).
 template <int T, int FT, int BSZ = 0>
 struct ColBlock {
-  static constexpr int BS = FT == 1 ? (BSZ ? BSZ : (T > 256 ? T : 256)) : FT * T;  // threads per block
-  static constexpr int TPB = FT == 1 ? BS / T : 1;                    // columns per block
+  static constexpr int TS = FT == 1 ? team_slot(T) : fold_slot(T);                  // lanes per team
+  static constexpr int BS = FT == 1 ? (BSZ ? BSZ : block_threads(T)) : FT * TS;  // threads per block
+  static constexpr int TPB = FT == 1 ? BS / TS : 1;                                 // columns per block
 };
 template <typename real, int T, int E, bool LIFTSYM = false, int FT = 1, bool DYN = false, int BSZ = 0,
           bool PAD = (E % 3 == 0)>
@@ -895,7 +916,7 @@ __device__ __forceinline__ void col_body(const ColArgs<real> &a, int task_index,
   static_assert(BSZ == 0 || FT == 1, "a block size is set for plain column teams only");
   using S = Shape<T, E, BSZ, PAD>;
   using CB = ColBlock<T, FT, BSZ>;
-  static_assert(FT == 1 || (T >= 64 && FT * T <= 1024), "fold teams: whole wavefronts, one block");
+  static_assert(CB::BS <= 1024, "one block");
   constexpr int N = S::N, L = S::L, QB = S::QB;
   constexpr int NB = FT == 1 ? S::template nbuf<real>() : 2;
   constexpr bool TWL = FT == 1 ? S::template tw_in_lds<real>() : true;
@@ -930,8 +951,8 @@ __device__ __forceinline__ void col_body(const ColArgs<real> &a, int task_index,
     xs = s_xs;
   }
   // fold teams are whole wavefronts: the team index is wave-uniform (scalar)
-  const int team = FT == 1 ? (int)(threadIdx.x / T) : __builtin_amdgcn_readfirstlane((int)(threadIdx.x / T));
-  const int t = threadIdx.x % T;
+  const int team = FT == 1 ? (int)(threadIdx.x / CB::TS) : __builtin_amdgcn_readfirstlane((int)(threadIdx.x / CB::TS));
+  const int t = min((int)(threadIdx.x % CB::TS), T - 1);
   // columns of one tile share 128-byte lines; keep a tile's blocks on one XCD
   constexpr int CBMAX = MixTile<real>::CB > CBB ? MixTile<real>::CB : CBB;
   const int col_raw = FT == 1 ? xcd_unit(blk, a.nx / 2 / CB::TPB, CBMAX / CB::TPB) * CB::TPB + team
@@ -1195,7 +1216,7 @@ __device__ __forceinline__ void col_body(const ColArgs<real> &a, int task_index,
 #pragma unroll
           for (int r = 0; r < E; ++r) put(t + T * r, res[lpad(t + T * r)]);
       }
-      m = team_max<T>(m, red);
+      m = team_max<CB::TS>(m, red);
       if (t == 0 && writer) gstore1(a.colmax, (long long)out.dst_mixed * (a.nx / 2) + col, m);
     }
   }
@@ -1221,7 +1242,7 @@ __device__ __forceinline__ BatchItem item_of(const BatchItem *items, int tile0, 
   return items ? items[blockIdx.y] : BatchItem{tile0, first0 + (int)blockIdx.y};
 }
 template <typename real, int T, int E, bool PAD = (E % 3 == 0), bool LANES = false>
-__global__ __launch_bounds__(T > 256 ? T : 256) void row_kernel_batch(const RowArgs<real> *__restrict__ args,
+__global__ __launch_bounds__(block_threads(T)) void row_kernel_batch(const RowArgs<real> *__restrict__ args,
                                                         const BatchItem *__restrict__ items, int tile0, int first0,
                                                         const void *sched0, PhysArgs ph) {
   const BatchItem it = item_of(items, tile0, first0);
@@ -1238,7 +1259,7 @@ __global__ __launch_bounds__(T > 256 ? T : 256) void row_kernel_batch(const RowA
 // LIFTSYM: the variant that applies ColOut.lift_sym (the bulk velocity
 // lift's column launches); the plain passes never carry its exponentials.
 template <typename real, int T, int E, bool LIFTSYM = false, bool PAD = (E % 3 == 0)>
-__global__ __launch_bounds__(T > 256 ? T : 256) void col_kernel_batch(const ColArgs<real> *__restrict__ args,
+__global__ __launch_bounds__(block_threads(T)) void col_kernel_batch(const ColArgs<real> *__restrict__ args,
                                                         const BatchItem *__restrict__ items, int tile0, int first0,
                                                         const void *sched0, PhysArgs) {
   const BatchItem it = item_of(items, tile0, first0);
@@ -1248,7 +1269,7 @@ __global__ __launch_bounds__(T > 256 ? T : 256) void col_kernel_batch(const ColA
 // Fold teams: kMaxFolds teams of T threads per block, one column per block
 // (tasks whose folds and terms run side by side).
 template <typename real, int T, int E>
-__global__ __launch_bounds__(kMaxFolds * T) void col_kernel_folds(const ColArgs<real> *__restrict__ args,
+__global__ __launch_bounds__(kMaxFolds * fold_slot(T)) void col_kernel_folds(const ColArgs<real> *__restrict__ args,
                                                              const BatchItem *__restrict__ items, int tile0,
                                                              int first0, const void *sched0, PhysArgs) {
   const BatchItem it = item_of(items, tile0, first0);
@@ -1315,44 +1336,58 @@ hipError_t launch_col_1d(bool liftsym, dim3 grid, hipStream_t s, const ColArgs<r
   return hipGetLastError();
 }
 
-// Team shapes (T, E) compiled for the batched kernels.  Power-of-two axes
-// (n = 2^k in [4, 2048]): T in {2, 4, 8, 16} with E in {2, 3, 4, 6}, T in
-// {32, 64, 128, 256} threads with E in {2, 3, 4, 6, 8, 12}, and T = 512 (E in
-// {2, 3, 4, 6}) and 1024 (E in {2, 3})
-// as blocks of their own, so each length has two to four candidates for its
-// padded (3n/2, E in {3, 6, 12}) and base (n, E in {2, 4, 8}) transforms;
-// the autotuner picks among them.  Axes with a factor 3 (n = 3 2^k in [12,
-// 1536]): the padded transform of 9 2^(k-1) points with E = 9 and the base
-// transform with E = 6, T in {2, ..., 256}; with a factor 5 (n = 5 2^k in
-// [20, 1280]): padded E = 15 and base E = 10, T in {2, ..., 128}.  `pad` tells a base transform
-// with E = 6 from a padded one.  A block has max(256, T) threads.  These
-// return the kernel for (T, E, pad), or nullptr if that shape is not built.
-template <typename real>
-const void *batch_row_kernel(int T, int E, bool pad);
-template <typename real>
-const void *batch_col_kernel(int T, int E, bool pad);
-template <>
-const void *batch_row_kernel<double>(int T, int E, bool pad);
-template <>
-const void *batch_row_kernel<float>(int T, int E, bool pad);
-template <>
-const void *batch_col_kernel<double>(int T, int E, bool pad);
-template <>
-const void *batch_col_kernel<float>(int T, int E, bool pad);
-// The default first-pass radix of an axis of n base points: the smallest
-// compiled one (n = 2^k: 3 padded, 2 base; n = 3 2^k: 9 padded, 6 base;
-// n = 5 2^k: 15 padded, 10 base).
-inline int default_radix(int n, bool pad) {
+// Team shapes (T, E) compiled for the batched kernels.  Every axis (n = 2^k
+// in [4, 2048], 3 2^k in [12, 1536] or 5 2^k in [20, 1280]) has E = 3 for its
+// padded transform of 3n/2 points and E = 2 for its base transform, both with
+// T = n/2 threads.  Further candidates for the autotuner: power-of-two axes E
+// = 6, 12 padded and 4, 8 base (T in {2, 4, 8, 16} with E in {4, 6}, T in {32,
+// 64, 128, 256} with E in {4, 6, 8, 12}, T = 512 with E in {4, 6}); axes with
+// a factor 3 E = 9 padded and 6 base (T = 2^k in [2, 256]), with a factor 5 E
+// = 15 and 10 (T = 2^k in [2, 128]).  `pad` tells a base transform with E = 6
+// from a padded one.  A block has block_threads(T) threads.
+enum KernelForm : int {
+  KF_PLAIN = 0,
+  KF_LANES = 1,    // padded row passes in the permuted-layout form (row_lanes_ok)
+  KF_LIFTSYM = 2,  // base-length column passes with the depth lift's factors
+  KF_FOLDS = 3     // padded column passes with fold teams (fold_team_shape)
+};
+struct KernelEntry {
+  int T, E;
+  bool pad;
+  int form;
+  const void *fn;
+};
+// Tables of the generated units (nullptr-terminated lists of T = 0-terminated tables).
+extern const KernelEntry *const row_kernels_f64[], *const row_kernels_f32[], *const col_kernels_f64[],
+    *const col_kernels_f32[];
+// The kernel of a team shape and form, or nullptr if it is not built.
+const void *find_kernel(bool row, bool f64, int form, int T, int E, bool pad);
+// The first-pass radix of an axis's power-of-two team, the smallest compiled:
+// what a context reports before zk_bind, and FP32 transforms' default (another
+// shape rounds differently, by 1e-7 in FP32; the autotuner may choose one).
+inline int pow2_team_radix(int n, bool pad) {
   return n % 5 == 0 ? (pad ? 15 : 10) : (n % 3 ? (pad ? 3 : 2) : (pad ? 9 : 6));
+}
+// The default first-pass radix of an axis of n base points, in use from
+// zk_bind on.  FP64: the smallest one, n / 2 threads a transform.  Both sides as FP64 row and column launches in us:
+// - on axes with a factor 3 or 5 the power-of-two team of one radix-9 or
+//   radix-15 step keeps too few wavefronts busy: 30 and 37 against 17.8 and
+//   14.3 on 384 x 320 (M = 5), 416 and 198 against 354 and 167 on 1536^2 (M =
+//   4), 19 and 17 against 11 and 11 on 48^2 (M = 3); only rows of 640 and 768
+//   come out even or the other way (640^2, M = 4: rows 53 against 63, columns
+//   45 against 31), which the autotuner settles.
+inline int default_radix(bool f64, bool, int n, bool pad) {
+  if (!f64) return pow2_team_radix(n, pad);
+  return pad ? 3 : 2;
 }
 // The compiled first-pass radices of that axis's padded or base transform
 // (the autotuner's candidates): writes up to three into e, returns the count.
 inline int radix_candidates(int n, bool pad, int *e) {
-  if (n % 3 == 0 || n % 5 == 0) {
-    e[0] = default_radix(n, pad);
-    return 1;
-  }
   e[0] = pad ? 3 : 2;
+  if (n % 3 == 0 || n % 5 == 0) {
+    e[1] = n % 5 == 0 ? (pad ? 15 : 10) : (pad ? 9 : 6);
+    return 2;
+  }
   e[1] = pad ? 6 : 4;
   e[2] = pad ? 12 : 8;
   return 3;
@@ -1365,68 +1400,10 @@ inline bool axis_len_ok(int n) {
   if (n % f || m <= 0 || (m & (m - 1))) return false;
   return f == 1 ? (n >= 4 && n <= 2048) : (f == 3 ? (n >= 12 && n <= 1536) : (n >= 20 && n <= 1280));
 }
-// Launch the kernel of shape (T, E, pad) (hipErrorInvalidValue if not built).
-template <typename real>
-hipError_t launch_batch_row(int T, int E, bool pad, dim3 grid, hipStream_t s, const RowArgs<real> *args,
-                            const BatchItem *items, int tile0, int first0, const void *sched0, PhysArgs ph);
-// The padded row kernels in the permuted-layout form (ZK_ROW_FFT_LANES),
-// built for every padded row shape with row_lanes_ok: the kernel, or nullptr;
-// the launch, or hipErrorInvalidValue.
-template <typename real>
-const void *lanes_row_kernel(int T, int E);
-template <>
-const void *lanes_row_kernel<double>(int T, int E);
-template <>
-const void *lanes_row_kernel<float>(int T, int E);
-template <typename real>
-hipError_t launch_lanes_row(int T, int E, dim3 grid, hipStream_t s, const RowArgs<real> *args, const BatchItem *items,
-                            int tile0, int first0, const void *sched0, PhysArgs ph);
-template <>
-hipError_t launch_lanes_row<double>(int, int, dim3, hipStream_t, const RowArgs<double> *, const BatchItem *, int, int,
-                                    const void *, PhysArgs);
-template <>
-hipError_t launch_lanes_row<float>(int, int, dim3, hipStream_t, const RowArgs<float> *, const BatchItem *, int, int,
-                                   const void *, PhysArgs);
-template <typename real>
-hipError_t launch_batch_col(int T, int E, bool pad, dim3 grid, hipStream_t s, const ColArgs<real> *args,
-                            const BatchItem *items, int tile0, int first0, const void *sched0, PhysArgs ph);
-template <>
-hipError_t launch_batch_row<double>(int, int, bool, dim3, hipStream_t, const RowArgs<double> *, const BatchItem *, int,
-                                   int, const void *, PhysArgs);
-template <>
-hipError_t launch_batch_row<float>(int, int, bool, dim3, hipStream_t, const RowArgs<float> *, const BatchItem *, int, int,
-                                  const void *, PhysArgs);
-template <>
-hipError_t launch_batch_col<double>(int, int, bool, dim3, hipStream_t, const ColArgs<double> *, const BatchItem *, int,
-                                   int, const void *, PhysArgs);
-template <>
-hipError_t launch_batch_col<float>(int, int, bool, dim3, hipStream_t, const ColArgs<float> *, const BatchItem *, int, int,
-                                  const void *, PhysArgs);
-// The lift_sym variant of the base-length column kernel (E in {2, 4, 8, 6}).
-template <typename real>
-hipError_t launch_batch_col_lift(int T, int E, dim3 grid, hipStream_t s, const ColArgs<real> *args,
-                                 const BatchItem *items, int tile0, int first0, const void *sched0, PhysArgs ph);
-template <>
-hipError_t launch_batch_col_lift<double>(int, int, dim3, hipStream_t, const ColArgs<double> *, const BatchItem *, int, int,
-                                        const void *, PhysArgs);
-template <>
-hipError_t launch_batch_col_lift<float>(int, int, dim3, hipStream_t, const ColArgs<float> *, const BatchItem *, int, int,
-                                       const void *, PhysArgs);
-
-// Fold-team column kernel (T in {64, 128, 256}, E in {2, 3}); grid.x = one
-// block per column.  hipErrorInvalidValue for a shape without an instance.
+// Shapes with a fold-team column kernel (one block per column).
 __host__ __device__ constexpr bool fold_team_shape(int T, int E) {
-  return (T == 64 || T == 128 || T == 256) && (E == 2 || E == 3);
+  return E == 3 && T >= 16 && kMaxFolds * fold_slot(T) <= 1024;
 }
-template <typename real>
-hipError_t launch_batch_col_folds(int T, int E, dim3 grid, hipStream_t s, const ColArgs<real> *args,
-                                  const BatchItem *items, int tile0, int first0, const void *sched0, PhysArgs ph);
-template <>
-hipError_t launch_batch_col_folds<double>(int, int, dim3, hipStream_t, const ColArgs<double> *, const BatchItem *, int, int,
-                                         const void *, PhysArgs);
-template <>
-hipError_t launch_batch_col_folds<float>(int, int, dim3, hipStream_t, const ColArgs<float> *, const BatchItem *, int, int,
-                                        const void *, PhysArgs);
 
 // Reflecting walls (zk_bc.hip): dst [2ny][2nx] = even extension of src
 // [ny][nx]; crop: dst [ny][nx] = the physical quarter of src [2ny][2nx].
