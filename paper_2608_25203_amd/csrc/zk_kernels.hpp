@@ -1369,15 +1369,20 @@ inline int pow2_team_radix(int n, bool pad) {
   return n % 5 == 0 ? (pad ? 15 : 10) : (n % 3 ? (pad ? 3 : 2) : (pad ? 9 : 6));
 }
 // The default first-pass radix of an axis of n base points, in use from
-// zk_bind on.  FP64: the smallest one, n / 2 threads a transform.  Both sides as FP64 row and column launches in us:
+// zk_bind on.  FP64: the smallest one, n / 2 threads a transform, except rows
+// of 1024 points and more.  Both sides as FP64 row and column launches in us:
 // - on axes with a factor 3 or 5 the power-of-two team of one radix-9 or
 //   radix-15 step keeps too few wavefronts busy: 30 and 37 against 17.8 and
 //   14.3 on 384 x 320 (M = 5), 416 and 198 against 354 and 167 on 1536^2 (M =
 //   4), 19 and 17 against 11 and 11 on 48^2 (M = 3); only rows of 640 and 768
 //   come out even or the other way (640^2, M = 4: rows 53 against 63, columns
-//   45 against 31), which the autotuner settles.
-inline int default_radix(bool f64, bool, int n, bool pad) {
+//   45 against 31), which the autotuner settles;
+// - rows of 1024 and 2048 points run E = 6 teams of half the threads, whose
+//   passes are 6, 8, ... instead of 3, 4, ...: 82 to 79 and 471 to 448 (at 512
+//   points E = 6 takes 26 against 21).
+inline int default_radix(bool f64, bool row, int n, bool pad) {
   if (!f64) return pow2_team_radix(n, pad);
+  if (row && pad && n >= 1024 && (n & (n - 1)) == 0) return 6;
   return pad ? 3 : 2;
 }
 // The compiled first-pass radices of that axis's padded or base transform
