@@ -1242,7 +1242,8 @@ __device__ __forceinline__ BatchItem item_of(const BatchItem *items, int tile0, 
   return items ? items[blockIdx.y] : BatchItem{tile0, first0 + (int)blockIdx.y};
 }
 template <typename real, int T, int E, bool PAD = (E % 3 == 0), bool LANES = false>
-__global__ __launch_bounds__(block_threads(T)) void row_kernel_batch(const RowArgs<real> *__restrict__ args,
+__global__ __launch_bounds__(block_threads(T))
+__attribute__((amdgpu_waves_per_eu(row_min_waves(sizeof(real) == 4, T, E, PAD, LANES), 8))) void row_kernel_batch(const RowArgs<real> *__restrict__ args,
                                                         const BatchItem *__restrict__ items, int tile0, int first0,
                                                         const void *sched0, PhysArgs ph) {
   const BatchItem it = item_of(items, tile0, first0);
@@ -1282,6 +1283,14 @@ __global__ __launch_bounds__(kMaxFolds * fold_slot(T)) void col_kernel_folds(con
 // in y and no ky Nyquist row) and a lift writes it back; one thread per
 // column, the same task records as col_body.
 template <typename real, bool LIFTSYM>
+// FP32 rows of 1024 threads (2048 points) are held to 64 VGPRs, so that two of
+// their blocks share a CU and one's barriers leave the other's wavefronts to
+// run: 307 to 243 us a launch on 2048^2 (M = 5) with 41 spilled registers; the
+// shorter rows, whose blocks are several a CU anyway, lose 2 us a launch to the
+// scratch set-up (512 points 15.7 to 18.1, 1024 points 46.6 to 45.3).
+constexpr int row_min_waves(bool f32, int T, int E, bool pad, bool lanes) {
+  return f32 && T == 1024 && E == 3 && pad && !lanes ? 8 : 1;
+}
 __device__ __forceinline__ void col_body_1d(const ColArgs<real> &a, int task_index, int col) {
   const ColTask task = uniform_load(a.tasks + task_index);
   if (col >= a.nx / 2) return;  // no barriers in this body
