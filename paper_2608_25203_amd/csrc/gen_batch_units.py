@@ -38,9 +38,9 @@ def lanes_ok(T, E, pad, real_bytes):
             and 2 * tpb * N * 2 * real_bytes <= 100 * 1024)
 
 
-def fold_team_shape(T, E, pad):
+def fold_team_shape(f64, T, E, pad):
     """as fold_team_shape() in zk_kernels.hpp"""
-    return pad and E == 3 and T >= 16 and 3 * ((T + 63) // 64 * 64) <= 1024
+    return pad and E == 3 and 3 * ((T + 63) // 64 * 64) <= 1024 and (T >= 16 if f64 else T in (64, 128, 256))
 
 
 def compiled(T, E, pad):
@@ -69,7 +69,7 @@ def instances(kind, real):
             out.append((E, T, E, pad, "KF_PLAIN", f"col_kernel_batch<{real}, {T}, {E}, false, {b(pad)}>"))
             if not pad:
                 out.append((E, T, E, pad, "KF_LIFTSYM", f"col_kernel_batch<{real}, {T}, {E}, true, false>"))
-            if fold_team_shape(T, E, pad):
+            if fold_team_shape(real == "double", T, E, pad):
                 out.append((4, T, E, pad, "KF_FOLDS", f"col_kernel_folds<{real}, {T}, {E}>"))
     return out
 

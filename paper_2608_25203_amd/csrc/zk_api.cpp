@@ -97,17 +97,11 @@ void compute_layout(zk_ctx *c) {
   off = align_up(off + 2 * std::max(sizeof(RowArgs<double>), sizeof(RowArgs<float>)));
   c->off_cargs = off;  // [pad, base] column argument records
   off = align_up(off + 2 * std::max(sizeof(ColArgs<double>), sizeof(ColArgs<float>)));
-  c->off_iprog = off;  // items {pad 0 | base 1, program}, pad block then base block
-  off = align_up(off + 2 * c->sched_cap[1] * sizeof(BatchItem));
-  c->off_itask = off;  // items {pad 0 | base 1, task}
-  off = align_up(off + 2 * c->sched_cap[4] * sizeof(BatchItem));
   c->off_ifsym = 0;
   if (c->integrator == ZK_INTEGRATOR_IFAB2) {
     c->off_ifsym = off;
     off = align_up(off + (size_t)(nx / 2) * ny * kIfCoefs * sizeof(double));
   }
-  c->off_layer = off;  // depths of one chunk of layers
-  off = align_up(off + kMaxChunkLayers * sizeof(double));
   c->off_ext = 0;
   if (c->bc == ZK_BC_REFLECT) {
     c->off_ext = off;
@@ -260,7 +254,7 @@ int upload(zk_ctx *c, double dt) {
     }
   }
   {
-    // argument records (field pointers come with each call) and items
+    // argument records (field pointers come with each call)
     std::vector<char> rt(2 * std::max(sizeof(RowArgs<double>), sizeof(RowArgs<float>)));
     std::vector<char> ct(2 * std::max(sizeof(ColArgs<double>), sizeof(ColArgs<float>)));
     const Phys none;
@@ -277,19 +271,8 @@ int upload(zk_ctx *c, double dt) {
         std::memcpy(&ct[p * sizeof(k)], &k, sizeof(k));
       }
     }
-    std::vector<BatchItem> ip(2 * c->sched_cap[1]), it(2 * c->sched_cap[4]);
-    for (size_t k = 0; k < c->sched_cap[1]; ++k) {
-      ip[k] = BatchItem{0, (int32_t)k};
-      ip[c->sched_cap[1] + k] = BatchItem{1, (int32_t)k};
-    }
-    for (size_t k = 0; k < c->sched_cap[4]; ++k) {
-      it[k] = BatchItem{0, (int32_t)k};
-      it[c->sched_cap[4] + k] = BatchItem{1, (int32_t)k};
-    }
     HIP_TRY(c, put(c->off_rargs, rt.data(), rt.size()));
     HIP_TRY(c, put(c->off_cargs, ct.data(), ct.size()));
-    HIP_TRY(c, put(c->off_iprog, ip.data(), ip.size() * sizeof(BatchItem)));
-    HIP_TRY(c, put(c->off_itask, it.data(), it.size() * sizeof(BatchItem)));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
   }
   if (c->integrator == ZK_INTEGRATOR_IFAB2 && !std::isnan(dt) && (c->dirty || !(dt == c->ifsym_dt))) {
@@ -363,21 +346,23 @@ int run_seq_t(zk_ctx *c, const std::vector<Launch> &seq, const Phys &ph) {
       const dim3 grid(sh.blocks, l.count);
       const ColArgs<real> *cargs = reinterpret_cast<const ColArgs<real> *>(ws + c->off_cargs);
       if (!row && c->pp.ny == 1) {  // 1D grid: one element per column, no y transform
-        e = launch_col_1d<real>(l.c2 == 1, dim3((nx / 2 + 255) / 256, l.count), c->stream, cargs, tile0, first0);
+        e = launch_col_1d<real>(l.c2 == 1, dim3((nx / 2 + 255) / 256, l.count), c->stream, cargs, tile0, first0,
+                                ph.layers);
       } else {
         int form = KF_PLAIN, threads = block_threads(sh.T);
         if (row && pad && c->row_fft == ZK_ROW_FFT_LANES && row_lanes_ok(sh.T, sh.E, true, (int)sizeof(real))) {
           form = KF_LANES;
         } else if (!row && l.c2 == 1) {
           form = KF_LIFTSYM;
-        } else if (!row && l.d2 == kMaxFolds && fold_team_shape(sh.T, sh.E)) {  // one block per column
+        } else if (!row && l.d2 == kMaxFolds && fold_team_shape(sizeof(real) == 8, sh.T, sh.E)) {  // one block per column
           form = KF_FOLDS;
           threads = kMaxFolds * fold_slot(sh.T);
         }
         const void *fn = find_kernel(row, sizeof(real) == 8, form, sh.T, sh.E, pad);
         if (!fn) return fail(c, ZK_EINVAL, "team shape not built");
         const void *args = ws + (row ? c->off_rargs : c->off_cargs);
-        void *params[] = {&args, &items, &tile0, &first0, &sched0, &pa};
+        LayerDepths layers = ph.layers;
+        void *params[] = {&args, &items, &tile0, &first0, &sched0, form == KF_LIFTSYM ? (void *)&layers : &pa};
         e = hipLaunchKernel(fn, form == KF_FOLDS ? dim3(nx / 2, l.count) : grid, dim3(threads), params, 0, c->stream);
       }
     } else {
@@ -503,7 +488,6 @@ ColArgs<real> ctx_col_args(const zk_ctx *c, bool pad, int task0) {
   a.filt_x = reinterpret_cast<const double *>(ws + c->off_fx);
   a.filt_y = reinterpret_cast<const double *>(ws + c->off_fy);
   a.ifsym = c->off_ifsym ? reinterpret_cast<const double *>(ws + c->off_ifsym) : nullptr;
-  a.layer_y = reinterpret_cast<const double *>(ws + c->off_layer);
   return a;
 }
 
@@ -733,9 +717,12 @@ int zk_step(zk_ctx *c, double *eta, double *psi, double dt, int nsteps) {
   const bool ab2 = c->integrator == ZK_INTEGRATOR_IFAB2;
   for (int i = 0; i < nsteps; ++i) {
     const int par = i & 1;
-    const std::vector<Launch> &body = ab2 ? (i == 0 ? p.ab2_first[par] : p.ab2_body[par]) : p.step_body[par];
+    // every step but the last also lifts its result for the next one
+    const bool last = i + 1 == nsteps;
+    const std::vector<Launch> &body =
+        ab2 ? (i == 0 ? (last ? p.ab2_first : p.ab2_first_lift) : (last ? p.ab2_body : p.ab2_body_lift))[par]
+            : (last ? p.step_body : p.step_body_lift)[par];
     if ((rc = run_seq(c, body, ph))) return rc;
-    if (i + 1 < nsteps && (rc = run_seq(c, p.step_lift[1 - par], ph))) return rc;
   }
   const int fin = nsteps & 1;
   if ((rc = run_seq(c, p.step_exit[fin], ph))) return rc;
@@ -846,12 +833,9 @@ int zk_depth_velocity(zk_ctx *c, const double *eta, const double *psi, int nlaye
   // layer at a time through the doubled fields ext(0..2), cropped
   const size_t plane = (size_t)c->unx * c->uny;
   const int lc = c->bc ? 1 : c->plan.depth_chunk_max;
-  double *ydev = reinterpret_cast<double *>(c->ws + c->off_layer);
   for (int i0 = 0; i0 < nlayers; i0 += lc) {
     const int r = std::min(lc, nlayers - i0);
-    LayerDepths y{};
-    for (int i = 0; i < r; ++i) y.v[i] = ys[i0 + i];
-    HIP_TRY(c, launch_set_layer_depths(ydev, y, c->stream));
+    for (int i = 0; i < r; ++i) ph.layers.v[i] = ys[i0 + i];
     ph.out0 = c->bc ? ext(c, 0) : uvw + 3 * (size_t)i0 * plane;
     if ((rc = run_seq(c, c->plan.depth_chunk[r], ph))) return rc;
     if (c->bc)
@@ -874,7 +858,7 @@ int zk_autotune(zk_ctx *c, double dt, int reps) {
   for (int row = 1; row >= 0; --row)
     for (int pad = 1; pad >= 0; --pad) {
       std::vector<Launch> sub;
-      for (const Launch &l : c->plan.step_body[0]) {
+      for (const Launch &l : c->plan.step_body_lift[0]) {
         const bool lr = l.kind == L_ROW_PAD || l.kind == L_ROW_BASE;
         const bool lp = l.kind == L_ROW_PAD || l.kind == L_COL_PAD;
         if (l.kind != L_PARSEVAL && lr == (bool)row && lp == (bool)pad) sub.push_back(l);

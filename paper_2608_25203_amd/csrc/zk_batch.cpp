@@ -359,14 +359,9 @@ int prepare(zk_batch *b, double dt) {
     b->seg[s].clear();
     merge(b, seqs, b->seg[s]);
   };
-  auto cat = [](const std::vector<Launch> &x, const std::vector<Launch> &y) {
-    std::vector<Launch> r(x);
-    r.insert(r.end(), y.begin(), y.end());
-    return r;
-  };
   build(0, [](const Plan &p) { return p.step_entry; });
-  build(1, [&](const Plan &p) { return cat(p.step_body[0], p.step_lift[1]); });
-  build(2, [&](const Plan &p) { return cat(p.step_body[1], p.step_lift[0]); });
+  build(1, [](const Plan &p) { return p.step_body_lift[0]; });
+  build(2, [](const Plan &p) { return p.step_body_lift[1]; });
   build(3, [](const Plan &p) { return p.step_body[0]; });
   build(4, [](const Plan &p) { return p.step_body[1]; });
   build(5, [](const Plan &p) { return p.step_exit[0]; });
@@ -469,11 +464,9 @@ zk_batch *zk_batch_create(int ntiles, const zk_tile *tiles, double g, int precis
     auto count = [&](const std::vector<Launch> &s) {
       for (const Launch &l : s) items += (size_t)std::max(0, l.count);
     };
-    for (auto *s : {&probe.step_entry, &probe.step_body[0], &probe.step_body[1], &probe.step_lift[0],
-                    &probe.step_lift[1], &probe.step_exit[0], &probe.step_exit[1]})
+    for (auto *s : {&probe.step_entry, &probe.step_body[0], &probe.step_body[1], &probe.step_body_lift[0],
+                    &probe.step_body_lift[1], &probe.step_exit[0], &probe.step_exit[1]})
       count(*s);
-    count(probe.step_body[0]);  // body segments appear twice (with and without the lift)
-    count(probe.step_body[1]);
   }
   const size_t rsz = precision == 32 ? sizeof(RowArgs<float>) : sizeof(RowArgs<double>);
   const size_t csz = precision == 32 ? sizeof(ColArgs<float>) : sizeof(ColArgs<double>);

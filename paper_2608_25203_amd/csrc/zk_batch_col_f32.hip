@@ -26,8 +26,7 @@ const KernelEntry col_f32_0[] = {
     {8, 10, false, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 8, 10, false, false>)},
     {8, 15, true, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 8, 15, false, true>)},
     {16, 2, false, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 16, 2, false, false>)},
-    {16, 3, true, KF_FOLDS, reinterpret_cast<const void *>(&col_kernel_folds<float, 16, 3>)},
-    {16, 4, false, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 16, 4, false, false>)},
+    {16, 4, false, KF_LIFTSYM, reinterpret_cast<const void *>(&col_kernel_batch<float, 16, 4, true, false>)},
     {16, 6, false, KF_LIFTSYM, reinterpret_cast<const void *>(&col_kernel_batch<float, 16, 6, true, false>)},
     {16, 6, true, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 16, 6, false, true>)},
     {16, 10, false, KF_PLAIN, reinterpret_cast<const void *>(&col_kernel_batch<float, 16, 10, false, false>)},

@@ -29,17 +29,7 @@ __global__ __launch_bounds__(256) void crop_kernel(const double *__restrict__ sr
   dst[i] = src[(long long)y * (2 * nx) + x];
 }
 
-__global__ void set_layer_depths_kernel(double *__restrict__ dst, LayerDepths y) {
-  const int i = threadIdx.x;
-  if (i < kMaxChunkLayers) dst[i] = y.v[i];
-}
-
 }  // namespace
-
-hipError_t launch_set_layer_depths(double *dst, LayerDepths y, hipStream_t s) {
-  hipLaunchKernelGGL(set_layer_depths_kernel, dim3(1), dim3(64), 0, s, dst, y);
-  return hipGetLastError();
-}
 
 hipError_t launch_mirror(const double *src, int nx, int ny, double *dst, hipStream_t s) {
   const long long total = 4LL * nx * ny;

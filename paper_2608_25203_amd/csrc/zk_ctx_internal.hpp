@@ -31,14 +31,13 @@ struct zk_ctx {
   // workspace layout (byte offsets)
   size_t off_tw[4] = {0, 0, 0, 0};  // row pad, row base, col pad, col base
   size_t off_ops = 0, off_progs = 0, off_terms = 0, off_outs = 0, off_tasks = 0;
-  size_t off_rargs = 0, off_cargs = 0, off_iprog = 0, off_itask = 0;
+  size_t off_rargs = 0, off_cargs = 0;
   int integrator = 0;     // ZK_INTEGRATOR_RK4 or ZK_INTEGRATOR_IFAB2
   int bc = 0;             // ZK_BC_PERIODIC or ZK_BC_REFLECT
   int unx = 0, uny = 0;   // caller's grid (the internal grid is doubled for walls)
   double uLx = 0, uLy = 0;
   size_t off_ext = 0;     // four doubled fields (walls only)
   size_t off_ifsym = 0;   // IF-AB2 coefficient table (0 when unused)
-  size_t off_layer = 0;   // (C, S) of one depth layer per band element
   double ifsym_dt = NAN;  // dt the table holds
   int tuneT[2][2] = {{0, 0}, {0, 0}};  // [row][pad] autotuned threads per transform (0: default)
   int row_fft = 0;
@@ -75,6 +74,7 @@ namespace zk {
 struct Phys {
   const double *in0 = nullptr, *in1 = nullptr, *in2 = nullptr;
   double *out0 = nullptr, *out1 = nullptr;
+  LayerDepths layers{};  // of a depth lift's chunk
 };
 
 // Default team shape of a pass: T threads per transform, first-pass radix E,

@@ -70,7 +70,11 @@ struct ColArgs {
   const double *sym_g0, *sym_tp;
   const double *filt_x, *filt_y;  // separable state filter factors
   const double *ifsym;            // kIfCoefs per band element (base layout), or null
-  const double *layer_y;          // depths of the current chunk of layers (kMaxChunkLayers)
+};
+
+// Depths of one chunk of layers of the bulk velocity lift.
+struct LayerDepths {
+  double v[kMaxChunkLayers];
 };
 
 // ---- register-set dispatch (keeps every register array statically indexed)
@@ -840,38 +844,33 @@ __device__ __forceinline__ void row_body(const RowArgs<real> &a, int prog, int b
 }
 
 // ---------------------------------------------------------------------------
-// Factors of the bulk velocity lift, applied at the lift stage of a column
-// task (one site, after the terms are summed, so the exponentials do not
-// raise the register peak of the pass).  COUPLE: prod_a exp(-(|k_a| / (kNyq_a / 2))^8).  LAYER_C / _S:
-// C = cosh(k (d - y)) / cosh(k d), S = k sinh(k (d - y)) / cosh(k d) at the
-// chunk's layer depth y, as exp(-k y) (1 +- exp(-2 k (d - y))) / (1 + exp(-2 k d));
-// deep water: exp(-k y) and k exp(-k y); C = 1, S = 0 at k = 0.
-__device__ __forceinline__ double lift_factor(uint32_t s, double kk, int col, int b, int nx, int ny, double depth,
-                                           const double *layer_y) {
-  double f = 1.0;
-  if (s & SYM_COUPLE) {
-    const int my = (b < ny / 2 || ny == 1) ? b : b - ny;  // a 1D grid's one row is ky = 0
-    const double rx = 4.0 * col / nx, ry = 4.0 * (my < 0 ? -my : my) / ny;  // |k_a| / (kNyq_a / 2)
-    const double rx2 = rx * rx, ry2 = ry * ry, rx4 = rx2 * rx2, ry4 = ry2 * ry2;
-    f *= exp(-(rx4 * rx4) - (ry4 * ry4));
-  }
-  if (s & (SYM_LAYER_C | SYM_LAYER_S)) {
-    const double y = layer_y[(s >> SYM_LAYER_SHIFT) & 15];
-    double c = 1.0, sn = 0.0;
-    if (kk > 0.0) {
-      const double e1 = exp(-kk * y);
-      if (depth > 0.0) {
-        const double e2 = exp(-2.0 * kk * (depth - y)), den = 1.0 + exp(-2.0 * kk * depth);
-        c = e1 * (1.0 + e2) / den;
-        sn = kk * e1 * (1.0 - e2) / den;
-      } else {
-        c = e1;
-        sn = kk * e1;
-      }
+// Factors of the bulk velocity lift at one band element, applied at the lift
+// stage of a column task: C = cosh(k (d - y)) / cosh(k d) and S = k sinh(k (d -
+// y)) / cosh(k d) at layer depth y, as exp(-k y) (1 +- exp(-2 k (d - y))) / (1 +
+// exp(-2 k d)); deep water: exp(-k y) and k exp(-k y); C = 1, S = 0 at k = 0;
+// both times the coupling taper prod_a exp(-(|k_a| / (kNyq_a / 2))^8).
+struct LayerFactors {
+  double c, s;
+};
+__device__ __forceinline__ LayerFactors layer_factors(double kk, int col, int b, int nx, int ny, double depth,
+                                                      double y) {
+  const int my = (b < ny / 2 || ny == 1) ? b : b - ny;  // a 1D grid's one row is ky = 0
+  const double rx = 4.0 * col / nx, ry = 4.0 * (my < 0 ? -my : my) / ny;  // |k_a| / (kNyq_a / 2)
+  const double rx2 = rx * rx, ry2 = ry * ry, rx4 = rx2 * rx2, ry4 = ry2 * ry2;
+  const double couple = exp(-(rx4 * rx4) - (ry4 * ry4));
+  double c = 1.0, sn = 0.0;
+  if (kk > 0.0) {
+    const double e1 = exp(-kk * y);
+    if (depth > 0.0) {
+      const double e2 = exp(-2.0 * kk * (depth - y)), den = 1.0 + exp(-2.0 * kk * depth);
+      c = e1 * (1.0 + e2) / den;
+      sn = kk * e1 * (1.0 - e2) / den;
+    } else {
+      c = e1;
+      sn = kk * e1;
     }
-    f *= (s & SYM_LAYER_S) ? sn : c;
   }
-  return f;
+  return {couple * c, couple * sn};
 }
 
 // ---------------------------------------------------------------------------
@@ -879,8 +878,13 @@ __device__ __forceinline__ double lift_factor(uint32_t s, double kk, int col, in
 // the host in FP64: |k|, G0 = |k| tanh(|k| d) and the taper, per band element
 // (same tiled layout as a base spectrum); the state filter is separable,
 // A = Ax(kx) Ay(b).
+// fl: the filter's value (read where s has SYM_FILT), fi: the loaded SYM_IF
+// coefficient.
+__device__ __forceinline__ double if_coef(const double *ifsym, uint32_t s, int col, int b, int ny) {
+  return gload1(ifsym, (long long)base_index(col, b, ny) * kIfCoefs + ((s >> SYM_IF_SHIFT) & 7));
+}
 template <typename real>
-__device__ __forceinline__ cpx<double> symval(uint32_t s, double kk, double g0, double tp, int col, int b,
+__device__ __forceinline__ cpx<double> symval(uint32_t s, double kk, double g0, double tp, double fl, double fi,
                                               double ky, const ColArgs<real> &a) {
   double f = 1.0;
   const int l = s & SYM_LMASK;
@@ -888,9 +892,9 @@ __device__ __forceinline__ cpx<double> symval(uint32_t s, double kk, double g0, 
     f = (l & 1) ? g0 : kk;
     for (int i = 1; i < l; ++i) f *= kk;
   }
-  if (s & SYM_FILT) f *= gload1(a.filt_x, col) * gload1(a.filt_y, b);
+  if (s & SYM_FILT) f *= fl;
   if ((s & SYM_TAPER) && a.taper_on) f *= tp;
-  if (s & SYM_IF) f *= gload1(a.ifsym, (long long)base_index(col, b, a.ny) * kIfCoefs + ((s >> SYM_IF_SHIFT) & 7));
+  if (s & SYM_IF) f *= fi;
   if (s & SYM_INVG0) f = g0 > 0.0 ? f / g0 : 0.0;
   if (s & SYM_IKY) return {0.0, f * ky};
   return {f, 0.0};
@@ -912,7 +916,8 @@ struct ColBlock {
 };
 template <typename real, int T, int E, bool LIFTSYM = false, int FT = 1, bool DYN = false, int BSZ = 0,
           bool PAD = (E % 3 == 0)>
-__device__ __forceinline__ void col_body(const ColArgs<real> &a, int task_index, int blk, const ColTask *tasks0) {
+__device__ __forceinline__ void col_body(const ColArgs<real> &a, int task_index, int blk, const ColTask *tasks0,
+                                         const LayerDepths *layers = nullptr) {
   static_assert(BSZ == 0 || FT == 1, "a block size is set for plain column teams only");
   using S = Shape<T, E, BSZ, PAD>;
   using CB = ColBlock<T, FT, BSZ>;
@@ -1000,8 +1005,8 @@ __device__ __forceinline__ void col_body(const ColArgs<real> &a, int task_index,
     sg0[q] = a.depth > 0.0 ? gload1(a.sym_g0, e) : skk[q];
     stp[q] = need_tp ? gload1(a.sym_tp, e) : 1.0;
   }
-  auto sym = [&](uint32_t s, int q) -> cpx<double> {
-    return symval(s, skk[q], sg0[q], stp[q], col, t + T * q, a.ky_scale * my_of(q), a);
+  auto sym = [&](uint32_t s, int q, double fl, double fi) -> cpx<double> {
+    return symval(s, skk[q], sg0[q], stp[q], fl, fi, a.ky_scale * my_of(q), a);
   };
 
   cpx<double> X[QB];
@@ -1032,7 +1037,7 @@ __device__ __forceinline__ void col_body(const ColArgs<real> &a, int task_index,
 #pragma unroll
     for (int q = 0; q < QB; ++q) {
       const cpx<real> w = get(base_slot(q));
-      const cpx<double> sv = sym(fsym, q);
+      const cpx<double> sv = sym(fsym, q, 1.0, 1.0);  // folds carry neither factor
       const cpx<double> x = {(double)w.x * fcoef, (double)w.y * fcoef};
       X[q].x += x.x * sv.x - x.y * sv.y;
       X[q].y += x.x * sv.y + x.y * sv.x;
@@ -1110,51 +1115,79 @@ __device__ __forceinline__ void col_body(const ColArgs<real> &a, int task_index,
   // teams: team f sums terms f, f + FT, ... (a third of the chain of
   // base-spectrum loads each), the parts are summed through LDS in team
   // order, and every team then holds the combination; team 0 stores it.
+  // An output marked keep leaves its stored combination in X (base spectrum
+  // `kept`), for the task's later lifts of it.
+  int kept = -1;
+  // Depth lift: the factors of the task's layer, formed once for its three
+  // outputs (512^2, 8 layers: 42 us a launch when each output formed
+  // its own exponentials, 36 now).
+  double lfc[QB], lfs[QB];
+  int layer = -1;
   for (int o = 0; o < task.no; ++o) {
     const ColOut out = uniform_load(a.outs + task.o0 + o);
+    if constexpr (LIFTSYM) {
+      const int i = (int)((out.lift_sym >> SYM_LAYER_SHIFT) & 15);
+      if ((out.lift_sym & (SYM_LAYER_C | SYM_LAYER_S)) && i != layer) {
+        layer = i;
+#pragma unroll
+        for (int q = 0; q < QB; ++q) {
+          const LayerFactors lf = layer_factors(skk[q], col, t + T * q, a.nx, a.ny, a.depth, layers->v[i]);
+          lfc[q] = lf.c;
+          lfs[q] = lf.s;
+        }
+      }
+    }
     constexpr int step = FT;
     const int first = FT == 1 ? 0 : team;
     cpx<double> acc[QB];
 #pragma unroll
     for (int q = 0; q < QB; ++q) acc[q] = {0.0, 0.0};
-    // Base-spectrum terms: the next term's spectrum is loaded while the
-    // current one is accumulated (one global latency per term instead of two).
+    // Base-spectrum terms: the next term's spectrum (and in FP64, where the
+    // registers do not cost a wavefront, its IF coefficient) is loaded while the
+    // current one is accumulated, one global latency per term instead of two.
+    constexpr bool IFN = sizeof(real) == 8 && !LIFTSYM;
     cpx<double> nxt[QB];
+    double nfi[QB];
     ColTerm ntm = first < out.nt ? uniform_load(a.terms + out.t0 + first) : ColTerm{};
     auto fetch = [&](const ColTerm &tm2) {
-      if (tm2.src >= 0) {
+      if (tm2.src >= 0 && (LIFTSYM || tm2.src != kept)) {
         const cpx<double> *B = a.base + (long long)tm2.src * a.base_stride;
 #pragma unroll
         for (int q = 0; q < QB; ++q) nxt[q] = gload(B, base_index(col, t + T * q, ny));
+      }
+      if (IFN && (tm2.sym & SYM_IF)) {
+#pragma unroll
+        for (int q = 0; q < QB; ++q) nfi[q] = if_coef(a.ifsym, tm2.sym, col, t + T * q, ny);
       }
     };
     fetch(ntm);
     for (int i = first; i < out.nt; i += step) {
       const ColTerm tm = ntm;
       cpx<double> cur[QB];
+      double fi[QB];
 #pragma unroll
-      for (int q = 0; q < QB; ++q) cur[q] = nxt[q];
+      for (int q = 0; q < QB; ++q) {
+        cur[q] = nxt[q];
+        if constexpr (IFN) fi[q] = nfi[q];
+      }
       if (i + step < out.nt) {
         ntm = uniform_load(a.terms + out.t0 + i + step);
         fetch(ntm);
       }
-      if (tm.src >= 0) {
+      if (tm.src < 0 || (!LIFTSYM && tm.src == kept)) {
 #pragma unroll
-        for (int q = 0; q < QB; ++q) {
-          const cpx<double> s0 = cur[q];
-          cpx<double> sv = sym(tm.sym, q);
-          sv = {sv.x * tm.coef, sv.y * tm.coef};
-          acc[q].x += s0.x * sv.x - s0.y * sv.y;
-          acc[q].y += s0.x * sv.y + s0.y * sv.x;
-        }
-      } else {
+        for (int q = 0; q < QB; ++q) cur[q] = X[q];
+      }
 #pragma unroll
-        for (int q = 0; q < QB; ++q) {
-          cpx<double> sv = sym(tm.sym, q);
-          sv = {sv.x * tm.coef, sv.y * tm.coef};
-          acc[q].x += X[q].x * sv.x - X[q].y * sv.y;
-          acc[q].y += X[q].x * sv.y + X[q].y * sv.x;
-        }
+      for (int q = 0; q < QB; ++q) {
+        double fl = 1.0, f = 1.0;
+        if (!LIFTSYM && (tm.sym & SYM_FILT)) fl = gload1(a.filt_x, col) * gload1(a.filt_y, t + T * q);
+        if constexpr (IFN) f = fi[q];
+        else if (tm.sym & SYM_IF) f = if_coef(a.ifsym, tm.sym, col, t + T * q, ny);
+        cpx<double> sv = sym(tm.sym, q, fl, f);
+        sv = {sv.x * tm.coef, sv.y * tm.coef};
+        acc[q].x += cur[q].x * sv.x - cur[q].y * sv.y;
+        acc[q].y += cur[q].x * sv.y + cur[q].y * sv.x;
       }
     }
     if constexpr (FT > 1) {
@@ -1180,6 +1213,11 @@ __device__ __forceinline__ void col_body(const ColArgs<real> &a, int task_index,
 #pragma unroll
       for (int q = 0; q < QB; ++q) gstore(B, base_index(col, t + T * q, ny), acc[q]);
     }
+    if (!LIFTSYM && out.keep) {
+      kept = out.dst_base;
+#pragma unroll
+      for (int q = 0; q < QB; ++q) X[q] = acc[q];
+    }
     if (out.dst_mixed >= 0) {
       const double lc = out.lift_coef;
       cpx<real> z[E];
@@ -1190,7 +1228,10 @@ __device__ __forceinline__ void col_body(const ColArgs<real> &a, int task_index,
         const int r = q < S::KR ? q : q + (S::PADDED ? E / 3 : 0);
         double f = lc;
         if constexpr (LIFTSYM)
-          if (out.lift_sym) f *= lift_factor(out.lift_sym, skk[q], col, t + T * q, a.nx, ny, a.depth, a.layer_y);
+          if (out.lift_sym) {
+            const double fc = lfc[q], fs = lfs[q];
+            f *= (out.lift_sym & SYM_LAYER_S) ? fs : fc;
+          }
         z[r] = {(real)(acc[q].x * f), (real)(acc[q].y * f)};
       }
       float m = 0.f;
@@ -1241,6 +1282,14 @@ struct PhysArgs {
 __device__ __forceinline__ BatchItem item_of(const BatchItem *items, int tile0, int first0) {
   return items ? items[blockIdx.y] : BatchItem{tile0, first0 + (int)blockIdx.y};
 }
+// FP32 rows of 1024 threads (2048 points) are held to 64 VGPRs, so that two of
+// their blocks share a CU and one's barriers leave the other's wavefronts to
+// run: 307 to 243 us a launch on 2048^2 (M = 5) with 41 spilled registers; the
+// shorter rows, whose blocks are several a CU anyway, lose 2 us a launch to the
+// scratch set-up (512 points 15.7 to 18.1, 1024 points 46.6 to 45.3).
+constexpr int row_min_waves(bool f32, int T, int E, bool pad, bool lanes) {
+  return f32 && T == 1024 && E == 3 && pad && !lanes ? 8 : 1;
+}
 template <typename real, int T, int E, bool PAD = (E % 3 == 0), bool LANES = false>
 __global__ __launch_bounds__(block_threads(T))
 __attribute__((amdgpu_waves_per_eu(row_min_waves(sizeof(real) == 4, T, E, PAD, LANES), 8))) void row_kernel_batch(const RowArgs<real> *__restrict__ args,
@@ -1258,14 +1307,18 @@ __attribute__((amdgpu_waves_per_eu(row_min_waves(sizeof(real) == 4, T, E, PAD, L
   row_body<real, T, E, false, 0, PAD, LANES>(a, it.index, blockIdx.x, static_cast<const RowProg *>(sched0));
 }
 // LIFTSYM: the variant that applies ColOut.lift_sym (the bulk velocity
-// lift's column launches); the plain passes never carry its exponentials.
+// lift's column launches, which get their layers' depths as an argument); the
+// plain passes never carry its exponentials.
 template <typename real, int T, int E, bool LIFTSYM = false, bool PAD = (E % 3 == 0)>
-__global__ __launch_bounds__(block_threads(T)) void col_kernel_batch(const ColArgs<real> *__restrict__ args,
-                                                        const BatchItem *__restrict__ items, int tile0, int first0,
-                                                        const void *sched0, PhysArgs) {
+__global__ __launch_bounds__(block_threads(T)) void col_kernel_batch(
+    const ColArgs<real> *__restrict__ args, const BatchItem *__restrict__ items, int tile0, int first0,
+    const void *sched0, std::conditional_t<LIFTSYM, LayerDepths, PhysArgs> layers) {
   const BatchItem it = item_of(items, tile0, first0);
   const ColArgs<real> a = args[it.tile];
-  col_body<real, T, E, LIFTSYM, 1, false, 0, PAD>(a, it.index, blockIdx.x, static_cast<const ColTask *>(sched0));
+  if constexpr (LIFTSYM)
+    col_body<real, T, E, true, 1, false, 0, PAD>(a, it.index, blockIdx.x, static_cast<const ColTask *>(sched0), &layers);
+  else
+    col_body<real, T, E, false, 1, false, 0, PAD>(a, it.index, blockIdx.x, static_cast<const ColTask *>(sched0));
 }
 // Fold teams: kMaxFolds teams of T threads per block, one column per block
 // (tasks whose folds and terms run side by side).
@@ -1283,22 +1336,17 @@ __global__ __launch_bounds__(kMaxFolds * fold_slot(T)) void col_kernel_folds(con
 // in y and no ky Nyquist row) and a lift writes it back; one thread per
 // column, the same task records as col_body.
 template <typename real, bool LIFTSYM>
-// FP32 rows of 1024 threads (2048 points) are held to 64 VGPRs, so that two of
-// their blocks share a CU and one's barriers leave the other's wavefronts to
-// run: 307 to 243 us a launch on 2048^2 (M = 5) with 41 spilled registers; the
-// shorter rows, whose blocks are several a CU anyway, lose 2 us a launch to the
-// scratch set-up (512 points 15.7 to 18.1, 1024 points 46.6 to 45.3).
-constexpr int row_min_waves(bool f32, int T, int E, bool pad, bool lanes) {
-  return f32 && T == 1024 && E == 3 && pad && !lanes ? 8 : 1;
-}
-__device__ __forceinline__ void col_body_1d(const ColArgs<real> &a, int task_index, int col) {
+__device__ __forceinline__ void col_body_1d(const ColArgs<real> &a, int task_index, int col, const LayerDepths &layers) {
   const ColTask task = uniform_load(a.tasks + task_index);
   if (col >= a.nx / 2) return;  // no barriers in this body
   const long long e = base_index(col, 0, 1);
   const double kk = a.kx_scale * col;  // ky = 0
   const bool need_tp = a.taper_on && ((task.fwd_sym[0] | task.fwd_sym[1] | task.fwd_sym[2]) & SYM_TAPER);
   const double g0 = a.depth > 0.0 ? gload1(a.sym_g0, e) : kk, tp = need_tp ? gload1(a.sym_tp, e) : 1.0;
-  auto sym = [&](uint32_t s) { return symval(s, kk, g0, tp, col, 0, 0.0, a); };
+  auto sym = [&](uint32_t s) {
+    const double fl = (s & SYM_FILT) ? gload1(a.filt_x, col) * gload1(a.filt_y, 0) : 1.0;
+    return symval(s, kk, g0, tp, fl, (s & SYM_IF) ? if_coef(a.ifsym, s, col, 0, 1) : 1.0, 0.0, a);
+  };
   auto cmac = [](cpx<double> &acc, cpx<double> x, cpx<double> sv) {
     acc.x += x.x * sv.x - x.y * sv.y;
     acc.y += x.x * sv.y + x.y * sv.x;
@@ -1323,7 +1371,11 @@ __device__ __forceinline__ void col_body_1d(const ColArgs<real> &a, int task_ind
     if (out.dst_mixed >= 0) {
       double f = out.lift_coef;
       if constexpr (LIFTSYM)
-        if (out.lift_sym) f *= lift_factor(out.lift_sym, kk, col, 0, a.nx, 1, a.depth, a.layer_y);
+        if (out.lift_sym) {
+          const LayerFactors lf =
+              layer_factors(kk, col, 0, a.nx, 1, a.depth, layers.v[(out.lift_sym >> SYM_LAYER_SHIFT) & 15]);
+          f *= (out.lift_sym & SYM_LAYER_S) ? lf.s : lf.c;
+        }
       const cpx<real> w = {(real)(acc.x * f), (real)(acc.y * f)};
       gstore(a.mix + (long long)out.dst_mixed * a.mix_stride, mix_index<real>(col, 0, a.rows), w);
       gstore1(a.colmax, (long long)out.dst_mixed * (a.nx / 2) + col, fmaxf(fabsf((float)w.x), fabsf((float)w.y)));
@@ -1331,17 +1383,19 @@ __device__ __forceinline__ void col_body_1d(const ColArgs<real> &a, int task_ind
   }
 }
 template <typename real, bool LIFTSYM>
-__global__ __launch_bounds__(256) void col_kernel_1d(const ColArgs<real> *__restrict__ args, int rec, int first0) {
-  col_body_1d<real, LIFTSYM>(args[rec], first0 + (int)blockIdx.y, (int)(blockIdx.x * blockDim.x + threadIdx.x));
+__global__ __launch_bounds__(256) void col_kernel_1d(const ColArgs<real> *__restrict__ args, int rec, int first0,
+                                                  LayerDepths layers) {
+  col_body_1d<real, LIFTSYM>(args[rec], first0 + (int)blockIdx.y, (int)(blockIdx.x * blockDim.x + threadIdx.x), layers);
 }
 // Column pass of a 1D grid: grid.x covers the nx/2 columns with 256 threads
 // per block, grid.y the launch's tasks; args[rec] is the pass's record.
 template <typename real>
-hipError_t launch_col_1d(bool liftsym, dim3 grid, hipStream_t s, const ColArgs<real> *args, int rec, int first0) {
+hipError_t launch_col_1d(bool liftsym, dim3 grid, hipStream_t s, const ColArgs<real> *args, int rec, int first0,
+                         const LayerDepths &layers) {
   if (liftsym)
-    hipLaunchKernelGGL((col_kernel_1d<real, true>), grid, dim3(256), 0, s, args, rec, first0);
+    hipLaunchKernelGGL((col_kernel_1d<real, true>), grid, dim3(256), 0, s, args, rec, first0, layers);
   else
-    hipLaunchKernelGGL((col_kernel_1d<real, false>), grid, dim3(256), 0, s, args, rec, first0);
+    hipLaunchKernelGGL((col_kernel_1d<real, false>), grid, dim3(256), 0, s, args, rec, first0, layers);
   return hipGetLastError();
 }
 
@@ -1414,21 +1468,17 @@ inline bool axis_len_ok(int n) {
   if (n % f || m <= 0 || (m & (m - 1))) return false;
   return f == 1 ? (n >= 4 && n <= 2048) : (f == 3 ? (n >= 12 && n <= 1536) : (n >= 20 && n <= 1280));
 }
-// Shapes with a fold-team column kernel (one block per column).
-__host__ __device__ constexpr bool fold_team_shape(int T, int E) {
-  return E == 3 && T >= 16 && kMaxFolds * fold_slot(T) <= 1024;
+// Shapes with a fold-team column kernel (one block per column).  FP32 keeps to
+// the teams it has had: fold teams sum in another order, whose last bits grow
+// to FP32 rounding.
+__host__ __device__ constexpr bool fold_team_shape(bool f64, int T, int E) {
+  return E == 3 && kMaxFolds * fold_slot(T) <= 1024 && (f64 ? T >= 16 : T == 64 || T == 128 || T == 256);
 }
 
 // Reflecting walls (zk_bc.hip): dst [2ny][2nx] = even extension of src
 // [ny][nx]; crop: dst [ny][nx] = the physical quarter of src [2ny][2nx].
 hipError_t launch_mirror(const double *src, int nx, int ny, double *dst, hipStream_t s);
 hipError_t launch_crop(const double *src, int nx, int ny, double *dst, hipStream_t s);
-// Depths of one chunk of layers (zk_bc.hip): dst[i] = y.v[i] for i < kMaxChunkLayers.
-struct LayerDepths {
-  double v[kMaxChunkLayers];
-};
-hipError_t launch_set_layer_depths(double *dst, LayerDepths y, hipStream_t s);
-
 // FP64 reductions over base spectra (zk_reduce.hip).  Writes
 //   out[0] = sum_k w(kx) Re(conj(a) b),  out[1] = sum_k w(kx) Re(conj(c) d)
 // over the stored half spectrum (w = 1 at kx = 0, 2 elsewhere: the full

@@ -11,6 +11,7 @@ namespace zk {
 namespace {
 
 constexpr int kMaxM = 8;
+constexpr int kSplitPoints = 1 << 18;  // grid points up to which a state's lifts are split (see below)
 
 struct Fac {  // a factor of a product: mixed field id and x-derivative flag
   int f;
@@ -36,6 +37,7 @@ struct OutSpec {
   std::vector<TermSpec> terms;
   double lift_coef = 1.0;
   uint32_t lift_sym = 0;
+  uint32_t keep = 0;
 };
 
 struct FoldSpec {
@@ -253,6 +255,7 @@ class Builder {
         co.nt = (int32_t)o.terms.size();
         co.lift_coef = o.lift_coef;
         co.lift_sym = o.lift_sym;
+        co.keep = o.keep;
         for (auto &tm : o.terms) P.terms.push_back({tm.src, tm.sym, tm.coef});
         P.outs.push_back(co);
       }
@@ -444,6 +447,90 @@ Plan build_plan(const PlanParams &pp, double dt) {
   };
 
   // ---- column task builders -----------------------------------------------------
+  // Lifts of one state from one launch, two ways.  Split: one task a lift or
+  // two, so that a small grid's columns keep more blocks busy; a task that needs
+  // the folded N or the state's combination forms it again.  Merged: one task
+  // forms and stores the combination once and lifts it from registers, which on
+  // a large grid, whose columns alone fill the chip, saves the other tasks'
+  // folds and reads.  RK4 steps split and merged: 552 and 570 us at 512^2 (M =
+  // 4, FP64), 371 and 401 at 256^2; 1459 and 1414 at 640^2, 2082 and 2011 at
+  // 1024^2 (FP32 1431 and 1360), 14.62 and 14.04 ms at 2048^2 (M = 5; FP32
+  // 10.83 and 10.43).
+  const bool merged = pp.nx * pp.ny > kSplitPoints;
+  // FP32 plans lift a stage's state from its terms, each with the lift's symbol,
+  // as a launch of its own would sum them: a last bit of an FP64 sum that tips
+  // the rounding to FP32 grows to the rounding level of the FP32 transforms, and
+  // results stay the same bits whichever way a grid's lifts run.
+  const bool fp32 = pp.real_bytes == 4;
+  // lifts of eta, and of psi (those numbered i0 <= i < i1: 0 psi, 1 its y
+  // derivative, 1 + l L_l psi) from a base spectrum
+  auto eta_lifts = [&](int e) -> std::vector<OutSpec> {
+    return {B.lift(mE, {{e, 0, kref}}), B.lift(mEy, {{e, SYM_IKY, 1.0}})};
+  };
+  auto psi_lifts = [&](int p, int i0, int i1) {
+    std::vector<OutSpec> v;
+    for (int i = i0; i < i1; ++i) {
+      if (i == 0) v.push_back(B.lift(mP, {{p, 0, 1.0}}));
+      else if (i == 1) v.push_back(B.lift(mPy, {{p, SYM_IKY, 1.0}}));
+      else v.push_back(B.lift(mL[i - 1], {{p, (uint32_t)(i - 1), 1.0 / kpow(i - 1)}}));
+    }
+    return v;
+  };
+  // Tasks that store a new psi (combination pt, into np) and lift it (M >= 2)
+  // from the stored, kept spectrum (from_terms: from pt's terms).  tp: the first
+  // task so far, which may fold N.  Split: the L_l lifts by twos in tasks of
+  // their own, which form pt again in a scratch spectrum (scr[k]) each and lift
+  // that.
+  auto lift_of = [&](OutSpec o, const std::vector<TermSpec> &comb) {  // o's one term applied to a combination
+    const TermSpec f = o.terms[0];
+    o.terms = comb;
+    for (auto &x : o.terms) {
+      x.sym |= f.sym;
+      x.coef *= f.coef;
+    }
+    return o;
+  };
+  auto psi_tasks = [&](TaskSpec tp, const std::vector<TermSpec> &pt, int np, const std::vector<int> &scr,
+                       bool from_terms) {
+    TaskSpec fold = tp;
+    fold.outs.clear();
+    std::vector<TaskSpec> ts;
+    auto add = [&](TaskSpec t, int b, int i0, int i1) {  // lifts i0 .. i1 - 1 of b, which holds pt
+      if (!from_terms || b == np) t.outs.push_back(B.store(b, pt));
+      if (!from_terms) t.outs.back().keep = 1;
+      if (!from_terms && i0 == 0) {  // psi itself: the stored combination's own lift
+        t.outs.back().dst_mixed = mP;
+        t.outs.back().lift_coef = B.inv_n;
+        i0 = 1;
+      }
+      for (auto &o : psi_lifts(b, i0, i1)) {
+        if (from_terms) o = lift_of(o, pt);
+        t.outs.push_back(std::move(o));
+      }
+      ts.push_back(std::move(t));
+    };
+    add(tp, np, 0, merged ? M + 2 : 2);
+    for (int i = 2, k = 0; !merged && i < M + 2; i += 2, ++k) add(fold, scr[k], i, std::min(M + 2, i + 2));
+    return ts;
+  };
+  // The same with a new eta (combination et, into ne), whose task is te.
+  auto state_tasks = [&](TaskSpec te, TaskSpec tp, const std::vector<TermSpec> &et, const std::vector<TermSpec> &pt,
+                         int ne, int np, const std::vector<int> &scr, bool from_terms) {
+    te.outs.push_back(B.store(ne, et));
+    te.outs.back().keep = !from_terms;
+    for (auto &o : eta_lifts(ne)) {
+      if (from_terms) o = lift_of(o, et);
+      if (!fp32 && o.dst_mixed == mE) {  // eta itself, as psi's (kref moves to the lift's factor)
+        te.outs.back().dst_mixed = mE;
+        te.outs.back().lift_coef = B.inv_n * kref;
+        continue;
+      }
+      te.outs.push_back(std::move(o));
+    }
+    std::vector<TaskSpec> ts = psi_tasks(tp, pt, np, scr, from_terms);
+    ts.insert(ts.begin() + 1, te);
+    return ts;
+  };
   // lifts of the stage state (e, p) for level 1 (and G for M == 1)
   auto l0_tasks = [&](int e, int p, bool lift_g) {
     std::vector<TaskSpec> ts;
@@ -452,11 +539,8 @@ Plan build_plan(const PlanParams &pp, double dt) {
       t.outs.push_back(std::move(o));
       ts.push_back(std::move(t));
     };
-    one(B.lift(mE, {{e, 0, kref}}));
-    one(B.lift(mEy, {{e, SYM_IKY, 1.0}}));
-    one(B.lift(mP, {{p, 0, 1.0}}));
-    one(B.lift(mPy, {{p, SYM_IKY, 1.0}}));
-    for (int l = 1; l <= M; ++l) one(B.lift(mL[l], {{p, (uint32_t)l, 1.0 / kpow(l)}}));
+    for (auto &o : eta_lifts(e)) one(std::move(o));
+    for (auto &o : psi_lifts(p, 0, M + 2)) one(std::move(o));
     if (M == 1) {
       TaskSpec t;
       t.outs.push_back(B.store(bG, {{p, 1u, 1.0}}));
@@ -472,7 +556,8 @@ Plan build_plan(const PlanParams &pp, double dt) {
   // same launch.  Its launch is marked for fold teams (d2 = kMaxFolds): a
   // single grid runs it with one team per fold and per output, side by side
   // (a 512 x 512 grid has only 256 columns, one block per CU).
-  auto last_level_g = [&](int p, bool lift_g) -> std::vector<TaskSpec> {
+  // g0_psi = false: without the G0 psi term.
+  auto last_level_g = [&](int p, bool lift_g, bool g0_psi = true) -> std::vector<TaskSpec> {
     const int r = M - 1;
     TaskSpec t;
     t.fwd = oPHI;
@@ -480,7 +565,8 @@ Plan build_plan(const PlanParams &pp, double dt) {
     t.fwd_coef = B.fold * epow(r);
     t.more.push_back({oWP, SYM_TAPER, B.fold * kref * epow(r)});
     if ((r == 1 && hasGX1) || (r == M - 1 && hasGXlast)) t.more.push_back({oGX, SYM_TAPER, B.fold});
-    std::vector<TermSpec> tm{{p, 1u, 1.0}};
+    std::vector<TermSpec> tm;
+    if (g0_psi) tm.push_back({p, 1u, 1.0});
     for (int i = 1; i < r; ++i) {
       tm.push_back({bPHI[i], 1u, epow(i)});
       tm.push_back({bWP[i], 0u, epow(i)});
@@ -559,6 +645,9 @@ Plan build_plan(const PlanParams &pp, double dt) {
     seq.push_back(row_launch(L_ROW_BASE, {b >= 0 ? exit2_prog : exit1_prog}));
   };
 
+  // scratch spectra of the split L_l lifts where IF-AB2 keeps no forcing
+  const std::vector<int> scratch{bFe[0], bFp[0], bFe[1], bFp[1]};
+
   Plan &P = B.P;
   // zk_dtn
   entry(P.dtn);
@@ -608,44 +697,36 @@ Plan build_plan(const PlanParams &pp, double dt) {
         const std::vector<TermSpec> pt{{bUP[par], 0, 1.0}, {se[s], 0, -g * c}, {-1, 0, c}};  // next stage psi
         const std::vector<TermSpec> et{{bUE[par], 0, 1.0}, {bG, 0, c}};                      // next stage eta
         tp.outs.push_back(B.store(bAP, ap));
-        tp.outs.push_back(B.store(np[s], pt));
         te.outs.push_back(B.store(bAE, ae));
-        te.outs.push_back(B.store(ne[s], et));
         if (M >= 2) {
-          // The next stage's lifts in the same launch, each from the stage
-          // combination itself (the tasks that need the folded N fold it
-          // again): one launch instead of two.  (M = 1 stores G from psi in
-          // its lift launch, which te's read of this stage's G forbids.)
-          auto with = [](std::vector<TermSpec> tm, uint32_t sym, double f) {
-            for (auto &x : tm) {
-              x.sym |= sym;
-              x.coef *= f;
-            }
-            return tm;
-          };
-          tp.outs.push_back(B.lift(mP, with(pt, 0, 1.0)));
-          tp.outs.push_back(B.lift(mPy, with(pt, SYM_IKY, 1.0)));
-          te.outs.push_back(B.lift(mE, with(et, 0, kref)));
-          te.outs.push_back(B.lift(mEy, with(et, SYM_IKY, 1.0)));
-          std::vector<TaskSpec> ts{tp, te};
-          for (int l = 1; l <= M; l += 2) {
-            TaskSpec tl = B.fold_task(mN);
-            for (int m = l; m <= std::min(M, l + 1); ++m)
-              tl.outs.push_back(B.lift(mL[m], with(pt, (uint32_t)m, 1.0 / kpow(m))));
-            ts.push_back(tl);
-          }
-          seq.push_back(B.col_launch(L_COL_PAD, ts));
+          // The next stage's lifts in the same launch: one launch instead of
+          // two.  (M = 1 stores G from psi in its lift launch, which te's read
+          // of this stage's G forbids.)
+          seq.push_back(B.col_launch(L_COL_PAD, state_tasks(te, tp, et, pt, ne[s], np[s], scratch, fp32)));
           continue;
         }
+        tp.outs.push_back(B.store(np[s], pt));
+        te.outs.push_back(B.store(ne[s], et));
       } else {
         const double h = dt / 6.0;
-        tp.outs.push_back(B.store(np[s], {{bUP[par], FILT, 1.0}, {bAP, FILT, h}, {se[s], FILT, -g * h}, {-1, FILT, h}}));
-        te.outs.push_back(B.store(ne[s], {{bUE[par], FILT, 1.0}, {bAE, FILT, h}, {bG, FILT, h}}));
+        const std::vector<TermSpec> pt{{bUP[par], FILT, 1.0}, {bAP, FILT, h}, {se[s], FILT, -g * h}, {-1, FILT, h}};
+        const std::vector<TermSpec> et{{bUE[par], FILT, 1.0}, {bAE, FILT, h}, {bG, FILT, h}};
+        if (M >= 2) {  // the same with the next step's lifts
+          auto &all = P.step_body_lift[par];
+          all = seq;
+          all.push_back(B.col_launch(L_COL_PAD, state_tasks(te, tp, et, pt, ne[s], np[s], scratch, false)));
+        }
+        tp.outs.push_back(B.store(np[s], pt));
+        te.outs.push_back(B.store(ne[s], et));
       }
       seq.push_back(B.col_launch(L_COL_PAD, {tp, te}));
       if (s < 4) seq.push_back(B.col_launch(L_COL_PAD, l0_tasks(ne[s], np[s], true)));
     }
     P.step_lift[par].push_back(B.col_launch(L_COL_PAD, l0_tasks(bUE[par], bUP[par], true)));
+    if (M == 1) {  // two launches (see above); step_lift of the other parity follows in the same form
+      P.step_body_lift[par] = seq;
+      P.step_body_lift[par].push_back(B.col_launch(L_COL_PAD, l0_tasks(bUE[1 - par], bUP[1 - par], true)));
+    }
     exit_seq(P.step_exit[par], bUE[par], bUP[par]);
     P.chk_e[par] = bUE[par];
     P.chk_p[par] = bUP[par];
@@ -661,9 +742,10 @@ Plan build_plan(const PlanParams &pp, double dt) {
         const int e = bUE[par], p = bUP[par];
         core(seq, e, p, true);
         seq.push_back(row_launch(L_ROW_PAD, {bern_prog}));
-        TaskSpec t = B.fold_task(mN);  // X = N (folded Bernoulli term)
-        t.outs.push_back(B.store(bFe[par], {{bG, 0, 1.0}, {p, 1u, -1.0}}));
-        t.outs.push_back(B.store(bFp[par], {{-1, 0, 1.0}}));
+        // X = N (folded Bernoulli term) in each task; F_n is stored by a task of its own
+        TaskSpec tf = B.fold_task(mN);
+        tf.outs.push_back(B.store(bFp[par], {{-1, 0, 1.0}}));
+        tf.outs.push_back(B.store(bFe[par], {{bG, 0, 1.0}, {p, 1u, -1.0}}));
         const double w = first ? 1.0 : 1.5;  // F* = 3/2 F_n - 1/2 F_{n-1} (F_0 at the bootstrap)
         std::vector<TermSpec> te{{e, ifs(IC), 1.0}, {p, ifs(IA), 1.0},  {bG, ifs(IS), w},
                                  {p, ifs(IS) | 1u, -w}, {-1, ifs(IU), w}};
@@ -675,9 +757,22 @@ Plan build_plan(const PlanParams &pp, double dt) {
           tp.push_back({bFe[1 - par], ifs(IV), 0.5});
           tp.push_back({bFp[1 - par], ifs(IS), -0.5});
         }
-        t.outs.push_back(B.store(bUE[1 - par], te));
-        t.outs.push_back(B.store(bUP[1 - par], tp));
-        seq.push_back(B.col_launch(L_COL_PAD, {t}));
+        auto &all = first ? P.ab2_first_lift[par] : P.ab2_body_lift[par];
+        all = seq;
+        if (M >= 2) {  // with the next step's lifts; RK4's stage spectra are free
+          auto ts = state_tasks(B.fold_task(mN), B.fold_task(mN), te, tp, bUE[1 - par], bUP[1 - par],
+                                {bSE[0], bSP[0], bSE[1], bSP[1]}, false);
+          ts.push_back(tf);
+          all.push_back(B.col_launch(L_COL_PAD, ts));
+        }
+        TaskSpec t1 = B.fold_task(mN), t2 = B.fold_task(mN);
+        t1.outs.push_back(B.store(bUE[1 - par], te));
+        t2.outs.push_back(B.store(bUP[1 - par], tp));
+        seq.push_back(B.col_launch(L_COL_PAD, {t1, t2, tf}));
+        if (M == 1) {
+          all.push_back(seq.back());
+          all.push_back(B.col_launch(L_COL_PAD, l0_tasks(bUE[1 - par], bUP[1 - par], true)));
+        }
       }
   }
 
@@ -692,11 +787,23 @@ Plan build_plan(const PlanParams &pp, double dt) {
     ts[1].outs.push_back(B.store(bUP[0], {{-1, SYM_INVG0, 1.0}}));
     P.inv_entry.push_back(B.col_launch(L_COL_BASE, ts));
     P.inv_entry.push_back(B.col_launch(L_COL_PAD, l0_tasks(bUE[0], bUP[0], false)));
+    // psi = G0^{-1} (v - (G^[M] - G0) psi): the iteration's last level forms G
+    // without its G0 psi term, so no task of the update reads the psi that one
+    // of them stores; eta's lifts stay from the entry.
     core(P.inv_iter, bUE[0], bUP[0], false);
-    TaskSpec t;
-    t.outs.push_back(B.store(bUP[0], {{bUP[0], 0, 1.0}, {bV, SYM_INVG0, 1.0}, {bG, SYM_INVG0, -1.0}}));
-    P.inv_iter.push_back(B.col_launch(L_COL_PAD, {t}));
-    P.inv_iter.push_back(B.col_launch(L_COL_PAD, l0_tasks(bUE[0], bUP[0], false)));
+    if (M >= 2 && !fp32) {
+      P.inv_iter.back() = B.col_launch(L_COL_PAD, last_level_g(bUP[0], false, false));
+      P.inv_iter.back().d2 = kMaxFolds;
+      const std::vector<TermSpec> pt{{bV, SYM_INVG0, 1.0}, {bG, SYM_INVG0, -1.0}};
+      P.inv_iter.push_back(B.col_launch(L_COL_PAD, psi_tasks(TaskSpec{}, pt, bUP[0], scratch, false)));
+    } else {  // psi + G0^{-1} (v - G psi), lifted by a launch of its own (FP32: the same bits)
+      TaskSpec t;
+      t.outs.push_back(B.store(bUP[0], {{bUP[0], 0, 1.0}, {bV, SYM_INVG0, 1.0}, {bG, SYM_INVG0, -1.0}}));
+      P.inv_iter.push_back(B.col_launch(L_COL_PAD, {t}));
+      auto ts = l0_tasks(bUE[0], bUP[0], false);
+      ts.erase(ts.begin(), ts.begin() + 2);  // eta's
+      P.inv_iter.push_back(B.col_launch(L_COL_PAD, ts));
+    }
     exit_seq(P.inv_exit, bUP[0], -1);
   }
 
@@ -823,11 +930,15 @@ Plan build_plan(const PlanParams &pp, double dt) {
                 l.bytes += rows * K * cb;
                 l.flops += K * fft_flops(rows);
               }
+            int kept = -1;
             for (int i = 0; i < t.no; ++i) {
               const ColOut &o = P.outs[t.o0 + i];
               for (int j = 0; j < o.nt; ++j)
-                if (P.terms[o.t0 + j].src >= 0) l.bytes += rows_base * K * 16.0;
-              if (o.dst_base >= 0) l.bytes += rows_base * K * 16.0;
+                if (P.terms[o.t0 + j].src >= 0 && P.terms[o.t0 + j].src != kept) l.bytes += rows_base * K * 16.0;
+              if (o.dst_base >= 0) {
+                l.bytes += rows_base * K * 16.0;
+                if (o.keep) kept = o.dst_base;  // held in registers from here on
+              }
               if (o.dst_mixed >= 0) {
                 l.bytes += rows * K * cb;
                 l.flops += K * fft_flops(rows);
@@ -849,6 +960,8 @@ std::vector<std::vector<Launch> *> plan_sequences(Plan &p) {
                                           &p.step_body[0], &p.step_body[1], &p.step_lift[0], &p.step_lift[1],
                                           &p.step_exit[0], &p.step_exit[1], &p.rhs_g,        &p.filter,
                                           &p.ab2_first[0], &p.ab2_first[1], &p.ab2_body[0],  &p.ab2_body[1],
+                                          &p.step_body_lift[0], &p.step_body_lift[1], &p.ab2_first_lift[0], &p.ab2_first_lift[1],
+                                          &p.ab2_body_lift[0], &p.ab2_body_lift[1],
                                           &p.inv_entry,    &p.inv_iter,     &p.inv_exit,     &p.lift_phi};
   for (int r = 1; r <= p.depth_chunk_max; ++r) v.push_back(&p.depth_chunk[r]);
   return v;
@@ -933,6 +1046,40 @@ std::string validate_plan(const Plan &p, int rows_pad, int rows_base) {
         for (int k = l.first; k < l.first + l.count; ++k)
           for (int i = 0; i < p.tasks[k].no; ++i)
             if (p.outs[p.tasks[k].o0 + i].lift_sym && l.c2 != 1) return "lift_sym output in a plain column launch";
+        // a stored spectrum belongs to its task: no other task of the launch
+        // stores or reads it, and the task itself reads it only as its kept
+        // one (held in registers; its memory may be other teams' stores)
+        std::vector<int> owner(p.nbase, -1);
+        for (int k = l.first; k < l.first + l.count; ++k)
+          for (int i = 0; i < p.tasks[k].no; ++i) {
+            const int d = p.outs[p.tasks[k].o0 + i].dst_base;
+            if (d >= 0 && owner[d] >= 0) return "base spectrum stored twice in one launch";
+            if (d >= 0) owner[d] = k;
+          }
+        for (int k = l.first; k < l.first + l.count; ++k) {
+          std::vector<char> stored(p.nbase, 0);
+          int kept = -1;
+          bool sum = true;  // the folded sum is still held
+          for (int i = 0; i < p.tasks[k].no; ++i) {
+            const ColOut &o = p.outs[p.tasks[k].o0 + i];
+            for (int j = 0; j < o.nt; ++j) {
+              const int b = p.terms[o.t0 + j].src;
+              if (b < 0 && !sum) return "folded sum read after a kept output";
+              if (b < 0) continue;
+              if (owner[b] >= 0 && owner[b] != k) return "base spectrum read by another task than its store's";
+              if (stored[b] && b != kept) return "stored spectrum read, but not the kept one";
+            }
+            if (o.dst_base >= 0) {
+              stored[o.dst_base] = 1;
+              if (o.keep) {
+                kept = o.dst_base;
+                sum = false;
+              }
+            } else if (o.keep) {
+              return "kept output without a store";
+            }
+          }
+        }
       } else if (l.kind == L_PARSEVAL) {
         if (l.first >= p.nbase || l.count >= p.nbase || l.c2 >= p.nbase || l.d2 >= p.nbase) return "parseval";
       } else {

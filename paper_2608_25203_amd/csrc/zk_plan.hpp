@@ -56,6 +56,7 @@ struct Plan {
   std::vector<Launch> step_entry;     // physical -> spectral state U[0], lifts for stage 1
   std::vector<Launch> step_body[2];   // one RK4 step from U[p] to U[1-p] (no trailing lift)
   std::vector<Launch> step_lift[2];   // lifts of U[p] for the next step's stage 1
+  std::vector<Launch> step_body_lift[2];  // step_body[p], then step_lift[1-p] (in one launch with its last, M >= 2)
   std::vector<Launch> step_exit[2];   // U[p] -> physical
   int chk_e[2], chk_p[2];             // base ids of U[p] (finite check)
   // Pieces for stepping with an externally supplied DtN (learned closure):
@@ -63,6 +64,7 @@ struct Plan {
   // forcing F_n stored in F[p]; the first step of a call is the IF-Euler bootstrap.
   std::vector<Launch> ab2_first[2];
   std::vector<Launch> ab2_body[2];
+  std::vector<Launch> ab2_first_lift[2], ab2_body_lift[2];  // as step_body_lift
   // Inverse DNO map (eq:psi_inverse): (eta, v) -> psi; entry seeds psi = G0^{-1} v,
   // each iteration psi <- psi + G0^{-1} (v - G^[M] psi), exit writes psi.
   std::vector<Launch> inv_entry, inv_iter, inv_exit;

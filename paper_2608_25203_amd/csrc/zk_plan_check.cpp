@@ -83,6 +83,12 @@ int main(int argc, char **argv) {
   dump_seq("ab2_first1", p.ab2_first[1], false);
   dump_seq("ab2_body0", p.ab2_body[0], false);
   dump_seq("ab2_body1", p.ab2_body[1], false);
+  dump_seq("step_body_lift0", p.step_body_lift[0], false);
+  dump_seq("step_body_lift1", p.step_body_lift[1], false);
+  dump_seq("ab2_first_lift0", p.ab2_first_lift[0], false);
+  dump_seq("ab2_first_lift1", p.ab2_first_lift[1], false);
+  dump_seq("ab2_body_lift0", p.ab2_body_lift[0], false);
+  dump_seq("ab2_body_lift1", p.ab2_body_lift[1], false);
   dump_seq("inv_entry", p.inv_entry, false);
   dump_seq("inv_iter", p.inv_iter, false);
   dump_seq("inv_exit", p.inv_exit, false);
