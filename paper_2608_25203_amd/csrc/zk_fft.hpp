@@ -117,9 +117,27 @@ constexpr double cos_sin_frac(int m, int n, bool want_sin) {
   return (double)(want_sin ? ss : cc);
 }
 
-// a * exp(DIR * 2 pi i * M / NN) for compile-time M, NN
+// a c + b s of two positive constants c, s: ORDER = 2 rounds b s first and
+// fuses the other product, 3 the other way; 1 leaves the choice to the compiler.
+template <int ORDER, typename R>
+__device__ __forceinline__ R sum2(R a, R c, R b, R s) {
+  if constexpr (ORDER == 2) return __builtin_elementwise_fma(a, c, b * s);
+  else if constexpr (ORDER == 3) return __builtin_elementwise_fma(b, s, a * c);
+  else return a * c + b * s;
+}
+// a * (c + i s) for constants; |DIR| is the ORDER of the part whose products add up
+template <int DIR, bool CPOS, typename R>
+__device__ __forceinline__ cpx<R> rotate(cpx<R> a, R c, R s) {
+  if constexpr (DIR > 1 && CPOS) return {a.x * c - a.y * s, sum2<DIR>(a.y, c, a.x, s)};
+  else if constexpr (DIR < -1 && CPOS) return {sum2<-DIR>(a.x, c, a.y, -s), a.x * s + a.y * c};
+  else return {a.x * c - a.y * s, a.x * s + a.y * c};
+}
+
+// a * exp(sgn(DIR) 2 pi i * M / NN) for compile-time M, NN (0 < M < NN / 2
+// where |DIR| > 1; rotate says what the size of DIR chooses)
 template <int M, int NN, int DIR, typename R>
 __device__ __forceinline__ cpx<R> twc(cpx<R> a) {
+  constexpr int SG = DIR > 0 ? 1 : -1;
   constexpr int mm = ((M % NN) + NN) % NN;
   if constexpr (mm == 0) {
     return a;
@@ -132,16 +150,16 @@ __device__ __forceinline__ cpx<R> twc(cpx<R> a) {
   } else if constexpr (48 % NN == 0) {
     constexpr int j = mm * (48 / NN);
     constexpr double cd = cos48(j);
-    constexpr double sd = DIR * sin48(j);
+    constexpr double sd = SG * sin48(j);
     const R c = (R)cd;
     const R s = (R)sd;
-    return {a.x * c - a.y * s, a.x * s + a.y * c};
+    return rotate<DIR, (cd > 0 && SG * sd > 0)>(a, c, s);
   } else {  // radix-9 and radix-18 steps
     constexpr double cd = cos_sin_frac(mm, NN, false);
-    constexpr double sd = DIR * cos_sin_frac(mm, NN, true);
+    constexpr double sd = SG * cos_sin_frac(mm, NN, true);
     const R c = (R)cd;
     const R s = (R)sd;
-    return {a.x * c - a.y * s, a.x * s + a.y * c};
+    return rotate<DIR, (cd > 0 && SG * sd > 0)>(a, c, s);
   }
 }
 
@@ -278,7 +296,8 @@ __host__ __device__ constexpr int num_passes(int T, int E) {
 __device__ __forceinline__ int lpad(int i) { return i; }
 __host__ __device__ constexpr int lds_len(int N) { return N; }
 
-// Team FFT of N = T * E points (unnormalised, sign DIR).  On entry thread t
+// Team FFT of N = T * E points (unnormalised, sign DIR; team_fft also takes |DIR| > 1
+// for the first pass, see rotate).  On entry thread t
 // holds element t + T*r in v[r].  The first pass is a radix-E butterfly in
 // registers; later passes exchange through LDS.  NBUF = 2 ping-pongs between
 // buf0 and buf1 (one barrier per pass); NBUF = 1 works in place in buf0 (two
@@ -392,7 +411,7 @@ __device__ __forceinline__ cpx<R> *team_fft_impl(cpx<R> (&v)[E], cpx<R> *buf0, c
           if constexpr (DIR > 0) tr.y = -tr.y;
           w[it][r] = cmul(w[it][r], tr);
         }
-        DFT<Rp, DIR, R>::run(w[it]);
+        DFT<Rp, (DIR > 0 ? 1 : -1), R>::run(w[it]);
         if constexpr (to_regs) {
 #pragma unroll
           for (int r = 0; r < Rp; ++r) o[it][r] = w[it][r];  // base = j in the last pass

@@ -1018,6 +1018,11 @@ __device__ __forceinline__ void col_body(const ColArgs<real> &a, int task_index,
   // LDS round trip fewer; 1024-thread teams and base lengths (measured
   // faster without) and the depth-lift variant (whose registers these forms
   // would push past an occupancy step) use team_fft with LDS readouts.
+  // FP32 base columns with a factor 3 or 5 pin which product of a first-pass
+  // rotation is rounded first: left open, the choice follows the code around the
+  // transform, and another one moves results by FP32 rounding.
+  constexpr bool PIN = sizeof(real) == 4 && !S::PADDED && (E == 6 || E == 10);
+  constexpr int FD = PIN ? 2 : 1, LD = PIN ? (LIFTSYM ? 3 : 2) : 1;  // folds, lifts
   // Either way a fold's result is element t + T r in v[r]; base element q
   // sits at padded (or base) position t + T base_slot(q).
   constexpr bool XP = T <= 512 && S::PADDED && !LIFTSYM, KEEP = XP;
@@ -1055,7 +1060,7 @@ __device__ __forceinline__ void col_body(const ColArgs<real> &a, int task_index,
       cpx<real> v[E];
 #pragma unroll
       for (int r = 0; r < E; ++r) v[r] = x[0][r];
-      const cpx<real> *res = team_fft<real, N, E, NB, -1>(v, b0, b1, tw, t);
+      const cpx<real> *res = team_fft<real, N, E, NB, -FD>(v, b0, b1, tw, t);
       if (use) fold_into([&](int r) { return res[lpad(t + T * r)]; }, fsym, fcoef);
     }
   };
@@ -1252,7 +1257,7 @@ __device__ __forceinline__ void col_body(const ColArgs<real> &a, int task_index,
 #pragma unroll
               for (int r = 0; r < HO::R; ++r) put(HO::elem(t, it, r), o[it][r]);
       } else {
-        const cpx<real> *res = team_fft<real, N, E, NB, +1>(z, b0, b1, tw, t);
+        const cpx<real> *res = team_fft<real, N, E, NB, LD>(z, b0, b1, tw, t);
         if (writer)
 #pragma unroll
           for (int r = 0; r < E; ++r) put(t + T * r, res[lpad(t + T * r)]);
