@@ -11,7 +11,8 @@ namespace zk {
 namespace {
 
 constexpr int kMaxM = 8;
-constexpr int kSplitPoints = 1 << 18;  // grid points up to which a state's lifts are split (see below)
+// a state's lifts are split up to so many grid points, and on shorter rows (see below)
+constexpr int kSplitPoints = 1 << 18, kSplitRow = 512;
 
 struct Fac {  // a factor of a product: mixed field id and x-derivative flag
   int f;
@@ -455,8 +456,11 @@ Plan build_plan(const PlanParams &pp, double dt) {
   // folds and reads.  RK4 steps split and merged: 552 and 570 us at 512^2 (M =
   // 4, FP64), 371 and 401 at 256^2; 1459 and 1414 at 640^2, 2082 and 2011 at
   // 1024^2 (FP32 1431 and 1360), 14.62 and 14.04 ms at 2048^2 (M = 5; FP32
-  // 10.83 and 10.43).
-  const bool merged = pp.nx * pp.ny > kSplitPoints;
+  // 10.83 and 10.43); rows of 256 points have too few columns at any height
+  // (256 x 2048, M = 3, FP32: columns 31 and 34 us a launch).  A batch's tiles
+  // follow the same rule (FP32 batches of tiles up to 256^2 and 512^2, split and
+  // merged: 3053 and 3261, 4861 and 4959 us).
+  const bool merged = pp.nx * pp.ny > kSplitPoints && pp.nx >= kSplitRow;
   // FP32 plans lift a stage's state from its terms, each with the lift's symbol,
   // as a launch of its own would sum them: a last bit of an FP64 sum that tips
   // the rounding to FP32 grows to the rounding level of the FP32 transforms, and

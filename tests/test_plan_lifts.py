@@ -38,3 +38,15 @@ def test_fused_lift_sequences_match_oracle(nx, ny, M, ab2):
     ref = (m.step_ifab2 if ab2 else m.step)(eta, psi, 0.004, 3)
     for a, b in zip(got, ref):
         assert rel(a, b) < 1e-13
+
+
+def test_tall_grid_splits_its_lifts():
+    """Above 2^18 points but on rows of fewer than 512: the fused sequences
+    of the split form, the bar as above."""
+    nx, ny, M = 320, 1024, 2
+    Lx, Ly = TWO_PI * nx / 32, TWO_PI * ny / 32
+    eta, psi = random_band_fields(nx, ny, 45, 5, amplitude=0.02)
+    I = Interp(nx, ny, Lx, Ly, 0.8, 9.81, M)
+    m = HOSModel(Grid(nx, ny, Lx, Ly, 0.8), M)
+    for a, b in zip(run_fused(I, eta, psi, 0.004, 2, False), m.step(eta, psi, 0.004, 2)):
+        assert rel(a, b) < 1e-13
