@@ -505,99 +505,120 @@ __device__ __forceinline__ void row_body(const RowArgs<real> &a, int prog, int b
   };
 
   // The operations, shared by the interpreter and the compiled shapes.
-  // maxima(op, ma, mb): the two fields' maxima over all columns
-  auto do_ld2 = [&](const RowOp &op, auto &&maxima) {
+  // LD2 in two halves, so that a compiled program of a small team can issue the
+  // next LD2's loads before it transforms the current one.  The two real fields
+  // share one complex transform; each is scaled by a power of two from its field
+  // maximum (published by the lifts that wrote it) so that neither drowns in
+  // the rounding of the other, and unscaled exactly afterwards.
+  // Padded passes up to 512-thread teams load the half spectra in the
+  // layout of the transposed transform's first butterflies (element
+  // p = j + NB r of butterfly j = t + T it); its result arrives in z[]
+  // as element t + T e without an LDS readout.  (1024-thread teams, and
+  // base lengths, whose last pass keeps only half the team busy,
+  // measured faster with team_fft from the t + T e layout.)  The
+  // permuted form loads element t + T e and leaves in z[s] the point
+  // s + E bitrev(t / 64) + E (T / 64) bitrev6(t % 64) of the row.
+  constexpr bool XP = !LANES && T <= 512 && S::PADDED;
+  using HL = HbmLayout<N, E, XP>;
+  using Ld2Regs = HbmRegs<real, N, E, XP>;
+  auto ld2_load = [&](const RowOp &op, Ld2Regs &xa, Ld2Regs &xb) {
     const cpx<real> *Fa = a.mix + (long long)op.fa * a.mix_stride;
     const bool has_b = op.fb >= 0;
     const cpx<real> *Fb = a.mix + (long long)(has_b ? op.fb : op.fa) * a.mix_stride;
-    const bool dxa = op.fla & FL_DX, dxb = op.flb & FL_DX;
-    // The two real fields share one complex transform; each is scaled by
-    // a power of two from its field maximum (published by the lifts that
-    // wrote it) so that neither drowns in the rounding of the other, and
-    // unscaled exactly afterwards.
-    // Data loads first; the field maxima (one per column, published by
-    // the lifts) are reduced over all columns by each wavefront on its
-    // own, so no block barrier sits between the loads and their use.
-    // Padded passes up to 512-thread teams load the half spectra in the
-    // layout of the transposed transform's first butterflies (element
-    // p = j + NB r of butterfly j = t + T it); its result arrives in z[]
-    // as element t + T e without an LDS readout.  (1024-thread teams, and
-    // base lengths, whose last pass keeps only half the team busy,
-    // measured faster with team_fft from the t + T e layout.)  The
-    // permuted form loads element t + T e and leaves in z[s] the point
-    // s + E bitrev(t / 64) + E (T / 64) bitrev6(t % 64) of the row.
-    auto ld2 = [&](auto xp_c, auto lanes_c) {
-      constexpr bool XP = decltype(xp_c)::value, PERMUTED = decltype(lanes_c)::value;
-      using HL = HbmLayout<N, E, XP>;
-      cpx<real> xa[HL::IT][HL::R], xb[HL::IT][HL::R];
-      auto elem = [&](int it, int r) { return HL::elem(t, it, r); };
-      auto live = [&](int it) { return HL::live(t, it); };
 #pragma unroll
-      for (int it = 0; it < HL::IT; ++it)
+    for (int it = 0; it < HL::IT; ++it)
 #pragma unroll
-        for (int r = 0; r < HL::R; ++r) {
-          const int p = elem(it, r);
-          const bool pos = p < S::KR * T, neg = p > S::NEG0 * T;  // kept band, upper half by symmetry
-          xa[it][r] = {(real)0, (real)0};
-          xb[it][r] = {(real)0, (real)0};
-          if (in_row && live(it) && (pos || neg)) {
-            const int idx = mix_index<real>(pos ? p : N - p, row, a.rows);
-            xa[it][r] = gload(Fa, idx);
-            if (has_b) xb[it][r] = gload(Fb, idx);
-          }
+      for (int r = 0; r < HL::R; ++r) {
+        const int p = HL::elem(t, it, r);
+        const bool pos = p < S::KR * T, neg = p > S::NEG0 * T;  // kept band, upper half by symmetry
+        xa[it][r] = {(real)0, (real)0};
+        xb[it][r] = {(real)0, (real)0};
+        if (in_row && HL::live(t, it) && (pos || neg)) {
+          const int idx = mix_index<real>(pos ? p : N - p, row, a.rows);
+          xa[it][r] = gload(Fa, idx);
+          if (has_b) xb[it][r] = gload(Fb, idx);
         }
-      float ma = 0.f, mb = 0.f;
-      maxima(op, ma, mb);
-      const float2 pa = pow2_scale(ma);
-      const float2 pb = has_b ? pow2_scale(mb) : make_float2(1.f, 1.f);
-      const real sa = (real)pa.x, sb = (real)pb.x;
-#pragma unroll
-      for (int it = 0; it < HL::IT; ++it)
-#pragma unroll
-        for (int r = 0; r < HL::R; ++r) {
-          const int p = elem(it, r);
-          const bool pos = p < S::KR * T, neg = p > S::NEG0 * T;
-          cpx<real> za = xa[it][r], zbr = xb[it][r];
-          if (pos || neg) {
-            const real kxv = (real)(a.kx_scale * (pos ? p : N - p));
-            if (dxa) za = {-kxv * za.y, kxv * za.x};
-            if (dxb) zbr = {-kxv * zbr.y, kxv * zbr.x};
-            if (neg) {
-              za.y = -za.y;
-              zbr.y = -zbr.y;
-            }
-          }
-          xa[it][r] = {za.x * sa - zbr.y * sb, za.y * sa + zbr.x * sb};
-        }
-      settle_tw();
-      if constexpr (PERMUTED) {
-#pragma unroll
-        for (int e = 0; e < E; ++e) z[e] = xa[0][e];
-        perm_ifft<real, T, E, +1>(z, b0, b1, tw, t);
-      } else {
-        fft_in<real, N, E, NB, +1, XP>(xa, z, b0, b1, tw, t);
       }
-      const real ia = (real)pa.y, ib = (real)pb.y;
+  };
+  // ma, mb: the two fields' maxima over all columns; next(): called before the
+  // transform, when xa and xb are free again
+  auto ld2_transform = [&](const RowOp &op, Ld2Regs &xa, Ld2Regs &xb, float ma, float mb, auto &&next) {
+    const bool has_b = op.fb >= 0, dxa = op.fla & FL_DX, dxb = op.flb & FL_DX;
+    const float2 pa = pow2_scale(ma);
+    const float2 pb = has_b ? pow2_scale(mb) : make_float2(1.f, 1.f);
+    const real sa = (real)pa.x, sb = (real)pb.x;
+    Ld2Regs x;
 #pragma unroll
-      for (int e = 0; e < E; ++e) z[e] = {z[e].x * ia, z[e].y * ib};
-    };
-    if constexpr (LANES) ld2(std::false_type{}, std::true_type{});
-    else ld2(std::integral_constant<bool, T <= 512 && S::PADDED>{}, std::false_type{});
+    for (int it = 0; it < HL::IT; ++it)
+#pragma unroll
+      for (int r = 0; r < HL::R; ++r) {
+        const int p = HL::elem(t, it, r);
+        const bool pos = p < S::KR * T, neg = p > S::NEG0 * T;
+        cpx<real> za = xa[it][r], zbr = xb[it][r];
+        if (pos || neg) {
+          const real kxv = (real)(a.kx_scale * (pos ? p : N - p));
+          if (dxa) za = {-kxv * za.y, kxv * za.x};
+          if (dxb) zbr = {-kxv * zbr.y, kxv * zbr.x};
+          if (neg) {
+            za.y = -za.y;
+            zbr.y = -zbr.y;
+          }
+        }
+        x[it][r] = {za.x * sa - zbr.y * sb, za.y * sa + zbr.x * sb};
+      }
+    settle_tw();
+    next();
+    if constexpr (LANES) {
+#pragma unroll
+      for (int e = 0; e < E; ++e) z[e] = x[0][e];
+      perm_ifft<real, T, E, +1>(z, b0, b1, tw, t);
+    } else {
+      fft_in<real, N, E, NB, +1, XP>(x, z, b0, b1, tw, t);
+    }
+    const real ia = (real)pa.y, ib = (real)pb.y;
+#pragma unroll
+    for (int e = 0; e < E; ++e) z[e] = {z[e].x * ia, z[e].y * ib};
   };
   constexpr int NC = S::KR * T;  // nx / 2 columns: the length of a field's column maxima
   // Each wavefront reduces every column maximum of the two fields on its own
   // (no barrier between the loads and their use).
-  auto wave_maxima = [&](const RowOp &op, float &ma, float &mb) {
+  constexpr int NCW = (NC + 63) / 64;
+  struct Maxima {
+    float a[NCW], b[NCW];
+  };
+  auto maxima_load = [&](const RowOp &op, Maxima &m) {
     const float *ca = a.colmax + (long long)op.fa * NC;
     const float *cb = a.colmax + (long long)(op.fb >= 0 ? op.fb : op.fa) * NC;
     const int lane = threadIdx.x & 63;
 #pragma unroll
-    for (int c = lane; c < NC; c += 64) {
-      ma = fmaxf(ma, gload1(ca, c));
-      mb = fmaxf(mb, gload1(cb, c));
+    for (int k = 0; k < NCW; ++k) {
+      const int c = lane + 64 * k;
+      m.a[k] = c < NC ? gload1(ca, c) : 0.f;
+      m.b[k] = c < NC ? gload1(cb, c) : 0.f;
+    }
+  };
+  auto maxima_reduce = [&](const Maxima &m, float &ma, float &mb) {
+    ma = mb = 0.f;
+#pragma unroll
+    for (int k = 0; k < NCW; ++k) {
+      ma = fmaxf(ma, m.a[k]);
+      mb = fmaxf(mb, m.b[k]);
     }
     ma = wave_max(ma);
     mb = wave_max(mb);
+  };
+  // LD2 with its loads right before (data loads first)
+  auto wave_maxima = [&](const RowOp &op, float &ma, float &mb) {
+    Maxima m;
+    maxima_load(op, m);
+    maxima_reduce(m, ma, mb);
+  };
+  auto do_ld2 = [&](const RowOp &op, auto &&maxima) {
+    Ld2Regs xa, xb;
+    ld2_load(op, xa, xb);
+    float ma = 0.f, mb = 0.f;
+    maxima(op, ma, mb);
+    ld2_transform(op, xa, xb, ma, mb, [] {});
   };
   // LDP and STP act on caller fields, whose rows have the base length only.
   auto do_ldp = [&](const RowOp &op) {
@@ -685,6 +706,30 @@ __device__ __forceinline__ void row_body(const RowArgs<real> &a, int prog, int b
           constexpr bool BLOCK_MAXIMA = NC >= kBlockMaximaCols;
           constexpr int NW = S::BS / 64;
           const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+          // Small teams (rows of up to 256 points, FP32 64): a grid of such rows
+          // leaves most of the chip idle, so a block's own latencies are the
+          // launch's time: every op record is read up front, and each LD2's data
+          // and maxima are requested before the transform of the LD2 before it
+          // (RK4 steps: 371 to 361 us at 256^2, 355 to 333 at 192^2, M = 4, FP64).
+          // Larger teams have other blocks to fill the gaps and would lose one
+          // of them to the registers (512 points: 21.9 to 22.9 us a launch), as
+          // would FP32's of 64 and 128 threads in a batch of tiles.
+          constexpr bool EARLY = T <= (sizeof(real) == 8 ? 128 : 32);
+          constexpr int LEN = kRowShapeLen[SH];
+          RowOp rec[EARLY ? LEN : 1];
+          Ld2Regs xa, xb;
+          Maxima mx;
+          if constexpr (EARLY) {
+#pragma unroll
+            for (int i = 0; i < LEN; ++i) rec[i] = uniform_load(a.ops + pg.op0 + i);
+            static_for<0, LEN>([&](auto ic) {
+              constexpr int I = decltype(ic)::value;
+              if constexpr ((kRowShapeOps[SH][I] & 255) == OP_LD2 && row_shape_ld2_ordinal(SH, I) == 0) {
+                ld2_load(rec[I], xa, xb);
+                maxima_load(rec[I], mx);
+              }
+            });
+          }
           static_for<0, kRowShapeLen[SH]>([&](auto ic) {
             constexpr int I = decltype(ic)::value;
             if constexpr (BLOCK_MAXIMA && (kRowShapeOps[SH][I] & 255) == OP_LD2) {
@@ -714,8 +759,23 @@ __device__ __forceinline__ void row_body(const RowArgs<real> &a, int prog, int b
             using IA = std::integral_constant<int, A>;
             using IB = std::integral_constant<int, B>;
             using IC = std::integral_constant<int, C>;
-            const RowOp op = uniform_load(a.ops + pg.op0 + I);
-            if constexpr (code == OP_LD2 && BLOCK_MAXIMA) {
+            RowOp op;
+            if constexpr (EARLY) op = rec[I];
+            else op = uniform_load(a.ops + pg.op0 + I);
+            if constexpr (code == OP_LD2 && EARLY) {
+              float ma, mb;
+              maxima_reduce(mx, ma, mb);
+              ld2_transform(op, xa, xb, ma, mb, [&] {
+                static_for<I + 1, LEN>([&](auto nc) {
+                  constexpr int K = decltype(nc)::value;
+                  if constexpr ((kRowShapeOps[SH][K] & 255) == OP_LD2 &&
+                                row_shape_ld2_ordinal(SH, K) == row_shape_ld2_ordinal(SH, I) + 1) {
+                    ld2_load(rec[K], xa, xb);
+                    maxima_load(rec[K], mx);
+                  }
+                });
+              });
+            } else if constexpr (code == OP_LD2 && BLOCK_MAXIMA) {
               constexpr int J = row_shape_ld2_ordinal(SH, I);
               do_ld2(op, [&](const RowOp &, float &ma, float &mb) {
 #pragma unroll
