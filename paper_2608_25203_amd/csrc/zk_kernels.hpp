@@ -1497,8 +1497,8 @@ inline int pow2_team_radix(int n, bool pad) {
   return n % 5 == 0 ? (pad ? 15 : 10) : (n % 3 ? (pad ? 3 : 2) : (pad ? 9 : 6));
 }
 // The default first-pass radix of an axis of n base points, in use from
-// zk_bind on.  FP64: the smallest one, n / 2 threads a transform, except rows
-// of 1024 points and more.  Both sides as FP64 row and column launches in us:
+// zk_bind on.  FP64: the smallest one, n / 2 threads a transform, except some
+// rows.  Both sides as FP64 row and column launches in us:
 // - on axes with a factor 3 or 5 the power-of-two team of one radix-9 or
 //   radix-15 step keeps too few wavefronts busy: 30 and 37 against 17.8 and
 //   14.3 on 384 x 320 (M = 5), 416 and 198 against 354 and 167 on 1536^2 (M =
@@ -1507,11 +1507,16 @@ inline int pow2_team_radix(int n, bool pad) {
 //   45 against 31), which the autotuner settles;
 // - rows of 1024 and 2048 points run E = 6 teams of half the threads, whose
 //   passes are 6, 8, ... instead of 3, 4, ...: 82 to 79 and 471 to 448 (at 512
-//   points E = 6 takes 26 against 21).
+//   points E = 6 takes 26 against 21);
+// - base rows of 256 and 1024 points run E = 4, one pass fewer (4, 4, 4, 4 and
+//   4, 4, 4, 4, 4 against 2, 4, 4, 4, 2 and 2, 4, 4, 4, 4, 2): depth lifts of 20
+//   layers on 1024 x 512 363 to 338, on 1024 x 320 275 to 268, of 32 on 256^2
+//   141 to 138; lengths whose pass count it leaves or raises lose (E = 2 and 4 on
+//   512^2 280 and 288, 128^2 96 and 103, 2048 x 256 415 and 418).
 inline int default_radix(bool f64, bool row, int n, bool pad) {
   if (!f64) return pow2_team_radix(n, pad);
   if (row && pad && n >= 1024 && (n & (n - 1)) == 0) return 6;
-  return pad ? 3 : 2;
+  return pad ? 3 : row && (n == 256 || n == 1024) ? 4 : 2;
 }
 // The compiled first-pass radices of that axis's padded or base transform
 // (the autotuner's candidates): writes up to three into e, returns the count.
