@@ -1349,11 +1349,14 @@ __device__ __forceinline__ BatchItem item_of(const BatchItem *items, int tile0, 
 }
 // FP32 rows of 1024 threads (2048 points) are held to 64 VGPRs, so that two of
 // their blocks share a CU and one's barriers leave the other's wavefronts to
-// run: 307 to 243 us a launch on 2048^2 (M = 5) with 41 spilled registers; the
+// run: 307 to 243 us a launch on 2048^2 (M = 5) with 41 spilled registers, 208
+// as the row program stands now (step 21.5 to 17.2 ms for two); the
 // shorter rows, whose blocks are several a CU anyway, lose 2 us a launch to the
 // scratch set-up (512 points 15.7 to 18.1, 1024 points 46.6 to 45.3).
+// FP32 rows with a radix-15 first pass are held to 256 registers, two wavefronts
+// a SIMD: at 261 a launch of 640 x 768 (M = 3) takes 52 us, at 256 33.
 constexpr int row_min_waves(bool f32, int T, int E, bool pad, bool lanes) {
-  return f32 && T == 1024 && E == 3 && pad && !lanes ? 8 : 1;
+  return f32 && T == 1024 && E == 3 && pad && !lanes ? 8 : f32 && E == 15 ? 2 : 1;
 }
 template <typename real, int T, int E, bool PAD = (E % 3 == 0), bool LANES = false>
 __global__ __launch_bounds__(block_threads(T))

@@ -457,10 +457,13 @@ Plan build_plan(const PlanParams &pp, double dt) {
   // 4, FP64), 371 and 401 at 256^2; 1459 and 1414 at 640^2, 2082 and 2011 at
   // 1024^2 (FP32 1431 and 1360), 14.62 and 14.04 ms at 2048^2 (M = 5; FP32
   // 10.83 and 10.43); rows of 256 points have too few columns at any height
-  // (256 x 2048, M = 3, FP32: columns 31 and 34 us a launch).  A batch's tiles
-  // follow the same rule (FP32 batches of tiles up to 256^2 and 512^2, split and
-  // merged: 3053 and 3261, 4861 and 4959 us).
-  const bool merged = pp.nx * pp.ny > kSplitPoints && pp.nx >= kSplitRow;
+  // (256 x 2048, M = 3, FP32: columns 31 and 34 us a launch).  FP32 passes are
+  // shorter and merge above twice as many points (three steps of M = 3: 512 x 640
+  // 1756 and 2059, 1024 x 512 1684 and 1685; 1024 x 768
+  // 2794 and 2745; of M = 2: 1536 x 384 1974 and 1946).  A batch's tiles follow
+  // the same rule (FP32 batches of tiles up to 256^2 and 512^2, split and merged:
+  // 3053 and 3261, 4861 and 4959 us).
+  const bool merged = pp.nx * pp.ny > (pp.real_bytes == 4 ? 2 : 1) * kSplitPoints && pp.nx >= kSplitRow;
   // FP32 plans lift a stage's state from its terms, each with the lift's symbol,
   // as a launch of its own would sum them: a last bit of an FP64 sum that tips
   // the rounding to FP32 grows to the rounding level of the FP32 transforms, and
