@@ -1355,8 +1355,12 @@ __device__ __forceinline__ BatchItem item_of(const BatchItem *items, int tile0, 
 // scratch set-up (512 points 15.7 to 18.1, 1024 points 46.6 to 45.3).
 // FP32 rows with a radix-15 first pass are held to 256 registers, two wavefronts
 // a SIMD: at 261 a launch of 640 x 768 (M = 3) takes 52 us, at 256 33.
+// Those with a radix-9 first pass of up to 64 threads to 168, three wavefronts,
+// without a spill: left alone they take 170 to 173 (batch of twelve 384^2 tiles,
+// M = 3, two steps: 4.41 and 3.86 ms; forty of 96^2 1.29 and 1.14).
 constexpr int row_min_waves(bool f32, int T, int E, bool pad, bool lanes) {
-  return f32 && T == 1024 && E == 3 && pad && !lanes ? 8 : f32 && E == 15 ? 2 : 1;
+  if (!f32 || lanes) return 1;
+  return T == 1024 && E == 3 && pad ? 8 : E == 9 && T <= 64 ? 3 : E == 15 ? 2 : 1;
 }
 template <typename real, int T, int E, bool PAD = (E % 3 == 0), bool LANES = false>
 __global__ __launch_bounds__(block_threads(T))
