@@ -48,6 +48,11 @@ def compiled(T, E, pad):
     return pad and ((E == 3 and T >= 16) or (E == 6 and 128 <= T <= 512))
 
 
+def early(T, E, pad, f64):
+    """as early_row_shape() in zk_kernels.hpp"""
+    return E == 3 and compiled(T, E, pad) and T <= (128 if f64 else 32)
+
+
 def b(v):
     return "true" if v else "false"
 
@@ -63,6 +68,8 @@ def instances(kind, real):
                 if T not in (2, 4):
                     continue
             out.append((30 if compiled(T, E, pad) else E, T, E, pad, "KF_PLAIN", f"row_kernel_batch<{real}, {T}, {E}, {b(pad)}>"))
+            if early(T, E, pad, real == "double"):
+                out.append((30, T, E, pad, "KF_EARLY", f"row_kernel_batch<{real}, {T}, {E}, true, false, true>"))
             if lanes_ok(T, E, pad, 8 if real == "double" else 4):
                 out.append((8, T, E, pad, "KF_LANES", f"row_kernel_batch<{real}, {T}, {E}, true, true>"))
         else:

@@ -352,6 +352,8 @@ int run_seq_t(zk_ctx *c, const std::vector<Launch> &seq, const Phys &ph) {
         int form = KF_PLAIN, threads = block_threads(sh.T);
         if (row && pad && c->row_fft == ZK_ROW_FFT_LANES && row_lanes_ok(sh.T, sh.E, true, (int)sizeof(real))) {
           form = KF_LANES;
+        } else if (row && early_row_launch(sizeof(real) == 8, sh.T, sh.E, pad, (long long)sh.blocks * l.count)) {
+          form = KF_EARLY;
         } else if (!row && l.c2 == 1) {
           form = KF_LIFTSYM;
         } else if (!row && l.d2 == kMaxFolds && fold_team_shape(sizeof(real) == 8, sh.T, sh.E)) {  // one block per column

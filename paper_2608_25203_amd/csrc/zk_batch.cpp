@@ -38,6 +38,7 @@ struct BL {  // one batched launch
   int nx, ny;
   int T, E, blocks;
   int item0, nitems;
+  long long phase_blocks;  // of all launches of its phase, which share the chip
 };
 using Phase = std::vector<BL>;
 using Key = std::tuple<int, int, int, int>;  // row, pad, nx, ny
@@ -102,8 +103,8 @@ int hip_fail(zk_batch *b, hipError_t e, const char *what) {
 
 bool is_row(int kind) { return kind == L_ROW_PAD || kind == L_ROW_BASE; }
 
-const void *kernel_for(const zk_batch *b, bool row, int T, int E, bool pad) {
-  return find_kernel(row, b->precision == 64, KF_PLAIN, T, E, pad);
+const void *kernel_for(const zk_batch *b, bool row, int T, int E, bool pad, bool early = false) {
+  return find_kernel(row, b->precision == 64, early ? KF_EARLY : KF_PLAIN, T, E, pad);
 }
 
 // Candidate team shapes of a transform of an axis of n points (radix_candidates),
@@ -166,13 +167,16 @@ void merge(zk_batch *b, const std::vector<std::vector<Launch>> &seqs, std::vecto
       const bool pad = std::get<1>(kv.first);
       const int nx = std::get<2>(kv.first), ny = std::get<3>(kv.first);
       const auto sh = shape_of(b, row, pad, nx, ny);
-      BL bl{row, pad, nx, ny, sh.first, sh.second, blocks_of(row, pad, nx, ny, sh.first), (int)b->items.size(), 0};
+      BL bl{row, pad, nx, ny, sh.first, sh.second, blocks_of(row, pad, nx, ny, sh.first), (int)b->items.size(), 0, 0};
       for (auto &tl : kv.second)
         for (int k = tl.second->first; k < tl.second->first + tl.second->count; ++k)
           b->items.push_back(BatchItem{2 * tl.first + (pad ? 0 : 1), k});
       bl.nitems = (int)b->items.size() - bl.item0;
       ph.push_back(bl);
     }
+    long long blocks = 0;
+    for (const BL &l : ph) blocks += (long long)l.blocks * l.nitems;
+    for (BL &l : ph) l.phase_blocks = blocks;
     // larger tiles first: their blocks start early
     std::sort(ph.begin(), ph.end(), [](const BL &x, const BL &y) { return x.nx * x.ny > y.nx * y.ny; });
     out.push_back(std::move(ph));
@@ -180,7 +184,8 @@ void merge(zk_batch *b, const std::vector<std::vector<Launch>> &seqs, std::vecto
 }
 
 void kernel_params(const zk_batch *b, const BL &l, const void **fn, void **args_dev, BatchItem **items_dev) {
-  *fn = kernel_for(b, l.row, l.T, l.E, l.pad);
+  *fn = kernel_for(b, l.row, l.T, l.E, l.pad,
+                   l.row && early_row_launch(b->precision == 64, l.T, l.E, l.pad, l.phase_blocks));
   *args_dev = b->ws + (l.row ? b->off_rargs : b->off_cargs);
   *items_dev = reinterpret_cast<BatchItem *>(b->ws + b->off_items) + l.item0;
 }

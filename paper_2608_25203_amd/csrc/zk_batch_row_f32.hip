@@ -6,23 +6,23 @@ namespace zk {
 
 extern const KernelEntry row_f32_0[];
 const KernelEntry row_f32_0[] = {
-    {2, 6, true, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<float, 2, 6, true>)},
-    {4, 15, true, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<float, 4, 15, true>)},
-    {8, 3, true, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<float, 8, 3, true>)},
-    {16, 6, false, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<float, 16, 6, false>)},
-    {16, 9, true, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<float, 16, 9, true>)},
-    {32, 2, false, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<float, 32, 2, false>)},
-    {32, 4, false, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<float, 32, 4, false>)},
-    {32, 10, false, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<float, 32, 10, false>)},
-    {64, 6, true, KF_LANES, reinterpret_cast<const void *>(&row_kernel_batch<float, 64, 6, true, true>)},
-    {64, 6, true, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<float, 64, 6, true>)},
-    {128, 6, true, KF_LANES, reinterpret_cast<const void *>(&row_kernel_batch<float, 128, 6, true, true>)},
+    {2, 2, false, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<float, 2, 2, false>)},
+    {2, 3, true, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<float, 2, 3, true>)},
+    {2, 6, false, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<float, 2, 6, false>)},
+    {2, 9, true, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<float, 2, 9, true>)},
+    {2, 15, true, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<float, 2, 15, true>)},
+    {8, 4, false, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<float, 8, 4, false>)},
+    {8, 6, true, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<float, 8, 6, true>)},
+    {8, 10, false, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<float, 8, 10, false>)},
+    {16, 3, true, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<float, 16, 3, true>)},
+    {64, 2, false, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<float, 64, 2, false>)},
+    {64, 6, false, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<float, 64, 6, false>)},
+    {64, 9, true, KF_LANES, reinterpret_cast<const void *>(&row_kernel_batch<float, 64, 9, true, true>)},
+    {64, 9, true, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<float, 64, 9, true>)},
     {128, 6, true, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<float, 128, 6, true>)},
-    {128, 15, true, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<float, 128, 15, true>)},
-    {256, 6, true, KF_LANES, reinterpret_cast<const void *>(&row_kernel_batch<float, 256, 6, true, true>)},
-    {256, 9, true, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<float, 256, 9, true>)},
-    {512, 2, false, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<float, 512, 2, false>)},
-    {512, 6, true, KF_LANES, reinterpret_cast<const void *>(&row_kernel_batch<float, 512, 6, true, true>)},
+    {128, 9, true, KF_LANES, reinterpret_cast<const void *>(&row_kernel_batch<float, 128, 9, true, true>)},
+    {256, 6, false, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<float, 256, 6, false>)},
+    {256, 9, true, KF_LANES, reinterpret_cast<const void *>(&row_kernel_batch<float, 256, 9, true, true>)},
     {1024, 3, true, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<float, 1024, 3, true>)},
     {0, 0, false, 0, nullptr}};
 

@@ -7,21 +7,21 @@ namespace zk {
 extern const KernelEntry row_f64_0[];
 const KernelEntry row_f64_0[] = {
     {2, 2, false, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<double, 2, 2, false>)},
-    {2, 6, true, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<double, 2, 6, true>)},
-    {2, 10, false, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<double, 2, 10, false>)},
-    {8, 3, true, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<double, 8, 3, true>)},
-    {32, 6, false, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<double, 32, 6, false>)},
+    {4, 3, true, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<double, 4, 3, true>)},
+    {4, 6, true, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<double, 4, 6, true>)},
+    {16, 3, true, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<double, 16, 3, true>)},
+    {32, 10, false, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<double, 32, 10, false>)},
     {48, 2, false, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<double, 48, 2, false>)},
-    {64, 12, true, KF_LANES, reinterpret_cast<const void *>(&row_kernel_batch<double, 64, 12, true, true>)},
-    {80, 3, true, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<double, 80, 3, true>)},
-    {128, 6, false, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<double, 128, 6, false>)},
-    {128, 15, true, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<double, 128, 15, true>)},
+    {48, 3, true, KF_EARLY, reinterpret_cast<const void *>(&row_kernel_batch<double, 48, 3, true, false, true>)},
+    {64, 4, false, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<double, 64, 4, false>)},
+    {64, 6, false, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<double, 64, 6, false>)},
+    {64, 8, false, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<double, 64, 8, false>)},
+    {64, 9, true, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<double, 64, 9, true>)},
+    {96, 3, true, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<double, 96, 3, true>)},
+    {128, 12, true, KF_LANES, reinterpret_cast<const void *>(&row_kernel_batch<double, 128, 12, true, true>)},
     {256, 2, false, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<double, 256, 2, false>)},
-    {256, 6, true, KF_LANES, reinterpret_cast<const void *>(&row_kernel_batch<double, 256, 6, true, true>)},
     {256, 6, true, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<double, 256, 6, true>)},
-    {256, 12, true, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<double, 256, 12, true>)},
     {512, 6, true, KF_LANES, reinterpret_cast<const void *>(&row_kernel_batch<double, 512, 6, true, true>)},
-    {1024, 2, false, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<double, 1024, 2, false>)},
     {1024, 3, true, KF_PLAIN, reinterpret_cast<const void *>(&row_kernel_batch<double, 1024, 3, true>)},
     {0, 0, false, 0, nullptr}};
 

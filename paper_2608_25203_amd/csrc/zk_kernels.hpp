@@ -279,6 +279,16 @@ __host__ __device__ constexpr bool row_compiled_shapes(int T, int E, bool padded
   return padded && ((E == 3 && T >= 16) || (E == 6 && T >= 128 && T <= 512));
 }
 
+// Shapes whose compiled programs also have an EARLY form: a launch of few such
+// rows leaves most of the chip idle, so a block's own latencies are its time.
+// Launches that fill the chip keep the plain form, which has a wavefront a SIMD
+// more (118 to 128 registers against 130 to 146): early_row_launch has the line.
+// Teams above these sizes would lose a wavefront in ordinary grids already (512
+// points: 21.9 to 22.9 us a launch).
+__host__ __device__ constexpr bool early_row_shape(bool f64, int T, int E, bool padded) {
+  return E == 3 && row_compiled_shapes(T, E, padded) && T <= (f64 ? 128 : 32);
+}
+
 template <int T, int E, int BSZ = 0, bool PAD = (E % 3 == 0)>
 struct Shape {
   static constexpr bool PADDED = PAD;
@@ -422,8 +432,9 @@ struct BatchItem {
 // Row pass body: TPB teams per block, one row each (block blk of the
 // pass), all running program progs[prog].
 // LANES: run the transforms in the permuted layout (only for a shape whose
-// lanes_ok() holds).
-template <typename real, int T, int E, bool DYN = false, int BSZ = 0, bool PAD = (E % 3 == 0), bool LANES = false>
+// lanes_ok() holds).  EARLY: see early_row_shape().
+template <typename real, int T, int E, bool DYN = false, int BSZ = 0, bool PAD = (E % 3 == 0), bool LANES = false,
+          bool EARLY = false>
 __device__ __forceinline__ void row_body(const RowArgs<real> &a, int prog, int blk, const RowProg *progs0) {
   using S = Shape<T, E, BSZ, PAD>;
   constexpr int N = S::N, L = S::L, NB = S::template nbuf<real, LANES>();
@@ -706,15 +717,9 @@ __device__ __forceinline__ void row_body(const RowArgs<real> &a, int prog, int b
           constexpr bool BLOCK_MAXIMA = NC >= kBlockMaximaCols;
           constexpr int NW = S::BS / 64;
           const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-          // Small teams (rows of up to 256 points, FP32 64): a grid of such rows
-          // leaves most of the chip idle, so a block's own latencies are the
-          // launch's time: every op record is read up front, and each LD2's data
-          // and maxima are requested before the transform of the LD2 before it
-          // (RK4 steps: 371 to 361 us at 256^2, 355 to 333 at 192^2, M = 4, FP64).
-          // Larger teams have other blocks to fill the gaps and would lose one
-          // of them to the registers (512 points: 21.9 to 22.9 us a launch), as
-          // would FP32's of 64 and 128 threads in a batch of tiles.
-          constexpr bool EARLY = T <= (sizeof(real) == 8 ? 128 : 32);
+          // EARLY (small launches of small teams, early_row_shape): every op
+          // record is read up front, and each LD2's data and maxima are requested
+          // before the transform of the LD2 before it.
           constexpr int LEN = kRowShapeLen[SH];
           RowOp rec[EARLY ? LEN : 1];
           Ld2Regs xa, xb;
@@ -1358,13 +1363,16 @@ __device__ __forceinline__ BatchItem item_of(const BatchItem *items, int tile0, 
 // Those with a radix-9 first pass of up to 64 threads to 168, three wavefronts,
 // without a spill: left alone they take 170 to 173 (batch of twelve 384^2 tiles,
 // M = 3, two steps: 4.41 and 3.86 ms; forty of 96^2 1.29 and 1.14).
-constexpr int row_min_waves(bool f32, int T, int E, bool pad, bool lanes) {
-  if (!f32 || lanes) return 1;
+// FP64 plain rows of 160 points to 128, four wavefronts (131 left alone; batch of
+// 24 160^2 tiles 2.17 and 1.97 ms).
+constexpr int row_min_waves(bool f32, int T, int E, bool pad, bool lanes, bool early) {
+  if (lanes || early) return 1;
+  if (!f32) return T == 80 && E == 3 ? 4 : 1;
   return T == 1024 && E == 3 && pad ? 8 : E == 9 && T <= 64 ? 3 : E == 15 ? 2 : 1;
 }
-template <typename real, int T, int E, bool PAD = (E % 3 == 0), bool LANES = false>
+template <typename real, int T, int E, bool PAD = (E % 3 == 0), bool LANES = false, bool EARLY = false>
 __global__ __launch_bounds__(block_threads(T))
-__attribute__((amdgpu_waves_per_eu(row_min_waves(sizeof(real) == 4, T, E, PAD, LANES), 8))) void row_kernel_batch(const RowArgs<real> *__restrict__ args,
+__attribute__((amdgpu_waves_per_eu(row_min_waves(sizeof(real) == 4, T, E, PAD, LANES, EARLY), 8))) void row_kernel_batch(const RowArgs<real> *__restrict__ args,
                                                         const BatchItem *__restrict__ items, int tile0, int first0,
                                                         const void *sched0, PhysArgs ph) {
   const BatchItem it = item_of(items, tile0, first0);
@@ -1376,7 +1384,7 @@ __attribute__((amdgpu_waves_per_eu(row_min_waves(sizeof(real) == 4, T, E, PAD, L
     a.pout0 = ph.out0;
     a.pout1 = ph.out1;
   }
-  row_body<real, T, E, false, 0, PAD, LANES>(a, it.index, blockIdx.x, static_cast<const RowProg *>(sched0));
+  row_body<real, T, E, false, 0, PAD, LANES, EARLY>(a, it.index, blockIdx.x, static_cast<const RowProg *>(sched0));
 }
 // LIFTSYM: the variant that applies ColOut.lift_sym (the bulk velocity
 // lift's column launches, which get their layers' depths as an argument); the
@@ -1484,7 +1492,8 @@ enum KernelForm : int {
   KF_PLAIN = 0,
   KF_LANES = 1,    // padded row passes in the permuted-layout form (row_lanes_ok)
   KF_LIFTSYM = 2,  // base-length column passes with the depth lift's factors
-  KF_FOLDS = 3     // padded column passes with fold teams (fold_team_shape)
+  KF_FOLDS = 3,    // padded column passes with fold teams (fold_team_shape)
+  KF_EARLY = 4     // padded row passes of few rows, loads ahead (early_row_shape)
 };
 struct KernelEntry {
   int T, E;
@@ -1497,6 +1506,17 @@ extern const KernelEntry *const row_kernels_f64[], *const row_kernels_f32[], *co
     *const col_kernels_f32[];
 // The kernel of a team shape and form, or nullptr if it is not built.
 const void *find_kernel(bool row, bool f64, int form, int T, int E, bool pad);
+// Blocks up to which row launches that run side by side take the EARLY form: three
+// a CU, what is resident at once.  RK4 steps plain and EARLY (FP64): 1255 and 1201
+// us at 256 x 64, 1097 and 1078 at 64^2, 1516 and 1467 at 256^2, 1406 and 1360 at
+// 128 x 512 (M = 4, four steps); 768 blocks 1800 and 1791 at 256 x 512, 1749 and
+// 1727 at 160 x 512, but 1735 and 1754 at 64 x 2048; past it 2056 and 2064 at 128 x
+// 2048, 1839 and 1874 at 256 x 1024, 3096 and 3253 at 192 x 2048 (M = 3), batches of
+// sixteen 256^2 tiles 2.60 and 2.75 ms, 192^2 1.90 and 2.02 (two steps).
+constexpr int kEarlyBlocks = 768;
+inline bool early_row_launch(bool f64, int T, int E, bool padded, long long blocks) {
+  return early_row_shape(f64, T, E, padded) && blocks <= kEarlyBlocks;
+}
 // The first-pass radix of an axis's power-of-two team, the smallest compiled:
 // what a context reports before zk_bind, and FP32 transforms' default (another
 // shape rounds differently, by 1e-7 in FP32; the autotuner may choose one).

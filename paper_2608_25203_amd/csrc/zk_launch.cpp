@@ -8,7 +8,7 @@ namespace zk {
 
 const void *find_kernel(bool row, bool f64, int form, int T, int E, bool pad) {
   auto key = [](int r, int d, int f, int t, int e, int p) {
-    return (uint32_t)(((((t * 16 + e) * 4 + f) * 2 + p) * 2 + d) * 2 + r);
+    return (uint32_t)(((((t * 16 + e) * 8 + f) * 2 + p) * 2 + d) * 2 + r);
   };
   static const std::unordered_map<uint32_t, const void *> table = [&] {
     std::unordered_map<uint32_t, const void *> m;

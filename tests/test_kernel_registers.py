@@ -69,4 +69,15 @@ def waves(registers):
 @pytest.mark.parametrize("T", [16, 32, 64])
 def test_fp32_radix9_rows_keep_three_wavefronts(kernels, T):
     """Rows of 96, 192 and 384 points: in a batch of tiles their launches fill the chip."""
-    assert waves(kernels[("row_kernel_batch", "f", T, 9, 1, 0)][0]) >= 3
+    assert waves(kernels[("row_kernel_batch", "f", T, 9, 1, 0, 0)][0]) >= 3
+
+
+@pytest.mark.parametrize("T", [16, 32, 64, 128, 24, 40, 48, 80, 96])
+def test_fp64_small_team_rows_keep_four_wavefronts(kernels, T):
+    """The plain form, which launches that fill the chip take."""
+    assert waves(kernels[("row_kernel_batch", "d", T, 3, 1, 0, 0)][0]) >= 4
+
+
+@pytest.mark.parametrize("T", [16, 32])
+def test_fp32_small_team_rows_keep_six_wavefronts(kernels, T):
+    assert waves(kernels[("row_kernel_batch", "f", T, 3, 1, 0, 0)][0]) >= 6
