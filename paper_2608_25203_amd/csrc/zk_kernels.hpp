@@ -943,13 +943,13 @@ __device__ __forceinline__ LayerFactors layer_factors(double kk, int col, int b,
 // the host in FP64: |k|, G0 = |k| tanh(|k| d) and the taper, per band element
 // (same tiled layout as a base spectrum); the state filter is separable,
 // A = Ax(kx) Ay(b).
-// fl: the filter's value (read where s has SYM_FILT), fi: the loaded SYM_IF
-// coefficient.
+// fl(), fi(): the filter's value and the SYM_IF coefficient, asked for where s has
+// their bits.
 __device__ __forceinline__ double if_coef(const double *ifsym, uint32_t s, int col, int b, int ny) {
   return gload1(ifsym, (long long)base_index(col, b, ny) * kIfCoefs + ((s >> SYM_IF_SHIFT) & 7));
 }
-template <typename real>
-__device__ __forceinline__ cpx<double> symval(uint32_t s, double kk, double g0, double tp, double fl, double fi,
+template <typename real, typename Filt, typename IfCoef>
+__device__ __forceinline__ cpx<double> symval(uint32_t s, double kk, double g0, double tp, Filt fl, IfCoef fi,
                                               double ky, const ColArgs<real> &a) {
   double f = 1.0;
   const int l = s & SYM_LMASK;
@@ -957,9 +957,9 @@ __device__ __forceinline__ cpx<double> symval(uint32_t s, double kk, double g0, 
     f = (l & 1) ? g0 : kk;
     for (int i = 1; i < l; ++i) f *= kk;
   }
-  if (s & SYM_FILT) f *= fl;
+  if (s & SYM_FILT) f *= fl();
   if ((s & SYM_TAPER) && a.taper_on) f *= tp;
-  if (s & SYM_IF) f *= fi;
+  if (s & SYM_IF) f *= fi();
   if (s & SYM_INVG0) f = g0 > 0.0 ? f / g0 : 0.0;
   if (s & SYM_IKY) return {0.0, f * ky};
   return {f, 0.0};
@@ -1070,7 +1070,7 @@ __device__ __forceinline__ void col_body(const ColArgs<real> &a, int task_index,
     sg0[q] = a.depth > 0.0 ? gload1(a.sym_g0, e) : skk[q];
     stp[q] = need_tp ? gload1(a.sym_tp, e) : 1.0;
   }
-  auto sym = [&](uint32_t s, int q, double fl, double fi) -> cpx<double> {
+  auto sym = [&](uint32_t s, int q, auto fl, auto fi) -> cpx<double> {
     return symval(s, skk[q], sg0[q], stp[q], fl, fi, a.ky_scale * my_of(q), a);
   };
 
@@ -1107,7 +1107,8 @@ __device__ __forceinline__ void col_body(const ColArgs<real> &a, int task_index,
 #pragma unroll
     for (int q = 0; q < QB; ++q) {
       const cpx<real> w = get(base_slot(q));
-      const cpx<double> sv = sym(fsym, q, 1.0, 1.0);  // folds carry neither factor
+      auto one = [] { return 1.0; };  // folds carry neither factor
+      const cpx<double> sv = sym(fsym, q, one, one);
       const cpx<double> x = {(double)w.x * fcoef, (double)w.y * fcoef};
       X[q].x += x.x * sv.x - x.y * sv.y;
       X[q].y += x.x * sv.y + x.y * sv.x;
@@ -1135,15 +1136,36 @@ __device__ __forceinline__ void col_body(const ColArgs<real> &a, int task_index,
     cpx<real> xn[HL::IT][HL::R];
     auto load_fold = [&](int f) { load_col(a.mix + (long long)task.fwd[f] * a.mix_stride, xn); };
     if (task.fwd[0] >= 0) load_fold(0);
-    for (int f = 0; f < kMaxFolds; ++f) {
-      if (task.fwd[f] < 0) break;
-      cpx<real> x[HL::IT][HL::R];
+    // FP32: unrolled by order, which keeps the task record, indexed by f, out of
+    // scratch (the compiler leaves the loops of radix-9 and -15 columns rolled;
+    // column launches of two RK4 steps, M = 3: 466 to 446 us in all on 160 x 192,
+    // 881 to 732 on 512 x 320).  FP64 is left to it.
+    if constexpr (sizeof(real) == 4) {
+      bool more = true;
+      static_for<0, kMaxFolds>([&](auto fc) {
+        constexpr int f = decltype(fc)::value;
+        more = more && task.fwd[f] >= 0;
+        if (!more) return;
+        cpx<real> x[HL::IT][HL::R];
 #pragma unroll
-      for (int it = 0; it < HL::IT; ++it)
+        for (int it = 0; it < HL::IT; ++it)
 #pragma unroll
-        for (int r = 0; r < HL::R; ++r) x[it][r] = xn[it][r];
-      if (f + 1 < kMaxFolds && task.fwd[f + 1] >= 0) load_fold(f + 1);
-      transform_fold(x, task.fwd_sym[f], task.fwd_coef[f], true);
+          for (int r = 0; r < HL::R; ++r) x[it][r] = xn[it][r];
+        if constexpr (f + 1 < kMaxFolds)
+          if (task.fwd[f + 1] >= 0) load_fold(f + 1);
+        transform_fold(x, task.fwd_sym[f], task.fwd_coef[f], true);
+      });
+    } else {
+      for (int f = 0; f < kMaxFolds; ++f) {
+        if (task.fwd[f] < 0) break;
+        cpx<real> x[HL::IT][HL::R];
+#pragma unroll
+        for (int it = 0; it < HL::IT; ++it)
+#pragma unroll
+          for (int r = 0; r < HL::R; ++r) x[it][r] = xn[it][r];
+        if (f + 1 < kMaxFolds && task.fwd[f + 1] >= 0) load_fold(f + 1);
+        transform_fold(x, task.fwd_sym[f], task.fwd_coef[f], true);
+      }
     }
   } else if (task.fwd[0] >= 0) {
     // Team f folds field f (a team without one transforms zeros); the parts
@@ -1185,8 +1207,13 @@ __device__ __forceinline__ void col_body(const ColArgs<real> &a, int task_index,
   // teams: team f sums terms f, f + FT, ... (a third of the chain of
   // base-spectrum loads each), the parts are summed through LDS in team
   // order, and every team then holds the combination; team 0 stores it.
-  // An output marked keep leaves its stored combination in X (base spectrum
-  // `kept`), for the task's later lifts of it.
+  // An output marked keep is read again by the task's later lifts.  FP64 leaves
+  // its combination in X (base spectrum `kept`); FP32 lets each lane read back
+  // what it stored (no other does: the plan validation holds tasks to their own
+  // spectra), as code for a kept X costs every launch registers and time that a
+  // step's one launch with a kept output does not win (with the factors' LATE
+  // loads below, the same column launches: 446 to 421 and 732 to 690 us).
+  constexpr bool HOLD = sizeof(real) == 8 && FT == 1 && !LIFTSYM;
   int kept = -1;
   // Depth lift: the factors of the task's layer, formed once for its three
   // outputs (512^2, 8 layers: 42 us a launch when each output formed
@@ -1220,7 +1247,7 @@ __device__ __forceinline__ void col_body(const ColArgs<real> &a, int task_index,
     double nfi[QB];
     ColTerm ntm = first < out.nt ? uniform_load(a.terms + out.t0 + first) : ColTerm{};
     auto fetch = [&](const ColTerm &tm2) {
-      if (tm2.src >= 0 && (LIFTSYM || tm2.src != kept)) {
+      if (tm2.src >= 0 && !(HOLD && tm2.src == kept)) {
         const cpx<double> *B = a.base + (long long)tm2.src * a.base_stride;
 #pragma unroll
         for (int q = 0; q < QB; ++q) nxt[q] = gload(B, base_index(col, t + T * q, ny));
@@ -1244,20 +1271,38 @@ __device__ __forceinline__ void col_body(const ColArgs<real> &a, int task_index,
         ntm = uniform_load(a.terms + out.t0 + i + step);
         fetch(ntm);
       }
-      if (tm.src < 0 || (!LIFTSYM && tm.src == kept)) {
+      // FP32 asks for a term's factors where they are multiplied in.
+      constexpr bool LATE = sizeof(real) == 4 && !LIFTSYM;
+      auto add = [&](const cpx<double> (&s)[QB]) {
 #pragma unroll
-        for (int q = 0; q < QB; ++q) cur[q] = X[q];
-      }
+        for (int q = 0; q < QB; ++q) {
+          auto filt = [&] { return gload1(a.filt_x, col) * gload1(a.filt_y, t + T * q); };
+          auto coef = [&] { return if_coef(a.ifsym, tm.sym, col, t + T * q, ny); };
+          cpx<double> sv;
+          if constexpr (LATE) {
+            sv = sym(tm.sym, q, filt, coef);
+          } else {
+            double fl = 1.0, f = 1.0;
+            if (!LIFTSYM && (tm.sym & SYM_FILT)) fl = filt();
+            if constexpr (IFN) f = fi[q];
+            else if (tm.sym & SYM_IF) f = coef();
+            sv = sym(tm.sym, q, [&] { return fl; }, [&] { return f; });
+          }
+          sv = {sv.x * tm.coef, sv.y * tm.coef};
+          acc[q].x += s[q].x * sv.x - s[q].y * sv.y;
+          acc[q].y += s[q].x * sv.y + s[q].y * sv.x;
+        }
+      };
+      const bool held = tm.src < 0 || (HOLD && tm.src == kept);
+      if constexpr (LATE) {
+        if (held) add(X);
+        else add(cur);
+      } else {
+        if (held) {
 #pragma unroll
-      for (int q = 0; q < QB; ++q) {
-        double fl = 1.0, f = 1.0;
-        if (!LIFTSYM && (tm.sym & SYM_FILT)) fl = gload1(a.filt_x, col) * gload1(a.filt_y, t + T * q);
-        if constexpr (IFN) f = fi[q];
-        else if (tm.sym & SYM_IF) f = if_coef(a.ifsym, tm.sym, col, t + T * q, ny);
-        cpx<double> sv = sym(tm.sym, q, fl, f);
-        sv = {sv.x * tm.coef, sv.y * tm.coef};
-        acc[q].x += cur[q].x * sv.x - cur[q].y * sv.y;
-        acc[q].y += cur[q].x * sv.y + cur[q].y * sv.x;
+          for (int q = 0; q < QB; ++q) cur[q] = X[q];
+        }
+        add(cur);
       }
     }
     if constexpr (FT > 1) {
@@ -1283,7 +1328,7 @@ __device__ __forceinline__ void col_body(const ColArgs<real> &a, int task_index,
 #pragma unroll
       for (int q = 0; q < QB; ++q) gstore(B, base_index(col, t + T * q, ny), acc[q]);
     }
-    if (!LIFTSYM && out.keep) {
+    if (HOLD && out.keep) {
       kept = out.dst_base;
 #pragma unroll
       for (int q = 0; q < QB; ++q) X[q] = acc[q];
@@ -1424,8 +1469,8 @@ __device__ __forceinline__ void col_body_1d(const ColArgs<real> &a, int task_ind
   const bool need_tp = a.taper_on && ((task.fwd_sym[0] | task.fwd_sym[1] | task.fwd_sym[2]) & SYM_TAPER);
   const double g0 = a.depth > 0.0 ? gload1(a.sym_g0, e) : kk, tp = need_tp ? gload1(a.sym_tp, e) : 1.0;
   auto sym = [&](uint32_t s) {
-    const double fl = (s & SYM_FILT) ? gload1(a.filt_x, col) * gload1(a.filt_y, 0) : 1.0;
-    return symval(s, kk, g0, tp, fl, (s & SYM_IF) ? if_coef(a.ifsym, s, col, 0, 1) : 1.0, 0.0, a);
+    return symval(s, kk, g0, tp, [&] { return gload1(a.filt_x, col) * gload1(a.filt_y, 0); },
+                  [&] { return if_coef(a.ifsym, s, col, 0, 1); }, 0.0, a);
   };
   auto cmac = [](cpx<double> &acc, cpx<double> x, cpx<double> sv) {
     acc.x += x.x * sv.x - x.y * sv.y;

@@ -1085,6 +1085,8 @@ std::string validate_plan(const Plan &p, int rows_pad, int rows_base) {
             } else if (o.keep) {
               return "kept output without a store";
             }
+            // a fold team stores for all: the others could not read it back
+            if (o.keep && l.d2 == kMaxFolds) return "kept output in a fold team launch";
           }
         }
       } else if (l.kind == L_PARSEVAL) {

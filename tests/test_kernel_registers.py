@@ -81,3 +81,9 @@ def test_fp64_small_team_rows_keep_four_wavefronts(kernels, T):
 @pytest.mark.parametrize("T", [16, 32])
 def test_fp32_small_team_rows_keep_six_wavefronts(kernels, T):
     assert waves(kernels[("row_kernel_batch", "f", T, 3, 1, 0, 0)][0]) >= 6
+
+
+@pytest.mark.parametrize("T,E", [(16, 9), (32, 9), (64, 9), (16, 15), (32, 15), (64, 15)])
+def test_fp32_columns_with_a_factor_3_or_5_use_no_scratch(kernels, T, E):
+    """Padded columns of 96 to 384 and 160 to 640 points: the task record stays in registers."""
+    assert kernels[("col_kernel_batch", "f", T, E, 0, 1)][1] == 0
