@@ -431,7 +431,7 @@ TeamShape ctx_team(const zk_ctx *c, bool row, bool pad) {
     sh.blocks = (c->pp.nx / 2 + 255) / 256;
     return sh;
   }
-  sh.T = c->tuneT[row][pad] ? c->tuneT[row][pad] : N / (c->bound ? default_radix(c->precision == 64, row, n, pad) : pow2_team_radix(n, pad));
+  sh.T = c->tuneT[row][pad] ? c->tuneT[row][pad] : N / (c->bound ? default_radix(c->precision == 64, row, n, pad, c->pp.ny) : pow2_team_radix(n, pad));
   sh.E = N / sh.T;
   const int tpb = block_threads(sh.T) / team_slot(sh.T);
   // (rows of a 1D grid: 1, in a block whose other teams idle)

@@ -128,8 +128,13 @@ std::pair<int, int> shape_of(zk_batch *b, bool row, bool pad, int nx, int ny) {
   const Key k{row, pad, nx, ny};
   auto it = b->tune.find(k);
   if (it != b->tune.end()) return it->second;
-  // default: the smallest first-pass radix (which the persistent kernel hosts too)
-  const int n = row ? nx : ny, E = b->precision == 64 ? (pad ? 3 : 2) : pow2_team_radix(n, pad);
+  // default: a context's, or on axes of 2^k points the smallest first-pass radix,
+  // which the persistent kernel hosts too
+  const int n = row ? nx : ny;
+  long long lines = 0;
+  for (const zk_ctx *c : b->tiles)
+    if (c->pp.nx == nx) lines += c->pp.ny;
+  const int E = n & (n - 1) ? default_radix(b->precision == 64, row, n, pad, lines) : (pad ? 3 : 2);
   return {(pad ? 3 * n / 2 : n) / E, E};
 }
 

@@ -1574,19 +1574,28 @@ inline int pow2_team_radix(int n, bool pad) {
 // - on axes with a factor 3 or 5 the power-of-two team of one radix-9 or
 //   radix-15 step keeps too few wavefronts busy: 30 and 37 against 17.8 and
 //   14.3 on 384 x 320 (M = 5), 416 and 198 against 354 and 167 on 1536^2 (M =
-//   4), 19 and 17 against 11 and 11 on 48^2 (M = 3); only rows of 640 and 768
-//   come out even or the other way (640^2, M = 4: rows 53 against 63, columns
-//   45 against 31), which the autotuner settles;
+//   4), 19 and 17 against 11 and 11 on 48^2 (M = 3);
+// - but padded rows of 640 and 768 points do keep it once there are enough of
+//   them (`lines`, the grid's ny or a batch's sum): at ny = 128 a launch takes 34
+//   and 26 with it, 18 and 21 with n / 2 threads, at ny = 320 and 384 35 and 53 (33
+//   and 48), from 512 and 1024 on less (640: 46 and 47 at 512, 48 and 61 at 640, 77
+//   and 89 at 1024, 91 and 112 at 1280; 768: 98 and 106 at 1024, 150 and 162 at
+//   1536, M = 3; batches of six 768 x 256 tiles, two steps, 4.88 and 5.11 ms, of
+//   eight 640 x 128 2.69 and 2.85, of four 640^2 6.58 and 7.77); 1280 points do not
+//   (101 and 96 on 1280 x 640);
 // - rows of 1024 and 2048 points run E = 6 teams of half the threads, whose
-//   passes are 6, 8, ... instead of 3, 4, ...: 82 to 79 and 471 to 448 (at 512
-//   points E = 6 takes 26 against 21);
+//   passes are 6, 8, ... instead of 3, 4, ...: 82 to 79 and 471 to 448, and no
+//   slower with few rows (M = 3, E = 3 and 6: one row 15.6 and 15.0, 21.9 and 21.2; 16
+//   rows 16.3 and 15.6, 23.5 and 22.3; at 512 points E = 6 takes 26 against 21);
 // - base rows of 256 and 1024 points run E = 4, one pass fewer (4, 4, 4, 4 and
-//   4, 4, 4, 4, 4 against 2, 4, 4, 4, 2 and 2, 4, 4, 4, 4, 2): depth lifts of 20
-//   layers on 1024 x 512 363 to 338, on 1024 x 320 275 to 268, of 32 on 256^2
-//   141 to 138; lengths whose pass count it leaves or raises lose (E = 2 and 4 on
-//   512^2 280 and 288, 128^2 96 and 103, 2048 x 256 415 and 418).
-inline int default_radix(bool f64, bool row, int n, bool pad) {
-  if (!f64) return pow2_team_radix(n, pad);
+//   4, 4, 4, 4, 4 against 2, 4, 4, 4, 2 and 2, 4, 4, 4, 4, 2): E = 2 and 4 in depth
+//   lifts of 32 layers, 256 x 2048 709 and 662, 256 x 768 343 and 327, 256 x 320 216
+//   and 214, but 256^2 193 and 196, 256 x 64 154 and 157; 1024 x 512 583 and 526, 1024 x
+//   256 372 and 334, 1024 x 16 even.  Of 20 layers 64 x 1024 133 and 137, 64^2 90 and
+//   94: such short rows lose by it, and so do lengths whose pass count it leaves or
+//   raises (512^2 280 and 288, 128^2 96 and 103, 2048 x 256 415 and 418).
+inline int default_radix(bool f64, bool row, int n, bool pad, long long lines) {
+  if (!f64 || (row && pad && ((n == 640 && lines >= 512) || (n == 768 && lines >= 1024)))) return pow2_team_radix(n, pad);
   if (row && pad && n >= 1024 && (n & (n - 1)) == 0) return 6;
   return pad ? 3 : row && (n == 256 || n == 1024) ? 4 : 2;
 }

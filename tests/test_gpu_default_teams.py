@@ -1,0 +1,57 @@
+"""Default padded row teams of 640 and 768 points (FP64): n / 2 threads, or on
+grids and batches of many rows the power-of-two team of one radix-15 or radix-9
+step; both against the oracle."""
+import math
+
+import numpy as np
+import pytest
+
+from oracle.hos import Grid, HOSModel
+from paper_2608_25203_amd.inputs import random_band_fields
+
+pytestmark = pytest.mark.gpu
+TWO_PI = 2 * math.pi
+
+
+def rel(a, b):
+    return float(np.max(np.abs(a - b)) / np.max(np.abs(b)))
+
+
+@pytest.mark.parametrize("nx,ny,T,E", [(640, 384, 320, 3), (640, 512, 64, 15), (768, 768, 384, 3), (768, 1024, 128, 9),
+                                       (1280, 640, 640, 3)])
+def test_default_row_team(nx, ny, T, E):
+    """G psi and the RHS at the bar of test_gpu_parity.py (1e-10)."""
+    import torch
+
+    from paper_2608_25203_amd.zk import Solver
+
+    Lx, Ly = TWO_PI * nx / 128, TWO_PI * ny / 128
+    eta, psi = random_band_fields(nx, ny, 21, 20, amplitude=0.01)
+    s = Solver(nx, ny, Lx, Ly, 0.6, 9.81, 2)
+    assert s.team_shapes()["row_pad"] == (T, E)
+    e, p = torch.from_numpy(eta).cuda(), torch.from_numpy(psi).cuda()
+    m = HOSModel(Grid(nx, ny, Lx, Ly, 0.6), 2)
+    assert rel(s.dtn(e, p).cpu().numpy(), m.dtn(eta, psi)) < 1e-10
+    for a, b in zip(s.rhs(e, p), m.rhs(eta, psi)):
+        assert rel(a.cpu().numpy(), b) < 1e-10
+
+
+@pytest.mark.parametrize("nx,ny,n", [(640, 20, 2), (640, 32, 16), (768, 48, 24)])
+def test_batch_of_many_rows_matches_single_grids(nx, ny, n):
+    """The bar of test_gpu_batch.py (1e-12)."""
+    import torch
+
+    from paper_2608_25203_amd.zk import Batch, Solver
+
+    Lx, Ly = TWO_PI * nx / 128, TWO_PI * ny / 128
+    eta, psi = random_band_fields(nx, ny, 22, 7, amplitude=0.01)
+    b = Batch([dict(nx=nx, ny=ny, Lx=Lx, Ly=Ly, depth=0.6, M=3)] * n, g=9.81, precision=64)
+    es, ps = ([torch.from_numpy(x.copy()).cuda() for _ in range(n)] for x in (eta, psi))
+    b.set_fields(es, ps)
+    b.step(0.002, 2)
+    s = Solver(nx, ny, Lx, Ly, 0.6, 9.81, 3)
+    e, p = torch.from_numpy(eta.copy()).cuda(), torch.from_numpy(psi.copy()).cuda()
+    s.step(e, p, 0.002, 2)
+    for x, y in ((es, e), (ps, p)):
+        for k in (0, n - 1):
+            assert float((x[k] - y).abs().max()) < 1e-12 * float(y.abs().max())
