@@ -431,7 +431,14 @@ TeamShape ctx_team(const zk_ctx *c, bool row, bool pad) {
     sh.blocks = (c->pp.nx / 2 + 255) / 256;
     return sh;
   }
-  sh.T = c->tuneT[row][pad] ? c->tuneT[row][pad] : N / (c->bound ? default_radix(c->precision == 64, row, n, pad, c->pp.ny) : pow2_team_radix(n, pad));
+  int E = c->bound ? default_radix(c->precision == 64, row, n, pad, c->pp.ny) : pow2_team_radix(n, pad);
+  // ZK_ROW_FFT_LANES asks for the permuted-layout form: rows of 384, 768 and 1536
+  // points have it at the power-of-two team only
+  if (row && pad && c->row_fft == ZK_ROW_FFT_LANES) {
+    const int rb = c->precision == 32 ? 4 : 8, P = pow2_team_radix(n, pad);
+    if (!row_lanes_ok(N / E, E, true, rb) && row_lanes_ok(N / P, P, true, rb)) E = P;
+  }
+  sh.T = c->tuneT[row][pad] ? c->tuneT[row][pad] : N / E;
   sh.E = N / sh.T;
   const int tpb = block_threads(sh.T) / team_slot(sh.T);
   // (rows of a 1D grid: 1, in a block whose other teams idle)

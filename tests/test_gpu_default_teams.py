@@ -55,3 +55,33 @@ def test_batch_of_many_rows_matches_single_grids(nx, ny, n):
     for x, y in ((es, e), (ps, p)):
         for k in (0, n - 1):
             assert float((x[k] - y).abs().max()) < 1e-12 * float(y.abs().max())
+
+
+@pytest.mark.parametrize("nx,T", [(384, 64), (768, 128), (1536, 256)])
+def test_lanes_option_keeps_its_form_on_axes_with_a_factor_3(nx, T):
+    """ZK_ROW_FFT_LANES without a team set by hand runs the permuted-layout form
+    (the same answer after zk_bind as before it), within 1e-12 of the Stockham
+    form (both round FP64 transforms); 320 points have no such form."""
+    import torch
+
+    from paper_2608_25203_amd import zk
+
+    ny = 32
+    eta, psi = random_band_fields(nx, ny, 23, 10, amplitude=0.01)
+    e, p = torch.from_numpy(eta).cuda(), torch.from_numpy(psi).cuda()
+    c = zk.zk_create(nx, ny, TWO_PI * nx / ny, TWO_PI, 0.6, 9.81, 3)
+    zk.zk_set_option(c, zk.ZK_OPT_ROW_FFT, zk.ZK_ROW_FFT_LANES)
+    before = zk.zk_get_option(c, zk.ZK_OPT_ROW_FFT)
+    zk.zk_destroy(c)
+    s = zk.Solver(nx, ny, TWO_PI * nx / ny, TWO_PI, 0.6, 9.81, 3)
+    assert s.team_shapes()["row_pad"] == (nx // 2, 3)
+    a = s.dtn(e, p)
+    s.set_option(zk.ZK_OPT_ROW_FFT, zk.ZK_ROW_FFT_LANES)
+    assert s.get_option(zk.ZK_OPT_ROW_FFT) == zk.ZK_ROW_FFT_LANES == before
+    assert s.team_shapes()["row_pad"] == (T, 9)
+    b = s.dtn(e, p)
+    assert float((a - b).abs().max()) < 1e-12 * float(a.abs().max())
+    o = zk.Solver(320, ny, TWO_PI, TWO_PI, 0.6, 9.81, 3)
+    o.set_option(zk.ZK_OPT_ROW_FFT, zk.ZK_ROW_FFT_LANES)
+    assert o.get_option(zk.ZK_OPT_ROW_FFT) == zk.ZK_ROW_FFT_STOCKHAM
+    assert o.team_shapes()["row_pad"] == (160, 3)
