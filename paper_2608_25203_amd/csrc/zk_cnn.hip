@@ -453,6 +453,7 @@ __global__ __launch_bounds__(64 * kDwWaves) void dw32_kernel(const uint16_t *__r
       for (int s = 0; s < 4; ++s) rd[s] = *reinterpret_cast<const u16x8 *>(src + (lane + 64 * s) * 8);
     };
     fetch_a(st.y0 - 1);
+    wave_sync();  // the previous strip's reads are done
     put_a(0);
     fetch_a(st.y0);
     put_a(1);
@@ -569,6 +570,7 @@ __global__ __launch_bounds__(64 * kDwWaves) void dw1_kernel(const uint16_t *__re
       for (int s = 0; s < 4; ++s) rd[s] = *reinterpret_cast<const u16x8 *>(src + (lane + 64 * s) * 8);
     };
     fetch_a(st.y0 - 1);
+    wave_sync();  // the previous strip's reads are done
     put_a(0);
     fetch_a(st.y0);
     put_a(1);
