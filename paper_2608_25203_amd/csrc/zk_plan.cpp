@@ -1052,7 +1052,13 @@ std::string validate_plan(const Plan &p, int rows_pad, int rows_base) {
           }
         for (int k = l.first; k < l.first + l.count; ++k)
           for (int i = 0; i < p.tasks[k].no; ++i)
-            if (p.outs[p.tasks[k].o0 + i].lift_sym && l.c2 != 1) return "lift_sym output in a plain column launch";
+            if (const uint32_t ls = p.outs[p.tasks[k].o0 + i].lift_sym) {
+              if (l.c2 != 1) return "lift_sym output in a plain column launch";
+              // the kernels have the two layer factors, each with the coupling taper
+              const uint32_t cs = ls & (SYM_LAYER_C | SYM_LAYER_S);
+              if (!(ls & SYM_COUPLE) || (cs != SYM_LAYER_C && cs != SYM_LAYER_S)) return "lift_sym without its layer factor";
+              if ((int)((ls >> SYM_LAYER_SHIFT) & 15) >= kMaxChunkLayers) return "lift_sym layer";
+            }
         // a stored spectrum belongs to its task: no other task of the launch
         // stores or reads it, and the task itself reads it only as its kept
         // one (held in registers; its memory may be other teams' stores)
