@@ -729,8 +729,8 @@ Plan build_plan(const PlanParams &pp, double dt) {
       seq.push_back(B.col_launch(L_COL_PAD, {tp, te}));
       if (s < 4) seq.push_back(B.col_launch(L_COL_PAD, l0_tasks(ne[s], np[s], true)));
     }
-    P.step_lift[par].push_back(B.col_launch(L_COL_PAD, l0_tasks(bUE[par], bUP[par], true)));
-    if (M == 1) {  // two launches (see above); step_lift of the other parity follows in the same form
+    if (pp.separate_lifts) P.step_lift[par].push_back(B.col_launch(L_COL_PAD, l0_tasks(bUE[par], bUP[par], true)));
+    if (M == 1) {  // two launches (see above)
       P.step_body_lift[par] = seq;
       P.step_body_lift[par].push_back(B.col_launch(L_COL_PAD, l0_tasks(bUE[1 - par], bUP[1 - par], true)));
     }

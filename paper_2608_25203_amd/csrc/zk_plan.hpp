@@ -41,6 +41,7 @@ struct PlanParams {
   double eps;
   bool taper, filt;
   int real_bytes = 8;  // bytes of one real in the transforms (8: FP64, 4: FP32)
+  bool separate_lifts = false;  // also plan step_lift (the plan checker compares it with the fused form)
 };
 
 struct Plan {
@@ -55,8 +56,8 @@ struct Plan {
   std::vector<Launch> dtn, rhs, ham;
   std::vector<Launch> step_entry;     // physical -> spectral state U[0], lifts for stage 1
   std::vector<Launch> step_body[2];   // one RK4 step from U[p] to U[1-p] (no trailing lift)
-  std::vector<Launch> step_lift[2];   // lifts of U[p] for the next step's stage 1
-  std::vector<Launch> step_body_lift[2];  // step_body[p], then step_lift[1-p] (in one launch with its last, M >= 2)
+  std::vector<Launch> step_lift[2];   // lifts of U[p] for the next step's stage 1 (separate_lifts only)
+  std::vector<Launch> step_body_lift[2];  // step_body[p], then those lifts of U[1-p] (in one launch with its last, M >= 2)
   std::vector<Launch> step_exit[2];   // U[p] -> physical
   int chk_e[2], chk_p[2];             // base ids of U[p] (finite check)
   // Pieces for stepping with an externally supplied DtN (learned closure):

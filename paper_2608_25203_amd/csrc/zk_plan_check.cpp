@@ -1,6 +1,6 @@
 // zk_plan_check.cpp -- host-only tool: builds a plan, validates it and dumps it
 // as JSON (used by the CPU tests to check the planner without a GPU).
-//   zk_plan_check nx ny M eps taper filt dt
+//   zk_plan_check nx ny M eps taper filt dt [precision]
 #include <cstdio>
 #include <cstdlib>
 #include <string>
@@ -17,8 +17,8 @@ static void dump_seq(const char *name, const std::vector<Launch> &s, bool last) 
 }
 
 int main(int argc, char **argv) {
-  if (argc != 8) {
-    std::fprintf(stderr, "usage: %s nx ny M eps taper filt dt\n", argv[0]);
+  if (argc != 8 && argc != 9) {
+    std::fprintf(stderr, "usage: %s nx ny M eps taper filt dt [precision]\n", argv[0]);
     return 2;
   }
   PlanParams pp{};
@@ -32,6 +32,8 @@ int main(int argc, char **argv) {
   pp.taper = std::atoi(argv[5]) != 0;
   pp.filt = std::atoi(argv[6]) != 0;
   const double dt = std::atof(argv[7]);
+  pp.real_bytes = argc == 9 && std::atoi(argv[8]) == 32 ? 4 : 8;
+  pp.separate_lifts = true;
   Plan p;
   try {
     p = build_plan(pp, dt);

@@ -32,6 +32,12 @@ int main(int, char **argv) {
     for (auto &l : p.step_body_lift[0])
       if (l.d2 == kMaxFolds)
         for (int k = l.first; k < l.first + l.count; ++k) p.outs[p.tasks[k].o0].keep = p.outs[p.tasks[k].o0].dst_base >= 0;
+  if (!strcmp(what, "step_lift")) {
+    std::printf("%d", (int)p.step_lift[0].size());
+    pp.separate_lifts = true;
+    std::printf(" %d", (int)build_plan(pp, 0.01).step_lift[0].size());
+    return 0;
+  }
   std::printf("%s", validate_plan(p, 3 * pp.ny / 2, pp.ny).c_str());
   return 0;
 }
@@ -53,3 +59,8 @@ def exe(tmp_path_factory):
                                          ("keep in folds", "kept output in a fold team launch")])
 def test_broken_plan_is_refused(exe, what, answer):
     assert subprocess.run([exe, what], check=True, capture_output=True, text=True).stdout == answer
+
+
+def test_separate_lifts_are_planned_for_the_checker_only(exe):
+    """The library's steps lift in their last launch; no call runs step_lift."""
+    assert subprocess.run([exe, "step_lift"], check=True, capture_output=True, text=True).stdout == "0 1"
