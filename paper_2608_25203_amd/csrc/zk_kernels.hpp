@@ -551,6 +551,20 @@ __device__ __forceinline__ void row_body(const RowArgs<real> &a, int prog, int b
         }
       }
   };
+  // element p of the two fields' joint spectrum
+  auto ld2_mix = [&](int p, cpx<real> za, cpx<real> zbr, bool dxa, bool dxb, real sa, real sb) -> cpx<real> {
+    const bool pos = p < S::KR * T, neg = p > S::NEG0 * T;
+    if (pos || neg) {
+      const real kxv = (real)(a.kx_scale * (pos ? p : N - p));
+      if (dxa) za = {-kxv * za.y, kxv * za.x};
+      if (dxb) zbr = {-kxv * zbr.y, kxv * zbr.x};
+      if (neg) {
+        za.y = -za.y;
+        zbr.y = -zbr.y;
+      }
+    }
+    return {za.x * sa - zbr.y * sb, za.y * sa + zbr.x * sb};
+  };
   // ma, mb: the two fields' maxima over all columns; next(): called before the
   // transform, when xa and xb are free again
   auto ld2_transform = [&](const RowOp &op, Ld2Regs &xa, Ld2Regs &xb, float ma, float mb, auto &&next) {
@@ -562,21 +576,8 @@ __device__ __forceinline__ void row_body(const RowArgs<real> &a, int prog, int b
 #pragma unroll
     for (int it = 0; it < HL::IT; ++it)
 #pragma unroll
-      for (int r = 0; r < HL::R; ++r) {
-        const int p = HL::elem(t, it, r);
-        const bool pos = p < S::KR * T, neg = p > S::NEG0 * T;
-        cpx<real> za = xa[it][r], zbr = xb[it][r];
-        if (pos || neg) {
-          const real kxv = (real)(a.kx_scale * (pos ? p : N - p));
-          if (dxa) za = {-kxv * za.y, kxv * za.x};
-          if (dxb) zbr = {-kxv * zbr.y, kxv * zbr.x};
-          if (neg) {
-            za.y = -za.y;
-            zbr.y = -zbr.y;
-          }
-        }
-        x[it][r] = {za.x * sa - zbr.y * sb, za.y * sa + zbr.x * sb};
-      }
+      for (int r = 0; r < HL::R; ++r)
+        x[it][r] = ld2_mix(HL::elem(t, it, r), xa[it][r], xb[it][r], dxa, dxb, sa, sb);
     settle_tw();
     next();
     if constexpr (LANES) {
@@ -624,12 +625,56 @@ __device__ __forceinline__ void row_body(const RowArgs<real> &a, int prog, int b
     maxima_load(op, m);
     maxima_reduce(m, ma, mb);
   };
+  // FP32 rows with a radix-9 or radix-15 first pass (interpreted, so never loaded
+  // ahead) run it as one body: cut in two it costs them four to six registers, the
+  // third wavefront a SIMD of the radix-9 rows (166 and 172; batch of twelve 384^2
+  // tiles, M = 3, two steps: 3.79 and 4.41 ms) and spills in the radix-15 rows (640 x
+  // 768: 34.0 and 34.7 us a launch).  Other rows lose by it (2048 points, FP32: 257
+  // and 303 us; 128-thread radix-15 teams).
+  constexpr bool ONE_BODY = sizeof(real) == 4 && !LANES && (E == 9 || (E == 15 && T <= 64));
   auto do_ld2 = [&](const RowOp &op, auto &&maxima) {
-    Ld2Regs xa, xb;
-    ld2_load(op, xa, xb);
-    float ma = 0.f, mb = 0.f;
-    maxima(op, ma, mb);
-    ld2_transform(op, xa, xb, ma, mb, [] {});
+    if constexpr (ONE_BODY) {
+      const cpx<real> *Fa = a.mix + (long long)op.fa * a.mix_stride;
+      const bool has_b = op.fb >= 0;
+      const cpx<real> *Fb = a.mix + (long long)(has_b ? op.fb : op.fa) * a.mix_stride;
+      const bool dxa = op.fla & FL_DX, dxb = op.flb & FL_DX;
+      Ld2Regs xa, xb;
+#pragma unroll
+      for (int it = 0; it < HL::IT; ++it)
+#pragma unroll
+        for (int r = 0; r < HL::R; ++r) {
+          const int p = HL::elem(t, it, r);
+          const bool pos = p < S::KR * T, neg = p > S::NEG0 * T;
+          xa[it][r] = {(real)0, (real)0};
+          xb[it][r] = {(real)0, (real)0};
+          if (in_row && HL::live(t, it) && (pos || neg)) {
+            const int idx = mix_index<real>(pos ? p : N - p, row, a.rows);
+            xa[it][r] = gload(Fa, idx);
+            if (has_b) xb[it][r] = gload(Fb, idx);
+          }
+        }
+      float ma = 0.f, mb = 0.f;
+      maxima(op, ma, mb);
+      const float2 pa = pow2_scale(ma);
+      const float2 pb = has_b ? pow2_scale(mb) : make_float2(1.f, 1.f);
+      const real sa = (real)pa.x, sb = (real)pb.x;
+#pragma unroll
+      for (int it = 0; it < HL::IT; ++it)
+#pragma unroll
+        for (int r = 0; r < HL::R; ++r)
+          xa[it][r] = ld2_mix(HL::elem(t, it, r), xa[it][r], xb[it][r], dxa, dxb, sa, sb);
+      settle_tw();
+      fft_in<real, N, E, NB, +1, XP>(xa, z, b0, b1, tw, t);
+      const real ia = (real)pa.y, ib = (real)pb.y;
+#pragma unroll
+      for (int e = 0; e < E; ++e) z[e] = {z[e].x * ia, z[e].y * ib};
+    } else {
+      Ld2Regs xa, xb;
+      ld2_load(op, xa, xb);
+      float ma = 0.f, mb = 0.f;
+      maxima(op, ma, mb);
+      ld2_transform(op, xa, xb, ma, mb, [] {});
+    }
   };
   // LDP and STP act on caller fields, whose rows have the base length only.
   auto do_ldp = [&](const RowOp &op) {
@@ -1405,15 +1450,12 @@ __device__ __forceinline__ BatchItem item_of(const BatchItem *items, int tile0, 
 // scratch set-up (512 points 15.7 to 18.1, 1024 points 46.6 to 45.3).
 // FP32 rows with a radix-15 first pass are held to 256 registers, two wavefronts
 // a SIMD: at 261 a launch of 640 x 768 (M = 3) takes 52 us, at 256 33.
-// Those with a radix-9 first pass of up to 64 threads to 168, three wavefronts,
-// without a spill: left alone they take 170 to 173 (batch of twelve 384^2 tiles,
-// M = 3, two steps: 4.41 and 3.86 ms; forty of 96^2 1.29 and 1.14).
 // FP64 plain rows of 160 points to 128, four wavefronts (131 left alone; batch of
 // 24 160^2 tiles 2.17 and 1.97 ms).
 constexpr int row_min_waves(bool f32, int T, int E, bool pad, bool lanes, bool early) {
   if (lanes || early) return 1;
   if (!f32) return T == 80 && E == 3 ? 4 : 1;
-  return T == 1024 && E == 3 && pad ? 8 : E == 9 && T <= 64 ? 3 : E == 15 ? 2 : 1;
+  return T == 1024 && E == 3 && pad ? 8 : E == 15 ? 2 : 1;
 }
 template <typename real, int T, int E, bool PAD = (E % 3 == 0), bool LANES = false, bool EARLY = false>
 __global__ __launch_bounds__(block_threads(T))

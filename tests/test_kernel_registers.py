@@ -87,3 +87,10 @@ def test_fp32_small_team_rows_keep_six_wavefronts(kernels, T):
 def test_fp32_columns_with_a_factor_3_or_5_use_no_scratch(kernels, T, E):
     """Padded columns of 96 to 384 and 160 to 640 points: the task record stays in registers."""
     assert kernels[("col_kernel_batch", "f", T, E, 0, 1)][1] == 0
+
+
+@pytest.mark.parametrize("T", [16, 32, 64])
+def test_fp32_radix15_rows_do_not_spill(kernels, T):
+    """Rows of 160, 320 and 640 points: two wavefronts a SIMD without scratch."""
+    regs, scratch = kernels[("row_kernel_batch", "f", T, 15, 1, 0, 0)]
+    assert waves(regs) >= 2 and scratch == 0
