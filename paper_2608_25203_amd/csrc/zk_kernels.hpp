@@ -222,7 +222,9 @@ __device__ __forceinline__ float2 pow2_scale(float m) {
 // Lanes set aside for a team of T threads: a power of two up to a wavefront,
 // whole wavefronts above.  Where T is less (axes with a factor 3 or 5) the
 // spare lanes shadow the team's last thread: they load, compute and store the
-// same values at the same addresses, so no access needs a guard of its own.
+// same values at the same addresses, so no access needs a guard of its own.  That
+// is safe, also where an update reads what it overwrites, because they sit in that
+// thread's wavefront (shadows_ok) and move with it.
 __host__ __device__ constexpr int team_slot(int T) {
   int s = 1;
   while (s < T && s < 64) s *= 2;
@@ -235,6 +237,7 @@ __host__ __device__ constexpr int block_threads(int T) {
 }
 // Lanes of a team that shares its column with others (fold teams): whole wavefronts.
 __host__ __device__ constexpr int fold_slot(int T) { return (T + 63) / 64 * 64; }
+__host__ __device__ constexpr bool shadows_ok(int T, int slot) { return slot >= T && (slot - 1) / 64 == (T - 1) / 64; }
 
 // Shape constants of a team: T threads, E first-pass elements per thread.
 // E % 3 == 0: a 3/2-padded transform of N = T E = 3n/2 points, whose n/2
@@ -297,6 +300,7 @@ struct Shape {
   static constexpr int NEG0 = PADDED ? 2 * E / 3 : E / 2;  // first negative slot
   static constexpr int QB = PADDED ? 2 * E / 3 : E;    // base-band elements per thread
   static constexpr int TS = team_slot(T);              // lanes per team
+  static_assert(shadows_ok(T, TS), "spare lanes shadow a thread of their own wavefront");
   static constexpr int BS = BSZ ? BSZ : block_threads(T);  // threads per block
   static constexpr int TPB = BS / TS;                  // teams per block
   static constexpr int L = lds_len(N);
@@ -1021,6 +1025,7 @@ __device__ __forceinline__ cpx<double> symval(uint32_t s, double kk, double g0, 
 template <int T, int FT, int BSZ = 0>
 struct ColBlock {
   static constexpr int TS = FT == 1 ? team_slot(T) : fold_slot(T);                  // lanes per team
+  static_assert(shadows_ok(T, TS), "spare lanes shadow a thread of their own wavefront");
   static constexpr int BS = FT == 1 ? (BSZ ? BSZ : block_threads(T)) : FT * TS;  // threads per block
   static constexpr int TPB = FT == 1 ? BS / TS : 1;                                 // columns per block
 };
@@ -1444,7 +1449,7 @@ __device__ __forceinline__ BatchItem item_of(const BatchItem *items, int tile0, 
 }
 // FP32 rows of 1024 threads (2048 points) are held to 64 VGPRs, so that two of
 // their blocks share a CU and one's barriers leave the other's wavefronts to
-// run: 307 to 243 us a launch on 2048^2 (M = 5) with 41 spilled registers, 208
+// run: 307 to 243 us a launch on 2048^2 (M = 5) with 37 spilled registers, 208
 // as the row program stands now (step 21.5 to 17.2 ms for two); the
 // shorter rows, whose blocks are several a CU anyway, lose 2 us a launch to the
 // scratch set-up (512 points 15.7 to 18.1, 1024 points 46.6 to 45.3).
