@@ -77,9 +77,12 @@ enum {
     ZK_OPT_ROW_FFT = 9,   /* form of the padded row passes' transforms:
                              ZK_ROW_FFT_STOCKHAM (default) or ZK_ROW_FFT_LANES;
                              zk_autotune times both at the chosen team shape
-                             and keeps the faster.  Same results to rounding. */
+                             and keeps the faster.  Same results to rounding.
+                             LANES also makes rows of 384, 768 and 1536 points
+                             default to the team shape that has the form.
+                             zk_get_option answers the form that runs.        */
     ZK_OPT_ROW_PROGRAMS = 10, /* 1 (default): padded row passes of the team
-                             shapes that compile them (E = 3 teams of 64 to
+                             shapes that compile them (E = 3 teams of 16 to
                              1024 threads, E = 6 teams of 128 to 512) run each
                              row program whose operation sequence is one of
                              the compiled shapes as straight-line code; other
@@ -261,8 +264,11 @@ int zk_kernel_stats(zk_ctx *ctx, int kind, double *ms, double *bytes, double *fl
 int zk_autotune(zk_ctx *ctx, double dt, int reps);
 
 /* Team shape in use for a pass kind (row != 0: row pass; pad != 0: padded
- * transform).  zk_bind settles the default shapes (by the axis and its length);
- * before it this reports the axis's power-of-two team of the smallest radix. */
+ * transform).  zk_bind settles the default shapes (by the axis, its length and
+ * for some padded rows their number; FP64 and FP32 differ on axes of 3 2^k and 5
+ * 2^k points).  On a context that is not bound no pass has a shape yet: unless
+ * one was chosen by hand, this then names the axis's power-of-two team of the
+ * smallest radix, which both precisions have built. */
 int zk_team_shape(const zk_ctx *ctx, int row, int pad, int *T, int *E);
 
 /* Choose the team shape of a pass kind by hand (the autotuner's setting):
@@ -271,7 +277,8 @@ int zk_team_shape(const zk_ctx *ctx, int row, int pad, int *T, int *E);
  * ZK_EINVAL if T does not divide N into a compiled shape (power-of-two axes:
  * E in {3, 6, 12} padded or {2, 4, 8} base; axes of 3 2^k points: E = 9
  * padded, 6 base; of 5 2^k points: 15 padded, 10 base; in FP64 also 3 padded, 2
- * base on both; and the pair built for the context's precision).  Host only; applies from the next call. */
+ * base on both; and the pair built for the context's precision).  Host only;
+ * applies from the next call. */
 int zk_set_team_shape(zk_ctx *ctx, int row, int pad, int T);
 
 /* Text of the last error on this context ("" if none).  Valid until the next
@@ -396,9 +403,12 @@ const char *zk_closure_last_error(const zk_closure *clo);
  * batched launch per phase and tile size (blockIdx.y runs over the tiles'
  * programs or tasks), and one step's phases are replayed as a HIP graph of
  * kernel nodes.  The team shape of each pass and size (threads per
- * transform and first-pass radix) is the default one (the smallest radix,
- * n / 2 threads) until zk_batch_autotune times the compiled alternatives on the
- * batch itself and keeps the fastest.  Tile sizes follow zk_create's rule.
+ * transform and first-pass radix) is the default one until zk_batch_autotune
+ * times the compiled alternatives on the batch itself and keeps the fastest:
+ * n / 2 threads (the smallest radix), except on axes of 3 2^k and 5 2^k points
+ * in FP32, and in FP64 for padded rows of 640 and 768 points where the batch has
+ * many, which run the power-of-two team (radix 9 or 15 padded, 6 or 10 base).
+ * Tile sizes follow zk_create's rule.
  * ------------------------------------------------------------------------- */
 typedef struct zk_tile {
     int nx, ny;           /* grid points (as zk_create)                     */

@@ -66,12 +66,14 @@ struct Plan {
   std::vector<Launch> ab2_first[2];
   std::vector<Launch> ab2_body[2];
   std::vector<Launch> ab2_first_lift[2], ab2_body_lift[2];  // as step_body_lift
-  // Inverse DNO map (eq:psi_inverse): (eta, v) -> psi; entry seeds psi = G0^{-1} v,
-  // each iteration psi <- psi + G0^{-1} (v - G^[M] psi), exit writes psi.
+  // Inverse DNO map (eq:psi_inverse): (eta, v) -> psi; entry seeds psi = G0^{-1} v
+  // and lifts eta, exit writes psi.  Each iteration: psi <- G0^{-1} (v - (G^[M] - G0)
+  // psi), stored and lifted by one launch (FP64, M >= 2); FP32 and M = 1 plans take
+  // the equal psi + G0^{-1} (v - G^[M] psi) and lift it with a launch of its own.
   std::vector<Launch> inv_entry, inv_iter, inv_exit;
   // Bulk velocity (Alg. ComputeVolumeVelFrom2D): lift_phi stores the tapered
   // first-order potential on the flat plane; depth_chunk[r] (1 <= r <=
-  // depth_chunk_max) lifts r layers, whose depths the column args carry, in
+  // depth_chunk_max) lifts r layers, whose depths the launch's argument carries, in
   // one column and one row launch and writes (u, v, w) of layer i to planes
   // 3i, 3i+1, 3i+2 of output slot 0.
   std::vector<Launch> lift_phi;
