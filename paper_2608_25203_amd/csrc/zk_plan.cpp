@@ -1061,7 +1061,7 @@ std::string validate_plan(const Plan &p, int rows_pad, int rows_base) {
             }
         // a stored spectrum belongs to its task: no other task of the launch
         // stores or reads it, and the task itself reads it only as its kept
-        // one (held in registers; its memory may be other teams' stores)
+        // one (held in registers, or read back by the lanes that stored it)
         std::vector<int> owner(p.nbase, -1);
         for (int k = l.first; k < l.first + l.count; ++k)
           for (int i = 0; i < p.tasks[k].no; ++i) {

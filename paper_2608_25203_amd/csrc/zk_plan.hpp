@@ -41,7 +41,7 @@ struct PlanParams {
   double eps;
   bool taper, filt;
   int real_bytes = 8;  // bytes of one real in the transforms (8: FP64, 4: FP32)
-  bool separate_lifts = false;  // also plan step_lift (the plan checker compares it with the fused form)
+  bool separate_lifts = false;  // also plan step_lift (zk_plan_check: the fused form against separate lifts)
 };
 
 struct Plan {

@@ -85,8 +85,9 @@ struct ColOut {
   int32_t t0, nt;     // terms [t0, t0 + nt)
   double lift_coef;   // extra factor applied before the lift (1/N)
   uint32_t lift_sym;  // depth-lift factors (SYM_COUPLE, SYM_LAYER_*) applied to the lifted copy only, or 0
-  uint32_t keep;      // 1: the stored combination (dst_base) takes X's registers, so that later
-                      // terms that name its spectrum read no memory (none reads X any more)
+  uint32_t keep;      // 1: later terms of the task may name the stored spectrum (dst_base), and none
+                      // reads X any more: FP64 passes hold the combination in X's registers, FP32
+                      // passes read back what each lane stored
 };
 
 // A column task folds up to kMaxFolds mixed fields (forward y-FFT, band

@@ -61,6 +61,6 @@ def test_broken_plan_is_refused(exe, what, answer):
     assert subprocess.run([exe, what], check=True, capture_output=True, text=True).stdout == answer
 
 
-def test_separate_lifts_are_planned_for_the_checker_only(exe):
+def test_separate_lifts_are_planned_on_request_only(exe):
     """The library's steps lift in their last launch; no call runs step_lift."""
     assert subprocess.run([exe, "step_lift"], check=True, capture_output=True, text=True).stdout == "0 1"
