@@ -569,6 +569,7 @@ int zk_set_option(zk_ctx *c, int key, double v) {
     case ZK_OPT_PRECISION:
       if (v != 32.0 && v != 64.0) return fail(c, ZK_EINVAL, "precision must be 32 or 64");
       if (c->bound && (int)v != c->precision) return fail(c, ZK_EINVAL, "set precision before zk_bind");
+      if ((int)v == c->precision) break;  // the layout (a plan) stands; so below
       c->precision = (int)v;
       c->pp.real_bytes = c->precision == 32 ? 4 : 8;
       compute_layout(c);
@@ -593,6 +594,7 @@ int zk_set_option(zk_ctx *c, int key, double v) {
       if (c->bound && (int)v != c->bc) return fail(c, ZK_EINVAL, "set the boundary before zk_bind");
       if (v == ZK_BC_REFLECT && (!axis_len_ok(2 * c->unx) || !axis_len_ok(2 * c->uny)))
         return fail(c, ZK_EINVAL, "reflecting walls double the grid: 2 nx and 2 ny must be built lengths");
+      if ((int)v == c->bc) break;
       c->bc = (int)v;
       c->pp.nx = c->bc ? 2 * c->unx : c->unx;
       c->pp.ny = c->bc ? 2 * c->uny : c->uny;
@@ -603,6 +605,7 @@ int zk_set_option(zk_ctx *c, int key, double v) {
     case ZK_OPT_INTEGRATOR:
       if (v != ZK_INTEGRATOR_RK4 && v != ZK_INTEGRATOR_IFAB2) return fail(c, ZK_EINVAL, "unknown integrator");
       if (c->bound && (int)v != c->integrator) return fail(c, ZK_EINVAL, "set the integrator before zk_bind");
+      if ((int)v == c->integrator) break;
       c->integrator = (int)v;
       compute_layout(c);
       break;

@@ -1062,7 +1062,7 @@ std::string validate_plan(const Plan &p, int rows_pad, int rows_base) {
         // a stored spectrum belongs to its task: no other task of the launch
         // stores or reads it, and the task itself reads it only as its kept
         // one (held in registers, or read back by the lanes that stored it)
-        std::vector<int> owner(p.nbase, -1);
+        std::vector<int> owner(p.nbase, -1), stored(p.nbase, -1);  // task that stores it; that has stored it
         for (int k = l.first; k < l.first + l.count; ++k)
           for (int i = 0; i < p.tasks[k].no; ++i) {
             const int d = p.outs[p.tasks[k].o0 + i].dst_base;
@@ -1070,7 +1070,6 @@ std::string validate_plan(const Plan &p, int rows_pad, int rows_base) {
             if (d >= 0) owner[d] = k;
           }
         for (int k = l.first; k < l.first + l.count; ++k) {
-          std::vector<char> stored(p.nbase, 0);
           int kept = -1;
           bool sum = true;  // the folded sum is still held
           for (int i = 0; i < p.tasks[k].no; ++i) {
@@ -1080,10 +1079,10 @@ std::string validate_plan(const Plan &p, int rows_pad, int rows_base) {
               if (b < 0 && !sum) return "folded sum read after a kept output";
               if (b < 0) continue;
               if (owner[b] >= 0 && owner[b] != k) return "base spectrum read by another task than its store's";
-              if (stored[b] && b != kept) return "stored spectrum read, but not the kept one";
+              if (stored[b] == k && b != kept) return "stored spectrum read, but not the kept one";
             }
             if (o.dst_base >= 0) {
-              stored[o.dst_base] = 1;
+              stored[o.dst_base] = k;
               if (o.keep) {
                 kept = o.dst_base;
                 sum = false;

@@ -64,3 +64,25 @@ def test_broken_plan_is_refused(exe, what, answer):
 def test_separate_lifts_are_planned_on_request_only(exe):
     """The library's steps lift in their last launch; no call runs step_lift."""
     assert subprocess.run([exe, "step_lift"], check=True, capture_output=True, text=True).stdout == "0 1"
+
+
+def test_options_set_to_their_value_keep_the_layout():
+    """zk_set_option with the value an option has re-plans nothing: a hundred such
+    calls take less than ten that change it (each of those builds a plan)."""
+    import time
+
+    from paper_2608_25203_amd import zk
+
+    c = zk.zk_create(128, 96, 1.0, 1.0, 1.0, 9.81, 5)
+    n = zk.zk_workspace_bytes(c)
+    t0 = time.perf_counter()
+    for _ in range(100):
+        zk.zk_set_option(c, zk.ZK_OPT_PRECISION, 64)
+    t1 = time.perf_counter()
+    assert zk.zk_workspace_bytes(c) == n
+    for k in range(10):
+        zk.zk_set_option(c, zk.ZK_OPT_PRECISION, 64 if k % 2 else 32)
+    t2 = time.perf_counter()
+    assert zk.zk_workspace_bytes(c) == n
+    zk.zk_destroy(c)
+    assert t1 - t0 < t2 - t1
