@@ -66,6 +66,7 @@ def test_separate_lifts_are_planned_on_request_only(exe):
     assert subprocess.run([exe, "step_lift"], check=True, capture_output=True, text=True).stdout == "0 1"
 
 
+@pytest.mark.skipif(not os.path.exists(os.path.join(ROOT, "paper_2608_25203_amd", "libzk.so")), reason="libzk.so not built")
 def test_options_set_to_their_value_keep_the_layout():
     """zk_set_option with the value an option has re-plans nothing: a hundred such
     calls take less than ten that change it (each of those builds a plan)."""
